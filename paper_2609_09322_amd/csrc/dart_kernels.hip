@@ -1230,6 +1230,8 @@ __global__ void __launch_bounds__(256) k_batch(BatchLaunch bl,
     }
 }
 
+#ifndef DART_MARCH_STORE  // (one unit holds the kernels that do not march)
+
 // Zero fill of the tiles a batch does not march (every ray of them misses the
 // grid): four 64-pixel tiles per 256-thread block, each lane one pixel in the
 // tile layout of k_batch, every channel.
@@ -1428,18 +1430,24 @@ __global__ void __launch_bounds__(256) k_read_epoch(StackDev st, int32_t m, Out 
     }
 }
 
+#endif  // DART_MARCH_STORE
+
 // ------------------------------------------------------------------ launchers
 
-static inline unsigned grid_for(uint64_t n, unsigned cap = 1u << 16) {
-    uint64_t b = (n + 255) / 256;
-    if (b < 1) b = 1;
-    if (b > cap) b = cap;
-    return (unsigned)b;
-}
+// The march kernels (k_plain, k_batch) of one storage type and ray precision
+// are a compilation unit of their own (DART_MARCH_STORE, DART_MARCH_F64_RAYS);
+// the unit without those names holds every other kernel and dispatches.
+template <int S, typename R>
+hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long long *step_acc,
+                      hipStream_t s);
+template <int S, typename R>
+hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipStream_t s);
+
+#ifdef DART_MARCH_STORE
 
 template <int S, typename R>
-static hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long long *step_acc,
-                             hipStream_t s) {
+hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long long *step_acc,
+                      hipStream_t s) {
     const dim3 g((unsigned)(((uint64_t)v.width * v.height + 255) / 256)), b(256);
     const bool lab = v.n_blocks > 0, ex = (v.flags & F_EXACT) != 0;
     if constexpr (S != ST_F64) {
@@ -1463,21 +1471,6 @@ static hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long l
     return hipGetLastError();
 }
 
-hipError_t launch_plain(const RayView &v, double *flux_acc, unsigned long long *step_acc,
-                        hipStream_t s) {
-    const bool f64 = (v.flags & F_F64_DDA) != 0;
-    switch (v.st.store) {
-        case ST_F64: return plain_impl<ST_F64, double>(v, flux_acc, step_acc, s);
-        case ST_F32: return f64 ? plain_impl<ST_F32, double>(v, flux_acc, step_acc, s)
-                                : plain_impl<ST_F32, float>(v, flux_acc, step_acc, s);
-        case ST_F16: return f64 ? plain_impl<ST_F16, double>(v, flux_acc, step_acc, s)
-                                : plain_impl<ST_F16, float>(v, flux_acc, step_acc, s);
-        case ST_BF16: return f64 ? plain_impl<ST_BF16, double>(v, flux_acc, step_acc, s)
-                                 : plain_impl<ST_BF16, float>(v, flux_acc, step_acc, s);
-    }
-    return hipErrorInvalidValue;
-}
-
 template <int S, typename R, int SYNC, bool LAB, bool EX, int JP = 0>
 static void batch_launch_k(const BatchLaunch &bl, bool k8, int grid_blocks, hipStream_t s) {
     const dim3 g((unsigned)grid_blocks), b(256);
@@ -1490,7 +1483,7 @@ static void batch_launch_k(const BatchLaunch &bl, bool k8, int grid_blocks, hipS
 }
 
 template <int S, typename R>
-static hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipStream_t s) {
+hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipStream_t s) {
     const bool k8 = (variant & KV_K8) != 0;
     if (variant & KV_VEC) {
         // vector stacks: own marching mode only (no depth sync, labels or
@@ -1539,12 +1532,41 @@ static hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks
     return hipGetLastError();
 }
 
+using MarchRay = std::conditional<DART_MARCH_F64_RAYS != 0, double, float>::type;
+template hipError_t plain_impl<DART_MARCH_STORE, MarchRay>(const RayView &, double *,
+                                                           unsigned long long *, hipStream_t);
+template hipError_t batch_impl<DART_MARCH_STORE, MarchRay>(const BatchLaunch &, int, int,
+                                                           hipStream_t);
+
+#else
+
+static inline unsigned grid_for(uint64_t n, unsigned cap = 1u << 16) {
+    uint64_t b = (n + 255) / 256;
+    if (b < 1) b = 1;
+    if (b > cap) b = cap;
+    return (unsigned)b;
+}
+
+hipError_t launch_plain(const RayView &v, double *flux_acc, unsigned long long *step_acc,
+                        hipStream_t s) {
+    const bool f64 = (v.flags & F_F64_DDA) != 0;
+    switch (v.st.store) {
+        case ST_F64: return plain_impl<ST_F64, double>(v, flux_acc, step_acc, s);
+        // (FP32 stacks always have FP64 ray parameters)
+        case ST_F32: return plain_impl<ST_F32, double>(v, flux_acc, step_acc, s);
+        case ST_F16: return f64 ? plain_impl<ST_F16, double>(v, flux_acc, step_acc, s)
+                                : plain_impl<ST_F16, float>(v, flux_acc, step_acc, s);
+        case ST_BF16: return f64 ? plain_impl<ST_BF16, double>(v, flux_acc, step_acc, s)
+                                 : plain_impl<ST_BF16, float>(v, flux_acc, step_acc, s);
+    }
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch(int store, bool f64, int variant, const BatchLaunch &bl, int grid_blocks,
                         hipStream_t s) {
     switch (store) {
         case ST_F64: return batch_impl<ST_F64, double>(bl, variant, grid_blocks, s);
-        case ST_F32: return f64 ? batch_impl<ST_F32, double>(bl, variant, grid_blocks, s)
-                                : batch_impl<ST_F32, float>(bl, variant, grid_blocks, s);
+        case ST_F32: return batch_impl<ST_F32, double>(bl, variant, grid_blocks, s);
         case ST_F16: return f64 ? batch_impl<ST_F16, double>(bl, variant, grid_blocks, s)
                                 : batch_impl<ST_F16, float>(bl, variant, grid_blocks, s);
         case ST_BF16: return f64 ? batch_impl<ST_BF16, double>(bl, variant, grid_blocks, s)
@@ -1568,8 +1590,7 @@ hipError_t launch_mark(const RayView &v, uint32_t *bitmap, int line_log2, bool m
     const bool mo = moving_only;
     switch (v.st.store) {
         case ST_F64: return mark_impl<ST_F64, double>(v, bitmap, line_log2, mo, s);
-        case ST_F32: return f64 ? mark_impl<ST_F32, double>(v, bitmap, line_log2, mo, s)
-                                : mark_impl<ST_F32, float>(v, bitmap, line_log2, mo, s);
+        case ST_F32: return mark_impl<ST_F32, double>(v, bitmap, line_log2, mo, s);
         case ST_F16: return f64 ? mark_impl<ST_F16, double>(v, bitmap, line_log2, mo, s)
                                 : mark_impl<ST_F16, float>(v, bitmap, line_log2, mo, s);
         case ST_BF16: return f64 ? mark_impl<ST_BF16, double>(v, bitmap, line_log2, mo, s)
@@ -1731,5 +1752,7 @@ hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s
                        (const float4 *)src, n);
     return hipGetLastError();
 }
+
+#endif  // DART_MARCH_STORE
 
 }  // namespace dart
