@@ -1137,10 +1137,24 @@ __device__ __forceinline__ void store_pixel(const RayView &v, int pi, int pj, do
 
 // ------------------------------------------------------------------ kernels
 
+// Adds one wavefront's flux and cell-steps to its slot (every lane is here;
+// wave: any number that differs between wavefronts that run together).
+__device__ __forceinline__ void add_sums(const RenderSums &sums, const RayView &v, uint32_t wave,
+                                         double val, uint32_t ns) {
+    if (!sums.slots) return;
+    const double fs = wave_sum(val);
+    const uint32_t cs = wave_sum_u32(ns);
+    if ((threadIdx.x & 63) == 0 && cs != 0u) {  // (a wavefront without cell-steps has no flux)
+        unsigned long long *p = sums.slots + ((uint64_t)v.acc_index * (sums.mask + 1u) +
+                                              (wave & sums.mask)) * sums.stride;
+        atomicAdd((double *)p, fs * v.ps * v.ps);
+        atomicAdd(p + 1, (unsigned long long)cs);
+    }
+}
+
 // Plain kernel: one thread per pixel in row order, one launch per image.
 template <int S, typename R, bool LAB, bool EX, bool VEC = false, int JP = 0>
-__global__ void __launch_bounds__(256) k_plain(RayView v, double *flux_acc,
-                                               unsigned long long *step_acc) {
+__global__ void __launch_bounds__(256) k_plain(RayView v, RenderSums sums) {
     __shared__ double s_tab[4][2 * EPOCH_TAB_MAX];
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long npix = (long long)v.width * v.height;
@@ -1160,12 +1174,7 @@ __global__ void __launch_bounds__(256) k_plain(RayView v, double *flux_acc,
         if constexpr (VEC)
             for (int c = 1; c < v.n_chan; c++) store_pixel(v, pi, pj, ext[c - 1], c);
     }
-    const double fs = wave_sum(val);
-    const uint32_t cs = wave_sum_u32(ns);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&flux_acc[v.acc_index], fs * v.ps * v.ps);
-        atomicAdd(&step_acc[v.acc_index], (unsigned long long)cs);
-    }
+    add_sums(sums, v, blockIdx.x * 4 + (threadIdx.x >> 6), val, ns);
 }
 
 // Persistent kernel: every wavefront pulls 64-pixel tiles (tile_w x tile_h)
@@ -1192,7 +1201,7 @@ __global__ void __launch_bounds__(256) k_batch(BatchLaunch bl,
         const uint32_t q = (q0 + qi) % nq;
         const uint32_t begin = bl.q_begin[q], end = bl.q_begin[q + 1];
         uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(&bl.head[q], 1u);
+        if (lane == 0) t = atomicAdd(&bl.head[q * bl.head_stride], 1u);
         t = __builtin_amdgcn_readfirstlane(t);
         if (t >= end - begin) {
             qi++;
@@ -1221,12 +1230,7 @@ __global__ void __launch_bounds__(256) k_batch(BatchLaunch bl,
             if constexpr (VEC)
                 for (int c = 1; c < v.n_chan; c++) store_pixel(v, pi, pj, ext[c - 1], c);
         }
-        const double fs = wave_sum(val);
-        const uint32_t cs = wave_sum_u32(ns);
-        if (lane == 0) {
-            atomicAdd(&bl.flux_acc[v.acc_index], fs * v.ps * v.ps);
-            atomicAdd(&bl.step_acc[v.acc_index], (unsigned long long)cs);
-        }
+        add_sums(bl.sums, v, blockIdx.x * 4 + (threadIdx.x >> 6), val, ns);
     }
 }
 
@@ -1438,36 +1442,34 @@ __global__ void __launch_bounds__(256) k_read_epoch(StackDev st, int32_t m, Out 
 // are a compilation unit of their own (DART_MARCH_STORE, DART_MARCH_F64_RAYS);
 // the unit without those names holds every other kernel and dispatches.
 template <int S, typename R>
-hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long long *step_acc,
-                      hipStream_t s);
+hipError_t plain_impl(const RayView &v, const RenderSums &sums, hipStream_t s);
 template <int S, typename R>
 hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipStream_t s);
 
 #ifdef DART_MARCH_STORE
 
 template <int S, typename R>
-hipError_t plain_impl(const RayView &v, double *flux_acc, unsigned long long *step_acc,
-                      hipStream_t s) {
+hipError_t plain_impl(const RayView &v, const RenderSums &sums, hipStream_t s) {
     const dim3 g((unsigned)(((uint64_t)v.width * v.height + 255) / 256)), b(256);
     const bool lab = v.n_blocks > 0, ex = (v.flags & F_EXACT) != 0;
     if constexpr (S != ST_F64) {
         // (the planner gives an emissivity plane only to plain stacks)
         if (v.st.jplane && !lab && v.n_chan == 1) {
             if (v.flags & F_PLANE32) {
-                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 2>), g, b, 0, s, v, flux_acc, step_acc);
-                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 2>), g, b, 0, s, v, flux_acc, step_acc);
+                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 2>), g, b, 0, s, v, sums);
+                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 2>), g, b, 0, s, v, sums);
             } else {
-                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 1>), g, b, 0, s, v, flux_acc, step_acc);
-                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 1>), g, b, 0, s, v, flux_acc, step_acc);
+                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 1>), g, b, 0, s, v, sums);
+                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 1>), g, b, 0, s, v, sums);
             }
             return hipGetLastError();
         }
     }
-    if (v.n_chan > 1) hipLaunchKernelGGL((k_plain<S, R, false, false, true>), g, b, 0, s, v, flux_acc, step_acc);
-    else if (lab && ex) hipLaunchKernelGGL((k_plain<S, R, true, true>), g, b, 0, s, v, flux_acc, step_acc);
-    else if (lab) hipLaunchKernelGGL((k_plain<S, R, true, false>), g, b, 0, s, v, flux_acc, step_acc);
-    else if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true>), g, b, 0, s, v, flux_acc, step_acc);
-    else hipLaunchKernelGGL((k_plain<S, R, false, false>), g, b, 0, s, v, flux_acc, step_acc);
+    if (v.n_chan > 1) hipLaunchKernelGGL((k_plain<S, R, false, false, true>), g, b, 0, s, v, sums);
+    else if (lab && ex) hipLaunchKernelGGL((k_plain<S, R, true, true>), g, b, 0, s, v, sums);
+    else if (lab) hipLaunchKernelGGL((k_plain<S, R, true, false>), g, b, 0, s, v, sums);
+    else if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true>), g, b, 0, s, v, sums);
+    else hipLaunchKernelGGL((k_plain<S, R, false, false>), g, b, 0, s, v, sums);
     return hipGetLastError();
 }
 
@@ -1533,8 +1535,8 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
 }
 
 using MarchRay = std::conditional<DART_MARCH_F64_RAYS != 0, double, float>::type;
-template hipError_t plain_impl<DART_MARCH_STORE, MarchRay>(const RayView &, double *,
-                                                           unsigned long long *, hipStream_t);
+template hipError_t plain_impl<DART_MARCH_STORE, MarchRay>(const RayView &, const RenderSums &,
+                                                           hipStream_t);
 template hipError_t batch_impl<DART_MARCH_STORE, MarchRay>(const BatchLaunch &, int, int,
                                                            hipStream_t);
 
@@ -1547,17 +1549,16 @@ static inline unsigned grid_for(uint64_t n, unsigned cap = 1u << 16) {
     return (unsigned)b;
 }
 
-hipError_t launch_plain(const RayView &v, double *flux_acc, unsigned long long *step_acc,
-                        hipStream_t s) {
+hipError_t launch_plain(const RayView &v, const RenderSums &sums, hipStream_t s) {
     const bool f64 = (v.flags & F_F64_DDA) != 0;
     switch (v.st.store) {
-        case ST_F64: return plain_impl<ST_F64, double>(v, flux_acc, step_acc, s);
+        case ST_F64: return plain_impl<ST_F64, double>(v, sums, s);
         // (FP32 stacks always have FP64 ray parameters)
-        case ST_F32: return plain_impl<ST_F32, double>(v, flux_acc, step_acc, s);
-        case ST_F16: return f64 ? plain_impl<ST_F16, double>(v, flux_acc, step_acc, s)
-                                : plain_impl<ST_F16, float>(v, flux_acc, step_acc, s);
-        case ST_BF16: return f64 ? plain_impl<ST_BF16, double>(v, flux_acc, step_acc, s)
-                                 : plain_impl<ST_BF16, float>(v, flux_acc, step_acc, s);
+        case ST_F32: return plain_impl<ST_F32, double>(v, sums, s);
+        case ST_F16: return f64 ? plain_impl<ST_F16, double>(v, sums, s)
+                                : plain_impl<ST_F16, float>(v, sums, s);
+        case ST_BF16: return f64 ? plain_impl<ST_BF16, double>(v, sums, s)
+                                 : plain_impl<ST_BF16, float>(v, sums, s);
     }
     return hipErrorInvalidValue;
 }

@@ -107,9 +107,12 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     if (st != DART_OK) return st;
     size_t nv = 0, nt = 0;
     assign_offsets(groups, &nv, &nt);
-    const size_t acc_words = 2 * (size_t)n + 4 * groups.size();
-    const size_t desc_off = align256(acc_words * sizeof(unsigned long long));
+    // (a batch that fits only with its sums side by side keeps them so)
     const size_t desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
+    SumLayout lay(n, groups.size());
+    if (align256(lay.words() * 8) + desc_bytes > (size_t)DART_NOALLOC_SCRATCH_BYTES)
+        lay = SumLayout(n, groups.size(), true);
+    const size_t desc_off = align256(lay.words() * 8);
     if (desc_off + desc_bytes > (size_t)DART_NOALLOC_SCRATCH_BYTES)
         return fail(DART_E_INVAL,
                     "%d views in %zu tiles need %zu bytes of scratch; the fixed scratch holds %zu "
@@ -124,6 +127,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     std::vector<unsigned char> host(desc_bytes);
     pack_descriptors(groups, nv, host.data());
     unsigned long long *acc = (unsigned long long *)sc->ptr;
+    const bool sums = flux_out || steps_out;
     const RayView *dviews = (const RayView *)(sc->ptr + desc_off);
     const Tile *dtiles = (const Tile *)(sc->ptr + desc_off + nv * sizeof(RayView));
     // Stream-ordered after earlier work that reads the scratch; the wait makes
@@ -132,19 +136,18 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
                                   hipMemcpyHostToDevice, stream),
                    "H2D descriptors");
     HIP_TRY_STATUS(hipStreamSynchronize(stream), "sync");
-    HIP_TRY_STATUS(enqueue_plan(groups, n, acc, dviews, dtiles, tun, device, stream),
+    HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, dviews, dtiles, tun, device, stream),
                    "batch kernels");
     for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
-    if (flux_out || steps_out) {
-        std::vector<unsigned long long> h(2 * (size_t)n);
-        HIP_TRY_STATUS(hipMemcpyAsync(h.data(), acc, h.size() * sizeof(unsigned long long),
+    if (sums) {
+        std::vector<unsigned long long> h(lay.sum_words());
+        HIP_TRY_STATUS(hipMemcpyAsync(h.data(), acc + lay.heads_words(), h.size() * 8,
                                       hipMemcpyDeviceToHost, stream),
                        "D2H accumulators");
         HIP_TRY_STATUS(hipStreamSynchronize(stream), "sync");
-        for (int32_t i = 0; i < n; i++) {
-            if (flux_out) memcpy(&flux_out[i], &h[i], sizeof(double));
-            if (steps_out) steps_out[i] = h[n + i];
-        }
+        for (int32_t i = 0; i < n; i++)
+            lay.total(h.data(), i, flux_out ? flux_out + i : nullptr,
+                      steps_out ? steps_out + i : nullptr);
     }
     return DART_OK;
 }

@@ -96,6 +96,31 @@ struct Group {
     uint32_t q_begin[MAX_QUEUES + 1] = {};  // chunk bounds in `tiles`
 };
 
+// Queue heads and sum slots of a launch of n views in some groups, in 64-bit
+// words from the start of one block: first every group's MAX_QUEUES heads, then
+// the slots of view 0, 1, ..  Heads and slots have a cache line each (16 words)
+// where several wavefronts would otherwise add to one line at a time: 64 slots
+// for a single view, fewer for more views (whose wavefronts are spread over the
+// views already; the slots of a launch take at most 64 KiB until each view is
+// down to one).  compact: heads and slots side by side, one slot per view.
+struct SumLayout {
+    size_t groups, n;
+    uint32_t slots, stride, head_stride;  // slots per view; words; heads: 32-bit words
+    SumLayout(size_t n_views, size_t n_groups, bool compact = false);
+    size_t head_words() const { return MAX_QUEUES * (size_t)head_stride / 2; }
+    size_t heads_words() const { return groups * head_words(); }
+    size_t sum_words() const { return n * slots * stride; }
+    size_t words() const { return heads_words() + sum_words(); }
+    uint32_t *head(unsigned long long *block, size_t group) const {
+        return (uint32_t *)(block + group * head_words());
+    }
+    RenderSums sums(unsigned long long *block) const {
+        return RenderSums{block + heads_words(), slots - 1u, stride};
+    }
+    // A view's totals from a host copy of the slots (sum_words() words).
+    void total(const unsigned long long *h, size_t view, double *flux, uint64_t *steps) const;
+};
+
 dart_status plan_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
                        void *const *images, const dart_tuning &tun, std::vector<Group> &groups);
 
@@ -105,8 +130,10 @@ struct Workspace {
     hipStream_t stream = nullptr;
     int device = 0;
     std::mutex mu;
-    unsigned long long *acc = nullptr;  // flux[n] (as double bits), steps[n], queue heads
+    unsigned long long *acc = nullptr;  // queue heads and sum slots (SumLayout)
     size_t acc_cap = 0;
+    void *sums_host = nullptr;          // pinned: the sum slots read back
+    size_t sums_host_cap = 0;
     RayView *views = nullptr;
     size_t views_cap = 0;
     Tile *tiles = nullptr;
@@ -117,8 +144,7 @@ struct Workspace {
     size_t stage_cap = 0;
     hipEvent_t stage_done{};
     bool stage_ready = false;
-    hipGraphExec_t graph_exec = nullptr;
-    std::vector<uint8_t> graph_key;
+    hipGraphExec_t graph_exec[2] = {nullptr, nullptr};  // without / with sums
     // the last batch plan (descriptors already on the device), replayed when
     // the next call has the same key
     std::vector<Group> plan_groups;
@@ -128,10 +154,12 @@ struct Workspace {
 
 Workspace *get_workspace(hipStream_t stream);
 hipError_t ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_u64,
-                      size_t n_queue_slots);
-hipError_t enqueue_plan(const std::vector<Group> &groups, int32_t n, unsigned long long *acc,
-                        const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,
-                        int device, hipStream_t stream);
+                      size_t acc_words);
+// sums: whether the launch adds up flux and cell-steps.
+hipError_t enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
+                        unsigned long long *acc, bool sums, const RayView *dviews,
+                        const Tile *dtiles, const dart_tuning &tun, int device,
+                        hipStream_t stream);
 void assign_offsets(std::vector<Group> &groups, size_t *n_views, size_t *n_tiles);
 void pack_descriptors(const std::vector<Group> &groups, size_t n_views, void *dst);
 

@@ -798,16 +798,42 @@ static hipError_t grow_host(void *&p, size_t &cap, size_t need) {
 }
 
 static void drop_graph(Workspace *ws) {
-    if (ws->graph_exec) (void)hipGraphExecDestroy(ws->graph_exec);
-    ws->graph_exec = nullptr;
-    ws->graph_key.clear();
+    for (hipGraphExec_t &g : ws->graph_exec) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
     ws->plan_ready = false;
     ws->plan_key.clear();
     ws->plan_groups.clear();
 }
 
+SumLayout::SumLayout(size_t n_views, size_t n_groups, bool compact)
+    : groups(n_groups), n(n_views), slots(1), stride(16), head_stride(32) {
+    if (compact) {
+        stride = 2;
+        head_stride = 1;
+        return;
+    }
+    while (slots < 64 && 2 * slots * n <= 512) slots *= 2;  // (512 lines: 64 KiB)
+}
+
+void SumLayout::total(const unsigned long long *h, size_t view, double *flux,
+                      uint64_t *steps) const {
+    double f = 0.0;
+    uint64_t c = 0;
+    for (uint32_t k = 0; k < slots; k++) {
+        const unsigned long long *p = h + (view * slots + k) * stride;
+        double d;
+        memcpy(&d, &p[0], sizeof(d));
+        f += d;
+        c += p[1];
+    }
+    if (flux) *flux = f;
+    if (steps) *steps = c;
+}
+
 hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_bytes,
-                            size_t n_queues) {
+                            size_t acc_words) {
     hipError_t e;
     // a captured graph holds these pointers: any reallocation invalidates it
     const void *before[4] = {ws->acc, ws->views, ws->tiles, ws->img};
@@ -815,8 +841,8 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
         e = hipEventSynchronize(ws->stage_done);
         if (e != hipSuccess) return e;
     }
-    if ((e = grow_dev(ws->acc, ws->acc_cap, 2 * std::max(n_views, (size_t)1) + n_queues)) != hipSuccess)
-        return e;
+    if ((e = grow_dev(ws->acc, ws->acc_cap, acc_words)) != hipSuccess) return e;
+    if ((e = grow_host(ws->sums_host, ws->sums_host_cap, acc_words * 8)) != hipSuccess) return e;
     if ((e = grow_dev(ws->views, ws->views_cap, std::max(n_views, (size_t)1))) != hipSuccess) return e;
     if ((e = grow_dev(ws->tiles, ws->tiles_cap, std::max(n_tiles, (size_t)1))) != hipSuccess) return e;
     if (img_bytes && (e = grow_dev(ws->img, ws->img_cap, img_bytes)) != hipSuccess) return e;
@@ -849,24 +875,22 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     std::lock_guard<std::mutex> g(ws->mu);
     const bool dev_img = (v->flags & DART_DEVICE_PTRS) != 0;
     const size_t img_bytes = (size_t)rv.n_chan * v->width * v->height * (rv.out_f64 ? 8 : 4);
-    HIP_TRY(ws_reserve(ws, 1, 0, dev_img ? 0 : img_bytes / 8 + 1, 0), "workspace");
+    const SumLayout lay(1, 0);
+    const bool sums = flux_out || steps_out;
+    HIP_TRY(ws_reserve(ws, 1, 0, dev_img ? 0 : img_bytes / 8 + 1, lay.words()), "workspace");
     rv.image = dev_img ? image : (void *)ws->img;
     rv.acc_index = 0;
-    double *flux_acc = (double *)ws->acc;
-    unsigned long long *step_acc = ws->acc + 1;
-    HIP_TRY(launch_fill_u64(ws->acc, 2, 0ull, stream), "clear accumulators");
-    HIP_TRY(launch_plain(rv, flux_acc, step_acc, stream), "render kernel");
+    if (sums) HIP_TRY(launch_fill_u64(ws->acc, lay.words(), 0ull, stream), "clear accumulators");
+    HIP_TRY(launch_plain(rv, sums ? lay.sums(ws->acc) : RenderSums{}, stream), "render kernel");
     note_use(s, stream);
     if (!dev_img)
         HIP_TRY(hipMemcpyAsync(image, ws->img, img_bytes, hipMemcpyDeviceToHost, stream), "D2H image");
-    if (flux_out || steps_out || !dev_img) {
-        unsigned long long acc[2];
-        HIP_TRY(hipMemcpyAsync(acc, ws->acc, sizeof(acc), hipMemcpyDeviceToHost, stream), "D2H acc");
+    if (sums)
+        HIP_TRY(hipMemcpyAsync(ws->sums_host, ws->acc, lay.sum_words() * 8, hipMemcpyDeviceToHost,
+                               stream), "D2H acc");
+    if (sums || !dev_img) {
         HIP_TRY(hipStreamSynchronize(stream), "sync");
-        double f;
-        memcpy(&f, &acc[0], sizeof(f));
-        if (flux_out) *flux_out = f;
-        if (steps_out) *steps_out = acc[1];
+        if (sums) lay.total((const unsigned long long *)ws->sums_host, 0, flux_out, steps_out);
     }
     return DART_OK;
 }
@@ -1297,13 +1321,13 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
     return DART_OK;
 }
 
-// Enqueues clear + persistent kernels of every group.  Accumulator layout:
-// flux[n] (double bits), steps[n], then 4 slots (8 x uint32 queue heads) per
-// group; dviews / dtiles hold the groups' descriptors at their offsets.
-hipError_t dart::enqueue_plan(const std::vector<Group> &groups, int32_t n,
-                              unsigned long long *acc, const RayView *dviews, const Tile *dtiles,
-                              const dart_tuning &tun, int device, hipStream_t stream) {
-    hipError_t e = launch_fill_u64(acc, 2 * (size_t)n + 4 * groups.size(), 0ull, stream);
+// Enqueues clear + persistent kernels of every group; dviews / dtiles hold the
+// groups' descriptors at their offsets.
+hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
+                              unsigned long long *acc, bool sums, const RayView *dviews,
+                              const Tile *dtiles, const dart_tuning &tun, int device,
+                              hipStream_t stream) {
+    hipError_t e = launch_fill_u64(acc, sums ? lay.words() : lay.heads_words(), 0ull, stream);
     if (e != hipSuccess) return e;
     const int cus = device_cus(device);
     const int blocks = std::max(1, cus * tun.waves_per_cu / 4);
@@ -1318,11 +1342,11 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, int32_t n,
         bl.views = dviews + g.view_off;
         bl.tiles = dtiles + g.tile_off;
         bl.n_tiles = (uint32_t)g.q_begin[g.n_queues];
-        bl.head = (uint32_t *)(acc + 2 * (size_t)n + 4 * gi);
+        bl.head = lay.head(acc, gi);
+        bl.head_stride = lay.head_stride;
         bl.n_queues = g.n_queues;
         for (uint32_t q = 0; q <= g.n_queues; q++) bl.q_begin[q] = g.q_begin[q];
-        bl.flux_acc = (double *)acc;
-        bl.step_acc = acc + n;
+        bl.sums = sums ? lay.sums(acc) : RenderSums{};
         const int variant = g.vec ? (KV_VEC | (tun.cells_per_batch == 8 ? KV_K8 : 0))
                                   : (tun.depth_sync > 0 ? KV_SYNC : 0) |
                                         (g.labelled ? KV_LABELLED : 0) | (g.exact ? KV_EXACT : 0) |
@@ -1446,7 +1470,8 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         if (st != DART_OK) return st;
         size_t nv = 0, nt = 0;
         assign_offsets(groups, &nv, &nt);
-        HIP_TRY(ws_reserve(ws, std::max(nv, (size_t)n), nt, img_bytes / 8 + 1, groups.size() * 4),
+        HIP_TRY(ws_reserve(ws, std::max(nv, (size_t)n), nt, img_bytes / 8 + 1,
+                           SumLayout(n, groups.size()).words()),
                 "workspace");
         for (Group &gr : groups)
             for (RayView &rv : gr.views)
@@ -1465,29 +1490,33 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         ws->plan_groups = groups;
         ws->plan_key = key;
         ws->plan_ready = true;
-        if (use_graph) {
-            hipGraph_t graph = nullptr;
-            HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
-            hipError_t e = enqueue_plan(groups, n, ws->acc, ws->views, ws->tiles, tun, ws->device, stream);
-            hipError_t e2 = hipStreamEndCapture(stream, &graph);
-            if (e != hipSuccess) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return hip_fail(e, "capture batch");
-            }
-            if (e2 != hipSuccess) return hip_fail(e2, "end capture");
-            hipGraphExec_t exec = nullptr;
-            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) return hip_fail(e, "instantiate graph");
-            ws->graph_exec = exec;
-            ws->graph_key = key;
+    }
+    const SumLayout lay(n, ws->plan_groups.size());
+    const bool sums = flux_out || steps_out;
+    hipGraphExec_t &exec = ws->graph_exec[sums ? 1 : 0];
+    if (use_graph && !exec) {
+        hipGraph_t graph = nullptr;
+        HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
+        hipError_t e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->views, ws->tiles, tun,
+                                    ws->device, stream);
+        hipError_t e2 = hipStreamEndCapture(stream, &graph);
+        if (e != hipSuccess) {
+            if (graph) (void)hipGraphDestroy(graph);
+            return hip_fail(e, "capture batch");
+        }
+        if (e2 != hipSuccess) return hip_fail(e2, "end capture");
+        e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(graph);
+        if (e != hipSuccess) {
+            exec = nullptr;
+            return hip_fail(e, "instantiate graph");
         }
     }
-    if (use_graph && ws->graph_exec)
-        HIP_TRY(hipGraphLaunch(ws->graph_exec, stream), "graph launch");
+    if (use_graph)
+        HIP_TRY(hipGraphLaunch(exec, stream), "graph launch");
     else
-        HIP_TRY(enqueue_plan(ws->plan_groups, n, ws->acc, ws->views, ws->tiles, tun, ws->device,
-                             stream),
+        HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->views, ws->tiles, tun,
+                             ws->device, stream),
                 "batch kernels");
     for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
     bool any_host = false;
@@ -1501,16 +1530,15 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
                     "D2H image");
         }
     }
-    if (flux_out || steps_out || any_host) {
-        std::vector<unsigned long long> acc(2 * (size_t)n);
-        HIP_TRY(hipMemcpyAsync(acc.data(), ws->acc, acc.size() * sizeof(unsigned long long),
+    if (sums)
+        HIP_TRY(hipMemcpyAsync(ws->sums_host, ws->acc + lay.heads_words(), lay.sum_words() * 8,
                                hipMemcpyDeviceToHost, stream),
                 "D2H acc");
+    if (sums || any_host) {
         HIP_TRY(hipStreamSynchronize(stream), "sync");
-        for (int32_t i = 0; i < n; i++) {
-            if (flux_out) memcpy(&flux_out[i], &acc[i], sizeof(double));
-            if (steps_out) steps_out[i] = acc[n + i];
-        }
+        for (int32_t i = 0; sums && i < n; i++)
+            lay.total((const unsigned long long *)ws->sums_host, i,
+                      flux_out ? flux_out + i : nullptr, steps_out ? steps_out + i : nullptr);
     }
     return DART_OK;
 }

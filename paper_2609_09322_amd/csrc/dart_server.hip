@@ -103,6 +103,7 @@ struct Wave {
     std::vector<Req *> reqs;
     int stream_idx = 0;
     bool done = false;
+    bool compact = false;        // layout of its sums (SumLayout)
     Clock::time_point t_plan;    // the scheduler starts planning the wave
     Clock::time_point t_launch;  // its device work is enqueued
     Clock::time_point t_done;    // the completion callback ran
@@ -174,12 +175,10 @@ static void retire(dart_server *srv, Wave *w) {
         srv->stream_waited[k] = !srv->queue.empty();
     }
     const unsigned long long *acc_h = (const unsigned long long *)srv->desc_host[w->stream_idx];
+    const SumLayout lay(n, 0, w->compact);
     for (size_t i = 0; i < n; i++) {
         Req *r = w->reqs[i];
-        double f;
-        memcpy(&f, &acc_h[i], sizeof(f));
-        r->flux = f;
-        r->steps = acc_h[n + i];
+        lay.total(acc_h, i, &r->flux, &r->steps);
         if (r->host_dest)
             memcpy(r->dest, (char *)srv->host_base + r->host_off, r->img_bytes);
         r->latency_ms =
@@ -252,7 +251,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     w->stream_idx = sidx;
     w->t_plan = Clock::now();
     // 256-B alignment of the accumulators + 64 B per request (flux, steps and
-    // queue heads) on top of each request's descriptor bound
+    // queue heads, side by side) on top of each request's descriptor bound
     size_t bound = 320;
     while (!srv->queue.empty() && srv->queue.front()->admitted &&
            (w->reqs.empty() || bound + srv->queue.front()->desc_bound <= srv->desc_cap)) {
@@ -288,10 +287,14 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     }
     size_t nv = 0, nt = 0;
     assign_offsets(groups, &nv, &nt);
-    const size_t acc_u64 = 2 * (size_t)n + 4 * groups.size();
     const size_t desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
     const size_t acc_off = (desc_bytes + 255) & ~(size_t)255;
-    if (acc_off + acc_u64 * 8 > srv->desc_cap) {
+    SumLayout lay(n, groups.size());
+    if (acc_off + lay.words() * 8 > srv->desc_cap) {
+        w->compact = true;
+        lay = SumLayout(n, groups.size(), true);
+    }
+    if (acc_off + lay.words() * 8 > srv->desc_cap) {
         // cannot happen: the per-request bounds cover the plan
         fail_wave(srv, w.get(), DART_E_INTERNAL, "wave descriptors exceed their buffer");
         return;
@@ -318,7 +321,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         e = hipMemcpyAsync(ddesc, hstage, desc_bytes, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kbegin[sidx], stream);
     if (e == hipSuccess)
-        e = enqueue_plan(groups, n, dacc, (const RayView *)ddesc,
+        e = enqueue_plan(groups, lay, dacc, true, (const RayView *)ddesc,
                          (const Tile *)(ddesc + nv * sizeof(RayView)), tun, srv->device, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kend[sidx], stream);
     for (int32_t i = 0; i < n && e == hipSuccess; i++) {
@@ -331,7 +334,8 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     }
     // the flux and step accumulators overwrite the (already consumed) descriptor staging
     if (e == hipSuccess)
-        e = hipMemcpyAsync(hstage, dacc, (size_t)n * 16, hipMemcpyDeviceToHost, stream);
+        e = hipMemcpyAsync(hstage, dacc + lay.heads_words(), lay.sum_words() * 8,
+                           hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_end[sidx], stream);
     if (e == hipSuccess) {
         for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);

@@ -332,7 +332,9 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     }
     ST_TRY(grow((void **)&s->d_views, &s->views_cap, std::max<size_t>(nv, 1) * sizeof(RayView)), "views");
     ST_TRY(grow((void **)&s->d_tiles, &s->tiles_cap, std::max<size_t>(nt, 1) * sizeof(Tile)), "tiles");
-    const size_t acc_n = 2 * (size_t)n + 4 * std::max<size_t>(groups.size(), 1);
+    const SumLayout lay(n, groups.size());
+    const size_t acc_n = lay.words();
+    const bool sums = flux_out || steps_out;
     ST_TRY(grow((void **)&s->acc, &s->acc_cap, acc_n * 8), "accumulators");
     if (nv > 0) {
         pack_descriptors(groups, nv, s->h_desc);
@@ -400,11 +402,11 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
             bl.views = s->d_views + g.view_off;
             bl.tiles = s->d_tiles + g.tile_off;
             bl.n_tiles = (uint32_t)g.tiles.size();
-            bl.head = (uint32_t *)(s->acc + 2 * (size_t)n + 4 * gi);
+            bl.head = lay.head(s->acc, gi);
+            bl.head_stride = lay.head_stride;
             bl.n_queues = g.n_queues;
             for (uint32_t q = 0; q <= g.n_queues; q++) bl.q_begin[q] = g.q_begin[q];
-            bl.flux_acc = (double *)s->acc;
-            bl.step_acc = s->acc + n;
+            bl.sums = sums ? lay.sums(s->acc) : RenderSums{};
             const int variant = (tun.depth_sync > 0 ? KV_SYNC : 0) | (g.labelled ? KV_LABELLED : 0) |
                                 (tun.cells_per_batch == 8 ? KV_K8 : 0);
             ST_TRY(launch_batch(g.store, g.f64, variant, bl, blocks, stream), "interval kernel");
@@ -416,8 +418,10 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     for (int32_t i = 0; i < n; i++)
         if (!(views[i].flags & DART_DEVICE_PTRS))
             ST_TRY(hipMemcpyAsync(images[i], dimg[i], img_bytes[i], hipMemcpyDeviceToHost, stream), "D2H image");
-    std::vector<unsigned long long> acc(2 * (size_t)n), bad(M);
-    ST_TRY(hipMemcpyAsync(acc.data(), s->acc, acc.size() * 8, hipMemcpyDeviceToHost, stream), "D2H acc");
+    std::vector<unsigned long long> acc(lay.sum_words()), bad(M);
+    if (sums)
+        ST_TRY(hipMemcpyAsync(acc.data(), s->acc + lay.heads_words(), acc.size() * 8,
+                              hipMemcpyDeviceToHost, stream), "D2H acc");
     ST_TRY(hipStreamSynchronize(s->copy), "sync copy stream");
     ST_TRY(hipMemcpyAsync(bad.data(), s->err, M * 8, hipMemcpyDeviceToHost, stream), "D2H err");
     ST_TRY(hipStreamSynchronize(stream), "sync");
@@ -429,10 +433,9 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
                         (unsigned long long)((c / rd.n[0]) % rd.n[1]),
                         (unsigned long long)(c / ((uint64_t)rd.n[0] * rd.n[1])));
         }
-    for (int32_t i = 0; i < n; i++) {
-        if (flux_out) memcpy(&flux_out[i], &acc[i], sizeof(double));
-        if (steps_out) steps_out[i] = acc[n + i];
-    }
+    for (int32_t i = 0; sums && i < n; i++)
+        lay.total(acc.data(), i, flux_out ? flux_out + i : nullptr,
+                  steps_out ? steps_out + i : nullptr);
     s->last.epochs_loaded = (int32_t)order.size();
     s->last.epochs_skipped = M - (int32_t)order.size();
     s->last.intervals = (int32_t)iv.size();
