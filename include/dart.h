@@ -259,7 +259,9 @@ typedef struct {
     dart_dtype out_dtype;
 } dart_view;
 
-/* Plain kernel: one launch, one thread per pixel.
+/* Plain kernel: one launch; a thread marches a pixel's ray, or one of the 2 or 4
+ * depth segments that the rays of small views are cut into (the pixel is the
+ * segments' sums added in order, here and in the batched form alike).
  *   image      [height][width] of out_dtype; host memory unless the view has
  *              DART_DEVICE_PTRS (then stream-ordered)
  *   flux_out   nullable host pointer: sum I ps^2

@@ -65,6 +65,13 @@ struct RayView {
     int32_t fixed_m;        // NO_LOOKBACK: epoch bracket at t_obs (-1: t_obs outside coverage)
     double fixed_w;         // NO_LOOKBACK: weight of epoch fixed_m + 1
     float fixed_wf;         // the same rounded to FP32 (read as such by FP32 walks)
+    // Depth segments: a ray's sum is made of 1 << seg_log2 partial sums over
+    // consecutive parts of its chord, added in order; which cells a part holds
+    // depends on the view and the ray alone.  seg_items: the parts of a tile are
+    // queued on their own (their sums meet in BatchLaunch::parts and k_finish
+    // adds them); 0: a lane marches its ray's parts one after the other.  The
+    // pixels are the same bit for bit.
+    int16_t seg_log2, seg_items;
     double sync_gap;        // batched kernel: depth-synchronous horizon (length), 0 = off
     void *image;            // [height][width] float or double (device)
     int32_t out_f64;
@@ -80,6 +87,9 @@ struct RayView {
     int32_t n_chan;
     const void *chan_data[3];
 };
+
+constexpr int TILE_SEG_SHIFT = 28;  // Tile::view: the view, and above it the depth segment
+constexpr int MAX_SEG_LOG2 = 2;
 
 struct Tile {
     uint32_t view;
@@ -113,6 +123,10 @@ struct BatchLaunch {
     uint32_t n_queues;      // at most MAX_QUEUES
     uint32_t q_begin[9];    // queue q holds tiles [q_begin[q], q_begin[q + 1])
     RenderSums sums;
+    // partial sums of the tiles queued by depth segment: channel c of lane k of
+    // queue position t at (t * C + c) * 64 + k, C = 4 for launches of vector
+    // stacks, else 1
+    double *parts;
 };
 
 // Host-side launchers (dart_kernels.hip).
@@ -151,7 +165,11 @@ hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);
-// Writes 0 to every pixel (and channel) of n tiles of the given views.
-hipError_t launch_clear_tiles(const RayView *views, const Tile *tiles, uint32_t n, hipStream_t s);
+// After a batched launch: adds up the parts of the tiles among the n_queued
+// queue positions that were queued by segment (parts null: there are none) and
+// stores their pixels, and writes 0 to every pixel (and channel) of the n_clear
+// tiles that follow them.
+hipError_t launch_finish(const RayView *views, const Tile *tiles, uint32_t n_queued,
+                         uint32_t n_clear, const double *parts, hipStream_t s);
 
 }  // namespace dart

@@ -294,6 +294,71 @@ __device__ __forceinline__ uint32_t off_z(const StackDev &st, int z) {
            ((uint32_t)z >> c) * ((((uint32_t)st.nb[1] * (uint32_t)st.nb[0]) << L) - (1u << L));
 }
 
+// Depth segments.  The chord [entry, stop) of a ray is divided in 1 << seg_log2
+// equal parts.  Part k holds the cells that a walk enters at or after E(k) and
+// before E(k + 1), where E(k) is the entry of the cell around division k: the
+// last plane at or before it, from the walk's own crossing values, so the part
+// that ends there and the part that starts there agree on it and every cell is
+// in one part, with the chord the whole walk gives it.
+// Crossings of one axis (n cells) at or before s: how many of the planes
+// fma(c, d, b), c = 0, 1, .., lie there (the count a walk has after taking
+// them), and in *e the last of them if it is later.  The first guess uses an
+// approximate reciprocal; the loops settle it on the planes themselves.  (s lies
+// before the ray's stop, hence before the grid face ahead, so the count stays
+// inside the grid.)  A parallel axis (b infinite, d 0) has none.
+template <typename R>
+__device__ __forceinline__ R crossings_to(R s, R b, R d, int n, R *e) {
+    const R guess = floor((s - b) * (R)__builtin_amdgcn_rcpf((float)d)) + (R)1;
+    R c = d > (R)0 ? fmin(fmax(guess, (R)0), (R)n) : (R)0;
+    while (c < (R)n && fma(c, d, b) <= s) c += (R)1;
+    while (c > (R)0 && fma(c - (R)1, d, b) > s) c -= (R)1;
+    if (c > (R)0) *e = fmax(*e, fma(c - (R)1, d, b));
+    return c;
+}
+
+// Moves a ray that stands at its start (in cell idx) to part k: its stop, and
+// its position.  False when the part holds no cell.
+template <typename R>
+__device__ __forceinline__ bool seek_part(const RayView &v, const StackDev &st, int k,
+                                          const int *idx, Ray<R> &r) {
+    const R start = r.entry, len = (r.stop - start) * ldexp((R)1, -v.seg_log2);
+    if (k + 1 < (1 << v.seg_log2)) {
+        const R s = fma((R)(k + 1), len, start);
+        R e = start;
+        (void)crossings_to(s, r.b0, r.d0, st.n[0], &e);
+        (void)crossings_to(s, r.b1, r.d1, st.n[1], &e);
+        (void)crossings_to(s, r.b2, r.d2, st.n[2], &e);
+        r.stop = fmin(r.stop, e);
+    }
+    if (k > 0) {
+        const R s = fma((R)k, len, start);
+        R e = start;
+        r.c0 = crossings_to(s, r.b0, r.d0, st.n[0], &e);
+        r.c1 = crossings_to(s, r.b1, r.d1, st.n[1], &e);
+        r.c2 = crossings_to(s, r.b2, r.d2, st.n[2], &e);
+        r.entry = e;
+        r.sa0 = fma(r.c0, r.d0, r.b0);
+        r.sa1 = fma(r.c1, r.d1, r.b1);
+        r.sa2 = fma(r.c2, r.d2, r.b2);
+        const int k0 = (int)r.c0, k1 = (int)r.c1, k2 = (int)r.c2;
+        r.off = off_x(st, v.shat[0] < 0.0 ? idx[0] - k0 : idx[0] + k0) +
+                off_y(st, v.shat[1] < 0.0 ? idx[1] - k1 : idx[1] + k1) +
+                off_z(st, v.shat[2] < 0.0 ? idx[2] - k2 : idx[2] + k2);
+    }
+    return r.entry < r.stop;
+}
+
+// x / cell, as a product with the exact inverse where cell is a power of two
+// (the usual unit cells among them): the same value without the division.  The
+// test is uniform over the wavefront.
+__device__ __forceinline__ double over_cell(double x, double cell) {
+    const uint64_t bits = (uint64_t)__double_as_longlong(cell);
+    const uint32_t e = (uint32_t)(bits >> 52);  // (cells are positive)
+    if ((bits << 12) == 0 && e >= 1u && e <= 2045u)
+        return x * __longlong_as_double((long long)((2046ull << 52) - bits));
+    return x / cell;
+}
+
 // FP64 set-up of pixel (pi, pj): slab test, clip to the window, starting cell
 // and crossing sequences.  False when no cell of the ray can contribute.
 // cell (if given) receives the starting cell's indices.
@@ -331,7 +396,7 @@ __device__ __forceinline__ bool ray_setup(const RayView &v, const StackDev &st,
     for (int a = 0; a < 3; a++) {
         const double d = v.shat[a];
         const double x = o[a] + s_start * d;
-        int k = (int)floor(x / st.cell[a]);
+        int k = (int)floor(over_cell(x, st.cell[a]));
         k = k < 0 ? 0 : (k >= st.n[a] ? st.n[a] - 1 : k);
         idx[a] = k;
         if (d == 0.0) {
@@ -464,6 +529,25 @@ __device__ __forceinline__ void bracket_init(const RayView &v, const StackDev &s
     b.am = epoch_a<R>(v, st, tab, b.m);
     b.am1 = M >= 2 ? epoch_a<R>(v, st, tab, b.m + 1) : b.am;
     b.inv_dt = M >= 2 ? epoch_inv_dt<R>(st, tab, b.m) : (R)0;
+}
+
+// The bracket of a walk that starts mid-ray at s, by bisection: the last m with
+// s <= a_m (a decreases with m), or 0, which is where stepping down from the
+// last bracket ends for s; no cell entered at or after s has a later one.
+template <typename R>
+__device__ __forceinline__ void bracket_jump(const RayView &v, const StackDev &st, R s,
+                                             Bracket<R> &b, const ldsdouble *tab) {
+    int lo = 0, hi = b.m;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s <= epoch_a<R>(v, st, tab, mid)) lo = mid;
+        else hi = mid - 1;
+    }
+    if (lo == b.m) return;
+    b.m = lo;
+    b.am = epoch_a<R>(v, st, tab, lo);
+    b.am1 = epoch_a<R>(v, st, tab, lo + 1);
+    b.inv_dt = epoch_inv_dt<R>(st, tab, lo);
 }
 
 template <typename R>
@@ -717,8 +801,9 @@ __device__ __forceinline__ bool in_window(double s, double lo, double hi) {
 // SINGLE: one epoch per cell (nearest-epoch mode, or a one-epoch stack), a
 // property of the view and stack, so each lane's walk has no per-cell test.
 //
-// Marches pixel (pi, pj) of view v and returns its intensity (FP64 for the
-// caller's reductions); adds the counted cell-steps to nsteps.
+// Marches depth segment seg of pixel (pi, pj) of view v and returns its
+// intensity (FP64 for the caller's reductions); adds the counted cell-steps to
+// nsteps.
 //
 // The walk does not depend on the data it reads, so each lane first walks a
 // batch of K cells (chord, epoch weight, record addresses), then requests the
@@ -733,7 +818,7 @@ __device__ __forceinline__ bool in_window(double s, double lo, double hi) {
 template <int S, typename R, int SYNC, bool EX, int K, bool VEC, bool SINGLE, int JP>
 __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &st,
                                              const double *centre, int pi, int pj, bool in_image,
-                                             const ldsdouble *tab, uint32_t &nsteps,
+                                             int seg, const ldsdouble *tab, uint32_t &nsteps,
                                              double *ext) {
     using A = typename std::conditional<S == ST_F64, double, float>::type;
     using V = typename RecT<S>::val;
@@ -757,7 +842,12 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
         for (int c = 0; c < NX; c++) ext[c] = 0.0;
     }
     Ray<R> r;
-    bool alive = in_image && ray_setup(v, st, centre, pi, pj, r);
+    bool alive = false;
+    if (in_image) {
+        int idx[3];
+        alive = ray_setup(v, st, centre, pi, pj, r, idx);
+        if (v.seg_log2 > 0 && alive) alive = seek_part(v, st, seg, idx, r);
+    }
     if (SYNC == 0 && !alive) return 0.0;
     const bool lookback = !(v.flags & F_NO_LOOKBACK);
     const bool beaming = !(v.flags & F_NO_BEAMING);
@@ -777,6 +867,7 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     const int64_t second = single ? 0 : estride;
     Bracket<R> br;
     bracket_init(v, st, lookback, br, tab);
+    if (seg > 0 && lookback && alive) bracket_jump(v, st, r.entry, br, tab);
     Doubled<R> dbl;
     doubled_of(br, dbl);
     const OffsetSteps os = offset_steps(st, v);
@@ -1070,25 +1161,25 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
 template <int S, typename R, int SYNC, bool EX, int K, bool VEC = false, int JP = 0>
 __device__ __forceinline__ double march(const RayView &v, const StackDev &st,
                                         const double *centre, int pi, int pj, bool in_image,
-                                        const ldsdouble *tab, uint32_t &nsteps,
+                                        int seg, const ldsdouble *tab, uint32_t &nsteps,
                                         double *ext = nullptr) {
     // uniform over the launch's view (flags, epoch count): a scalar branch
     if ((v.flags & F_NEAREST) || st.n_epochs == 1)
-        return march_walk<S, R, SYNC, EX, K, VEC, true, JP>(v, st, centre, pi, pj, in_image, tab,
-                                                             nsteps, ext);
-    return march_walk<S, R, SYNC, EX, K, VEC, false, JP>(v, st, centre, pi, pj, in_image, tab,
+        return march_walk<S, R, SYNC, EX, K, VEC, true, JP>(v, st, centre, pi, pj, in_image, seg,
+                                                             tab, nsteps, ext);
+    return march_walk<S, R, SYNC, EX, K, VEC, false, JP>(v, st, centre, pi, pj, in_image, seg, tab,
                                                           nsteps, ext);
 }
 
-// Intensity of pixel (pi, pj): one march through the stack, or, for a labelled
-// stack (LAB), one march through each of its sub-domains in order, summed
-// (emission adds along the ray; sub-domains do not overlap).  The block loop
-// is uniform over the wavefront, as the depth-synchronous mode needs.
+// Intensity of one depth segment of pixel (pi, pj): one march through the stack,
+// or, for a labelled stack (LAB), one march through each of its sub-domains in
+// order, summed (emission adds along the ray; sub-domains do not overlap).  The
+// block loop is uniform over the wavefront, as the depth-synchronous mode needs.
 // Vector stacks (VEC, never with LAB) also return components 1.. in ext.
 template <int S, typename R, int SYNC, bool LAB, bool EX, int K, bool VEC = false,
           int JP = 0>
 __device__ __forceinline__ double pixel_value(const RayView &v, int pi, int pj, bool in_image,
-                                              const ldsdouble *tab, uint32_t &nsteps,
+                                              int seg, const ldsdouble *tab, uint32_t &nsteps,
                                               double *ext = nullptr) {
     // (labelled stacks get kernels of their own: the block loop would
     // otherwise raise the register count, and lower the occupancy, of every
@@ -1096,13 +1187,13 @@ __device__ __forceinline__ double pixel_value(const RayView &v, int pi, int pj, 
     static_assert(!(LAB && VEC), "vector stacks are not labelled");
     static_assert(!(LAB && JP), "labelled stacks read whole records");
     if constexpr (!LAB) {
-        return march<S, R, SYNC, EX, K, VEC, JP>(v, v.st, v.centre, pi, pj, in_image, tab, nsteps,
-                                                 ext);
+        return march<S, R, SYNC, EX, K, VEC, JP>(v, v.st, v.centre, pi, pj, in_image, seg, tab,
+                                                 nsteps, ext);
     } else {
         double acc = 0.0;
         for (int b = 0; b < v.n_blocks; b++)
             acc += march<S, R, SYNC, EX, K>(v, v.blocks[b].st, v.blocks[b].centre, pi, pj,
-                                         in_image, tab, nsteps);
+                                         in_image, seg, tab, nsteps);
         return acc;
     }
 }
@@ -1152,29 +1243,51 @@ __device__ __forceinline__ void add_sums(const RenderSums &sums, const RayView &
     }
 }
 
-// Plain kernel: one thread per pixel in row order, one launch per image.
+// Plain kernel: one launch per image, four wavefronts per workgroup.  Each marches
+// one depth segment of an 8 x 8 pixel tile; the first of a tile's wavefronts adds
+// its segments up.
 template <int S, typename R, bool LAB, bool EX, bool VEC = false, int JP = 0>
 __global__ void __launch_bounds__(256) k_plain(RayView v, RenderSums sums) {
     __shared__ double s_tab[4][2 * EPOCH_TAB_MAX];
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long npix = (long long)v.width * v.height;
+    __shared__ double s_part[4][VEC ? 4 : 1][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     ldsdouble *tab = nullptr;
     if (v.st.n_epochs <= EPOCH_TAB_MAX) {
-        tab = (ldsdouble *)&s_tab[threadIdx.x >> 6][0];
+        tab = (ldsdouble *)&s_tab[wave][0];
         epoch_tab_fill(tab, v.st, v.t_obs);
     }
-    double val = 0.0;
+    const int n = 1 << v.seg_log2, seg = wave & (n - 1), tw_log2 = v.tile_w_log2;
+    const uint32_t tile = (blockIdx.x * 4 + (uint32_t)wave) >> v.seg_log2;
+    const uint32_t ntx = ((uint32_t)v.width + (1u << tw_log2) - 1u) >> tw_log2;
+    const uint32_t ty = tile / ntx;
+    const int pi = (int)((tile - ty * ntx) << tw_log2) + (lane & ((1 << tw_log2) - 1));
+    const int pj = (int)(ty << (6 - tw_log2)) + (lane >> tw_log2);
+    const bool in_image = pi < v.width && pj < v.height;
     uint32_t ns = 0;
-    if (idx < npix) {
-        const int pi = (int)(idx % v.width), pj = (int)(idx / v.width);
-        double ext[3];
-        val = pixel_value<S, R, 0, LAB, EX, CELLS_PER_BATCH, VEC, JP>(v, pi, pj, true, tab, ns,
-                                                                      ext);
+    double ext[3] = {0.0, 0.0, 0.0};
+    double val = pixel_value<S, R, 0, LAB, EX, CELLS_PER_BATCH, VEC, JP>(v, pi, pj, in_image, seg,
+                                                                         tab, ns, ext);
+    add_sums(sums, v, blockIdx.x * 4 + wave, val, ns);
+    if (n > 1) {
+        s_part[wave][0][lane] = val;
+        if constexpr (VEC)
+            for (int c = 1; c < v.n_chan; c++) s_part[wave][c][lane] = ext[c - 1];
+        __syncthreads();
+        if (seg != 0) return;
+        val = 0.0;
+        for (int k = 0; k < n; k++) val += s_part[wave + k][0][lane];
+        if constexpr (VEC)
+            for (int c = 1; c < v.n_chan; c++) {
+                ext[c - 1] = 0.0;
+                for (int k = 0; k < n; k++) ext[c - 1] += s_part[wave + k][c][lane];
+            }
+    }
+    if (in_image) {
         store_pixel(v, pi, pj, val);
         if constexpr (VEC)
             for (int c = 1; c < v.n_chan; c++) store_pixel(v, pi, pj, ext[c - 1], c);
     }
-    add_sums(sums, v, blockIdx.x * 4 + (threadIdx.x >> 6), val, ns);
 }
 
 // Persistent kernel: every wavefront pulls 64-pixel tiles (tile_w x tile_h)
@@ -1197,18 +1310,25 @@ __global__ void __launch_bounds__(256) k_batch(BatchLaunch bl,
     const int lane = threadIdx.x & 63;
     const uint32_t nq = bl.n_queues;
     const uint32_t q0 = blockIdx.x % nq;
+    // a tile marched segment by segment on this wave: its segments so far
+    __shared__ double s_val[4][VEC ? 4 : 1][64];
+    uint32_t t = 0, seg = 0, seg_end = 0;  // queue position; its next segments
     for (uint32_t qi = 0; qi < nq;) {
-        const uint32_t q = (q0 + qi) % nq;
-        const uint32_t begin = bl.q_begin[q], end = bl.q_begin[q + 1];
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(&bl.head[q * bl.head_stride], 1u);
-        t = __builtin_amdgcn_readfirstlane(t);
-        if (t >= end - begin) {
-            qi++;
-            continue;
+        if (seg == seg_end) {
+            const uint32_t q = (q0 + qi) % nq;
+            const uint32_t begin = bl.q_begin[q], end = bl.q_begin[q + 1];
+            uint32_t k = 0;
+            if (lane == 0) k = atomicAdd(&bl.head[q * bl.head_stride], 1u);
+            k = __builtin_amdgcn_readfirstlane(k);
+            if (k >= end - begin) {
+                qi++;
+                continue;
+            }
+            t = begin + k;
         }
-        const Tile tile = tiles[begin + t];
-        const uint32_t vi = __builtin_amdgcn_readfirstlane(tile.view);
+        const Tile tile = tiles[t];
+        const uint32_t vs = __builtin_amdgcn_readfirstlane(tile.view);
+        const uint32_t vi = vs & ((1u << TILE_SEG_SHIFT) - 1u);
         const RayView &v = views[vi];
         const bool use_tab = v.st.n_epochs <= EPOCH_TAB_MAX;
         if (use_tab && vi != tab_view) {
@@ -1223,34 +1343,69 @@ __global__ void __launch_bounds__(256) k_batch(BatchLaunch bl,
         uint32_t ns = 0;
         const bool in_image = pi < v.width && pj < v.height;
         double ext[3];
-        const double val = pixel_value<S, R, SYNC, LAB, EX, K, VEC, JP>(
-            v, pi, pj, in_image, use_tab ? wave_tab : nullptr, ns, ext);
+        if (seg == seg_end) {
+            // the item's depth segment (k_finish adds them up), or all of them
+            seg = vs >> TILE_SEG_SHIFT;
+            seg_end = v.seg_items ? seg + 1 : 1u << v.seg_log2;
+        }
+        double val = pixel_value<S, R, SYNC, LAB, EX, K, VEC, JP>(
+            v, pi, pj, in_image, (int)seg, use_tab ? wave_tab : nullptr, ns, ext);
+        add_sums(bl.sums, v, blockIdx.x * 4 + (threadIdx.x >> 6), val, ns);
+        seg++;
+        if (v.seg_items) {
+            double *p = bl.parts + (uint64_t)t * (VEC ? 4 : 1) * 64 + lane;
+            p[0] = val;
+            if constexpr (VEC)
+                for (int c = 1; c < v.n_chan; c++) p[c * 64] = ext[c - 1];
+            continue;
+        }
+        if (v.seg_log2 > 0) {
+            double(*sv)[64] = s_val[threadIdx.x >> 6];
+            const bool first = seg == 1;
+            sv[0][lane] = val = (first ? 0.0 : sv[0][lane]) + val;
+            if constexpr (VEC)
+                for (int c = 1; c < v.n_chan; c++)
+                    sv[c][lane] = ext[c - 1] = (first ? 0.0 : sv[c][lane]) + ext[c - 1];
+            if (seg < seg_end) continue;
+        }
         if (in_image) {
             store_pixel(v, pi, pj, val);
             if constexpr (VEC)
                 for (int c = 1; c < v.n_chan; c++) store_pixel(v, pi, pj, ext[c - 1], c);
         }
-        add_sums(bl.sums, v, blockIdx.x * 4 + (threadIdx.x >> 6), val, ns);
     }
 }
 
 #ifndef DART_MARCH_STORE  // (one unit holds the kernels that do not march)
 
-// Zero fill of the tiles a batch does not march (every ray of them misses the
-// grid): four 64-pixel tiles per 256-thread block, each lane one pixel in the
-// tile layout of k_batch, every channel.
-__global__ void __launch_bounds__(256) k_clear_tiles(const RayView *__restrict__ views,
-                                                     const Tile *__restrict__ tiles, uint32_t n) {
-    const uint32_t k = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (k >= n) return;
+// What a batch does not store itself: the tiles queued by depth segment (their
+// parts, at consecutive queue positions from segment 0, added in order) and the
+// tiles it does not march (every ray of them misses the grid), whose pixels are
+// 0.  Four 64-pixel tiles per 256-thread block, each lane one pixel in the tile
+// layout of k_batch, every channel.
+__global__ void __launch_bounds__(256) k_finish(const RayView *__restrict__ views,
+                                                const Tile *__restrict__ tiles, uint32_t first,
+                                                uint32_t n_queued, uint32_t end,
+                                                const double *__restrict__ parts) {
+    const uint32_t k = first + blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= end) return;
     const Tile tile = tiles[k];
+    if (tile.view >> TILE_SEG_SHIFT) return;
     const RayView &v = views[tile.view];
     const int lane = threadIdx.x & 63;
+    const bool queued = k < n_queued;
+    if (queued && !v.seg_items) return;
     const uint32_t tw_log2 = (uint32_t)v.tile_w_log2;
     const int pi = (int)((uint32_t)tile.tx << tw_log2) + (lane & ((1 << tw_log2) - 1));
     const int pj = (int)((uint32_t)tile.ty << (6 - tw_log2)) + (lane >> tw_log2);
-    if (pi < v.width && pj < v.height)
-        for (int c = 0; c < v.n_chan; c++) store_pixel(v, pi, pj, 0.0, c);
+    if (pi >= v.width || pj >= v.height) return;
+    for (int c = 0; c < v.n_chan; c++) {
+        double val = 0.0;
+        if (queued)
+            for (int s = 0; s < 1 << v.seg_log2; s++)
+                val += parts[((uint64_t)(k + s) * (v.n_chan > 1 ? 4 : 1) + c) * 64 + lane];
+        store_pixel(v, pi, pj, val, c);
+    }
 }
 
 // Sample marking for the compulsory-bytes count (untimed instrumentation).
@@ -1450,7 +1605,11 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
 
 template <int S, typename R>
 hipError_t plain_impl(const RayView &v, const RenderSums &sums, hipStream_t s) {
-    const dim3 g((unsigned)(((uint64_t)v.width * v.height + 255) / 256)), b(256);
+    const int tw = 1 << v.tile_w_log2, th = 64 >> v.tile_w_log2;
+    const uint64_t waves = (uint64_t)((v.width + tw - 1) / tw) *
+                           (uint64_t)((v.height + th - 1) / th) << v.seg_log2;
+    static_assert(MAX_SEG_LOG2 <= 2, "a workgroup of k_plain holds a tile's segments");
+    const dim3 g((unsigned)((waves + 3) / 4)), b(256);
     const bool lab = v.n_blocks > 0, ex = (v.flags & F_EXACT) != 0;
     if constexpr (S != ST_F64) {
         // (the planner gives an emissivity plane only to plain stacks)
@@ -1736,8 +1895,12 @@ hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_
     return hipGetLastError();
 }
 
-hipError_t launch_clear_tiles(const RayView *views, const Tile *tiles, uint32_t n, hipStream_t s) {
-    hipLaunchKernelGGL(k_clear_tiles, dim3((n + 3) / 4), dim3(256), 0, s, views, tiles, n);
+hipError_t launch_finish(const RayView *views, const Tile *tiles, uint32_t n_queued,
+                         uint32_t n_clear, const double *parts, hipStream_t s) {
+    const uint32_t first = parts ? 0 : n_queued, end = n_queued + n_clear;
+    if (first == end) return hipSuccess;
+    hipLaunchKernelGGL(k_finish, dim3((end - first + 3) / 4), dim3(256), 0, s, views, tiles, first,
+                       n_queued, end, parts);
     return hipGetLastError();
 }
 

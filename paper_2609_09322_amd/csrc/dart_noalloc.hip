@@ -103,7 +103,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     }
     const dart_tuning tun = tuning_for(stacks[0]);
     std::vector<Group> groups;
-    st = plan_batch(stacks, views, n, images, tun, groups);
+    st = plan_batch(stacks, views, n, images, tun, 0, groups);
     if (st != DART_OK) return st;
     size_t nv = 0, nt = 0;
     assign_offsets(groups, &nv, &nt);
@@ -136,7 +136,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
                                   hipMemcpyHostToDevice, stream),
                    "H2D descriptors");
     HIP_TRY_STATUS(hipStreamSynchronize(stream), "sync");
-    HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, dviews, dtiles, tun, device, stream),
+    HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, nullptr, dviews, dtiles, tun, device, stream),
                    "batch kernels");
     for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
     if (sums) {

@@ -27,6 +27,7 @@ struct dart_stack {
                                                     // or data change
     int device = 0;
     dart_tuning tuning{32, 2, 8, 0, 1, 0, 4};
+    bool interval = false;             // a streamed interval (marched in whole rays)
     bool placed = false;               // set by dart_stack_set_placement
     double origin[3] = {0, 0, 0}, centre[3] = {0, 0, 0};
     bool tuned = false;
@@ -90,6 +91,7 @@ struct Group {
     // miss the grid (their pixels are set to 0 by a fill kernel)
     std::vector<Tile> tiles;
     std::vector<Tile> clear;  // (planner scratch)
+    size_t parts = 0;         // values of BatchLaunch::parts (0: no tile is queued by segment)
     uint32_t n_clear = 0;
     size_t view_off = 0, tile_off = 0;  // offsets in the uploaded descriptor arrays
     uint32_t n_queues = 8;
@@ -121,8 +123,12 @@ struct SumLayout {
     void total(const unsigned long long *h, size_t view, double *flux, uint64_t *steps) const;
 };
 
+// max_parts: the most values of BatchLaunch::parts the caller has room for.
 dart_status plan_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
-                       void *const *images, const dart_tuning &tun, std::vector<Group> &groups);
+                       void *const *images, const dart_tuning &tun, size_t max_parts,
+                       std::vector<Group> &groups);
+// The launches of a plan share one parts array (they run one after the other).
+size_t parts_of(const std::vector<Group> &groups);
 
 // Per-(device, stream) scratch: accumulators, descriptor arrays, image staging,
 // pinned upload staging and the last captured batch graph.
@@ -138,6 +144,8 @@ struct Workspace {
     size_t views_cap = 0;
     Tile *tiles = nullptr;
     size_t tiles_cap = 0;
+    double *parts = nullptr;            // BatchLaunch::parts
+    size_t parts_cap = 0;
     unsigned long long *img = nullptr;  // staging for host-destined images
     size_t img_cap = 0;
     void *stage = nullptr;              // pinned host staging for descriptor uploads
@@ -154,12 +162,12 @@ struct Workspace {
 
 Workspace *get_workspace(hipStream_t stream);
 hipError_t ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_u64,
-                      size_t acc_words);
+                      size_t acc_words, size_t n_parts = 0);
 // sums: whether the launch adds up flux and cell-steps.
 hipError_t enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
-                        unsigned long long *acc, bool sums, const RayView *dviews,
-                        const Tile *dtiles, const dart_tuning &tun, int device,
-                        hipStream_t stream);
+                        unsigned long long *acc, bool sums, double *parts,
+                        const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,
+                        int device, hipStream_t stream);
 void assign_offsets(std::vector<Group> &groups, size_t *n_views, size_t *n_tiles);
 void pack_descriptors(const std::vector<Group> &groups, size_t n_views, void *dst);
 

@@ -647,6 +647,42 @@ static void sincos_deg(double deg, double *s, double *c) {
     *c = co + 0.0;
 }
 
+// Depth segments per ray (RayView::seg_log2) of a view.  A view of few rays
+// leaves the card waiting for its longest ray (256^2 rays are 4 wavefronts per
+// CU, each some hundred batches of dependent steps and gathers), so its rays are
+// cut in 2 or 4 parts that run at once.  The rule depends on the view and the
+// stack alone, never on the batch: every path sums a view's rays in the same
+// parts and gives the same pixels.
+// Measured (whole / 2 / 4 / 8 parts): one 512^2 image of a 128x128x256 FP32 jet
+// 185 / 127 / 87 / 97 us, four 256^2 FP64 images of 128^3 cells 625 / 443 / 379 /
+// 385, two 512^2 I,Q,U images 1305 / 953 / 896 / 926, the 128^2 FP64 image of 64^3
+// cells 184 / 158 / 135 / 118, four 512^2 views of the FP32 jet 528 / 500 / 499 /
+// 561.  A part costs a set-up of its own (about 3 us of a wavefront), so:
+//   SEG_WAVES  the parts of the rays that meet the grid fill at most this many
+//              wavefronts (64-view FP16 batch: 9.07 ms at 3500, 9.16 at 7000,
+//              9.35 at 9000; the single image 127, 87, 87 us);
+//   SEG_CELLS  a part of the mean ray has at least this many cells;
+// labelled stacks (a set-up per sub-domain: 513 us whole, 544 in 2 parts) and
+// streamed intervals (a few dozen cells per ray already: 1.50 ms whole, 1.68 in
+// 2 parts) march whole rays.
+constexpr double SEG_WAVES = 7000.0, SEG_CELLS = 8.0;
+
+static int segments_log2(const dart_stack *s, const RayView &rv) {
+    if (s->labelled() || s->interval) return 0;
+    double volume = 1.0, area = 0.0, per_len = 0.0;  // area: of the grid's projection
+    for (int a = 0; a < 3; a++) volume *= rv.st.n[a] * rv.st.cell[a];
+    for (int a = 0; a < 3; a++) {
+        area += fabs(rv.shat[a]) * volume / (rv.st.n[a] * rv.st.cell[a]);
+        per_len += fabs(rv.shat[a]) / rv.st.cell[a];
+    }
+    const double rays = std::min((double)rv.width * rv.height, area / (rv.ps * rv.ps));
+    const double cells = std::min(volume / area, rv.s_hi - rv.s_lo) * per_len;
+    int l = 0;
+    while (l < MAX_SEG_LOG2 && rays / 64.0 * (2 << l) <= SEG_WAVES && cells / (2 << l) >= SEG_CELLS)
+        l++;
+    return l;
+}
+
 dart_status dart::resolve_view(const dart_stack *s, const dart_view *v, RayView *rv) {
     if (!s || !v || !rv) return fail(DART_E_INVAL, "NULL stack or view");
     for (int32_t m = 0; m < s->dev.n_epochs; m++)
@@ -750,6 +786,7 @@ dart_status dart::resolve_view(const dart_stack *s, const dart_view *v, RayView 
         rv->fixed_w = 0.0;
     }
     rv->fixed_wf = (float)rv->fixed_w;
+    rv->seg_log2 = (int16_t)segments_log2(s, *rv);
     return DART_OK;
 }
 
@@ -833,14 +870,22 @@ void SumLayout::total(const unsigned long long *h, size_t view, double *flux,
 }
 
 hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_bytes,
-                            size_t acc_words) {
+                            size_t acc_words, size_t n_parts) {
     hipError_t e;
-    // a captured graph holds these pointers: any reallocation invalidates it
-    const void *before[4] = {ws->acc, ws->views, ws->tiles, ws->img};
     if (ws->stage_ready) {
         e = hipEventSynchronize(ws->stage_done);
         if (e != hipSuccess) return e;
     }
+    // a captured graph holds these pointers: any reallocation invalidates it
+    // (also when a later buffer fails: an earlier one may have moved)
+    struct Moved {
+        Workspace *ws;
+        const void *before[5];
+        ~Moved() {
+            const void *after[5] = {ws->acc, ws->views, ws->tiles, ws->img, ws->parts};
+            if (memcmp(before, after, sizeof(before)) != 0) drop_graph(ws);
+        }
+    } moved{ws, {ws->acc, ws->views, ws->tiles, ws->img, ws->parts}};
     if ((e = grow_dev(ws->acc, ws->acc_cap, acc_words)) != hipSuccess) return e;
     if ((e = grow_host(ws->sums_host, ws->sums_host_cap, acc_words * 8)) != hipSuccess) return e;
     if ((e = grow_dev(ws->views, ws->views_cap, std::max(n_views, (size_t)1))) != hipSuccess) return e;
@@ -853,8 +898,7 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
             return e;
         ws->stage_ready = true;
     }
-    const void *after[4] = {ws->acc, ws->views, ws->tiles, ws->img};
-    if (memcmp(before, after, sizeof(before)) != 0) drop_graph(ws);
+    if (n_parts && (e = grow_dev(ws->parts, ws->parts_cap, n_parts)) != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -880,6 +924,7 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     HIP_TRY(ws_reserve(ws, 1, 0, dev_img ? 0 : img_bytes / 8 + 1, lay.words()), "workspace");
     rv.image = dev_img ? image : (void *)ws->img;
     rv.acc_index = 0;
+    rv.tile_w_log2 = 3;
     if (sums) HIP_TRY(launch_fill_u64(ws->acc, lay.words(), 0ull, stream), "clear accumulators");
     HIP_TRY(launch_plain(rv, sums ? lay.sums(ws->acc) : RenderSums{}, stream), "render kernel");
     note_use(s, stream);
@@ -1136,7 +1181,7 @@ static double tile_cost(const RayView &rv, int tx, int ty, int tw, int th) {
 }
 
 dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
-                             void *const *images, const dart_tuning &tun,
+                             void *const *images, const dart_tuning &tun, size_t max_parts,
                              std::vector<Group> &groups) {
     groups.clear();
     const int lw0 = ilog2_exact(tun.tile_w);
@@ -1204,6 +1249,24 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
                     g.tiles.push_back(t);
                 }
             }
+        }
+    }
+    // Tiles of views with depth segments are queued segment by segment, view by
+    // view while their sums fit (the tiles of the others are marched segment
+    // after segment by one wave, without the parallel parts: FP16 batch 9.25 ->
+    // 9.6 ms if all are).
+    for (Group &g : groups) {
+        std::vector<size_t> tiles(g.views.size(), 0);
+        for (const Tile &t : g.tiles) tiles[t.view]++;
+        const size_t per_item = 64 * (g.vec ? 4 : 1);
+        size_t room = std::min(max_parts, (size_t)UINT32_MAX) / per_item;  // queue positions
+        room -= std::min(room, g.tiles.size());
+        for (size_t v = 0; v < g.views.size() && g.views.size() <= (1u << TILE_SEG_SHIFT); v++) {
+            const size_t more = tiles[v] * ((1u << g.views[v].seg_log2) - 1);
+            if (more == 0 || more > room) continue;
+            room -= more;
+            g.views[v].seg_items = 1;
+            g.parts = per_item;  // (sized once the queue is laid out)
         }
     }
     for (Group &g : groups) {
@@ -1313,6 +1376,24 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
         if (!bounds_set)
             for (size_t q = 0; q <= nq; q++)
                 g.q_begin[q] = (uint32_t)(((uint64_t)g.tiles.size() * q) / nq);
+        if (g.parts) {
+            // each tile's segments at consecutive places of its queue
+            std::vector<Tile> items;
+            uint32_t q = 0;
+            for (uint32_t k = 0; k <= g.tiles.size(); k++) {
+                while (q <= nq && g.q_begin[q] == k) g.q_begin[q++] = (uint32_t)items.size();
+                if (k == g.tiles.size()) break;
+                Tile t = g.tiles[k];
+                const RayView &tv = g.views[t.view];
+                const uint32_t n_seg = tv.seg_items ? 1u << tv.seg_log2 : 1u;
+                for (uint32_t s = 0; s < n_seg; s++) {
+                    items.push_back(t);
+                    items.back().view |= s << TILE_SEG_SHIFT;
+                }
+            }
+            g.tiles.swap(items);
+            g.parts *= g.tiles.size();
+        }
         // the tiles to clear follow the queued ones in the same array
         g.n_clear = (uint32_t)g.clear.size();
         g.tiles.insert(g.tiles.end(), g.clear.begin(), g.clear.end());
@@ -1324,20 +1405,15 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
 // Enqueues clear + persistent kernels of every group; dviews / dtiles hold the
 // groups' descriptors at their offsets.
 hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
-                              unsigned long long *acc, bool sums, const RayView *dviews,
-                              const Tile *dtiles, const dart_tuning &tun, int device,
-                              hipStream_t stream) {
+                              unsigned long long *acc, bool sums, double *parts,
+                              const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,
+                              int device, hipStream_t stream) {
     hipError_t e = launch_fill_u64(acc, sums ? lay.words() : lay.heads_words(), 0ull, stream);
     if (e != hipSuccess) return e;
     const int cus = device_cus(device);
     const int blocks = std::max(1, cus * tun.waves_per_cu / 4);
     for (size_t gi = 0; gi < groups.size(); gi++) {
         const Group &g = groups[gi];
-        if (g.n_clear > 0) {
-            e = launch_clear_tiles(dviews + g.view_off, dtiles + g.tile_off + g.q_begin[g.n_queues],
-                                   g.n_clear, stream);
-            if (e != hipSuccess) return e;
-        }
         BatchLaunch bl;
         bl.views = dviews + g.view_off;
         bl.tiles = dtiles + g.tile_off;
@@ -1347,6 +1423,7 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout 
         bl.n_queues = g.n_queues;
         for (uint32_t q = 0; q <= g.n_queues; q++) bl.q_begin[q] = g.q_begin[q];
         bl.sums = sums ? lay.sums(acc) : RenderSums{};
+        bl.parts = g.parts ? parts : nullptr;
         const int variant = g.vec ? (KV_VEC | (tun.cells_per_batch == 8 ? KV_K8 : 0))
                                   : (tun.depth_sync > 0 ? KV_SYNC : 0) |
                                         (g.labelled ? KV_LABELLED : 0) | (g.exact ? KV_EXACT : 0) |
@@ -1358,9 +1435,17 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout 
         // every queue head
         const int grid = std::max(1, std::min(blocks, (int)((bl.n_tiles + 3) / 4)));
         e = launch_batch(g.store, g.f64, variant, bl, grid, stream);
+        if (e == hipSuccess)
+            e = launch_finish(bl.views, bl.tiles, bl.n_tiles, g.n_clear, bl.parts, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+size_t dart::parts_of(const std::vector<Group> &groups) {
+    size_t most = 0;
+    for (const Group &g : groups) most = std::max(most, g.parts);
+    return most;
 }
 
 void dart::assign_offsets(std::vector<Group> &groups, size_t *n_views, size_t *n_tiles) {
@@ -1383,6 +1468,10 @@ void dart::pack_descriptors(const std::vector<Group> &groups, size_t n_views, vo
         memcpy(ht + gr.tile_off * sizeof(Tile), gr.tiles.data(), gr.tiles.size() * sizeof(Tile));
     }
 }
+
+// Segment sums a batch's workspace holds at most: 256 MiB, the 512 bytes per
+// item of some 500000 items (64 views of the largest split images have 200000).
+static constexpr size_t MAX_PARTS = (256u << 20) / sizeof(double);
 
 extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const dart_view *views,
                                          int32_t n, void *const *images, double *flux_out,
@@ -1466,13 +1555,18 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         std::vector<void *> tmp_images(n);
         for (int32_t i = 0; i < n; i++)
             tmp_images[i] = images[i];
-        dart_status st = plan_batch(stacks, views, n, tmp_images.data(), tun, groups);
-        if (st != DART_OK) return st;
         size_t nv = 0, nt = 0;
-        assign_offsets(groups, &nv, &nt);
-        HIP_TRY(ws_reserve(ws, std::max(nv, (size_t)n), nt, img_bytes / 8 + 1,
-                           SumLayout(n, groups.size()).words()),
-                "workspace");
+        for (size_t max_parts : {MAX_PARTS, (size_t)0}) {
+            dart_status st = plan_batch(stacks, views, n, tmp_images.data(), tun, max_parts, groups);
+            if (st != DART_OK) return st;
+            assign_offsets(groups, &nv, &nt);
+            hipError_t e = ws_reserve(ws, std::max(nv, (size_t)n), nt, img_bytes / 8 + 1,
+                                      SumLayout(n, groups.size()).words(), parts_of(groups));
+            if (e == hipSuccess) break;
+            // (without room for the segments' sums: no tile queued by segment)
+            if (e != hipErrorOutOfMemory || parts_of(groups) == 0) return hip_fail(e, "workspace");
+            (void)hipGetLastError();
+        }
         for (Group &gr : groups)
             for (RayView &rv : gr.views)
                 if (!(views[rv.acc_index].flags & DART_DEVICE_PTRS))
@@ -1497,8 +1591,8 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (use_graph && !exec) {
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
-        hipError_t e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->views, ws->tiles, tun,
-                                    ws->device, stream);
+        hipError_t e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, ws->views,
+                                    ws->tiles, tun, ws->device, stream);
         hipError_t e2 = hipStreamEndCapture(stream, &graph);
         if (e != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -1515,7 +1609,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (use_graph)
         HIP_TRY(hipGraphLaunch(exec, stream), "graph launch");
     else
-        HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->views, ws->tiles, tun,
+        HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, ws->views, ws->tiles, tun,
                              ws->device, stream),
                 "batch kernels");
     for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);

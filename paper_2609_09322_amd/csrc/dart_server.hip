@@ -280,16 +280,24 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     // tuned shape with tiles in row order instead.
     if (tun.order == 1 || tun.order == 4) tun.order = 0;
     std::vector<Group> groups;
-    dart_status st = plan_batch(stacks.data(), views.data(), n, imgs.data(), tun, groups);
-    if (st != DART_OK) {
-        fail_wave(srv, w.get(), st, dart_last_error());
-        return;
+    size_t nv = 0, nt = 0, desc_bytes = 0, acc_off = 0, parts_off = 0;
+    SumLayout lay(n, 0);
+    // (tiles queued by depth segment when the buffer holds their parts too)
+    for (size_t max_parts : {srv->desc_cap / 8 * 3 / 4, srv->desc_cap / 8 / 4, (size_t)0}) {
+        dart_status st = plan_batch(stacks.data(), views.data(), n, imgs.data(), tun, max_parts,
+                                    groups);
+        if (st != DART_OK) {
+            fail_wave(srv, w.get(), st, dart_last_error());
+            return;
+        }
+        assign_offsets(groups, &nv, &nt);
+        desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
+        acc_off = (desc_bytes + 255) & ~(size_t)255;
+        lay = SumLayout(n, groups.size());
+        parts_off = (acc_off + lay.words() * 8 + 511) & ~(size_t)511;
+        const size_t parts = parts_of(groups);
+        if (parts == 0 || parts_off + parts * 8 <= srv->desc_cap) break;
     }
-    size_t nv = 0, nt = 0;
-    assign_offsets(groups, &nv, &nt);
-    const size_t desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
-    const size_t acc_off = (desc_bytes + 255) & ~(size_t)255;
-    SumLayout lay(n, groups.size());
     if (acc_off + lay.words() * 8 > srv->desc_cap) {
         w->compact = true;
         lay = SumLayout(n, groups.size(), true);
@@ -321,7 +329,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         e = hipMemcpyAsync(ddesc, hstage, desc_bytes, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kbegin[sidx], stream);
     if (e == hipSuccess)
-        e = enqueue_plan(groups, lay, dacc, true, (const RayView *)ddesc,
+        e = enqueue_plan(groups, lay, dacc, true, (double *)(ddesc + parts_off), (const RayView *)ddesc,
                          (const Tile *)(ddesc + nv * sizeof(RayView)), tun, srv->device, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kend[sidx], stream);
     for (int32_t i = 0; i < n && e == hipSuccess; i++) {

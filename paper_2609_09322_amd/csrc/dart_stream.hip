@@ -271,6 +271,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     for (int32_t m : iv) {
         std::unique_ptr<dart_stack> is(new dart_stack);
         is->dev = rd;
+        is->interval = true;
         const int32_t ne = M > 1 ? 2 : 1;
         is->dev.n_epochs = ne;
         is->dev.data = (const char *)rd.data + (size_t)slot[m] * rd.epoch_stride * rb;
@@ -299,7 +300,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
                 gidx.push_back(i);
             }
         std::vector<Group> g;
-        dart_status st = plan_batch(sts.data(), vv.data(), (int32_t)vv.size(), im.data(), tun, g);
+        dart_status st = plan_batch(sts.data(), vv.data(), (int32_t)vv.size(), im.data(), tun, 0, g);
         if (st != DART_OK) return st;
         const bool lo_open = M > 1 && m + 1 < M - 1;
         for (Group &gr : g)
@@ -401,12 +402,13 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
             BatchLaunch bl;
             bl.views = s->d_views + g.view_off;
             bl.tiles = s->d_tiles + g.tile_off;
-            bl.n_tiles = (uint32_t)g.tiles.size();
+            bl.n_tiles = g.q_begin[g.n_queues];
             bl.head = lay.head(s->acc, gi);
             bl.head_stride = lay.head_stride;
             bl.n_queues = g.n_queues;
             for (uint32_t q = 0; q <= g.n_queues; q++) bl.q_begin[q] = g.q_begin[q];
             bl.sums = sums ? lay.sums(s->acc) : RenderSums{};
+            bl.parts = nullptr;  // (whole rays)
             const int variant = (tun.depth_sync > 0 ? KV_SYNC : 0) | (g.labelled ? KV_LABELLED : 0) |
                                 (tun.cells_per_batch == 8 ? KV_K8 : 0);
             ST_TRY(launch_batch(g.store, g.f64, variant, bl, blocks, stream), "interval kernel");
