@@ -437,7 +437,8 @@ dart_status dart_gather_probe(const void *src, uint64_t bytes, int32_t reps, voi
  * A render server keeps stacks resident (the caller's) and runs a host
  * scheduler thread that batches requests as they arrive (continuous batching):
  * every admitted, unfinished request is rendered by the next wave, waves run
- * on several streams and overlap on the device.  Output images are staged in
+ * on several streams and overlap on the device.  Output images for host memory
+ * (and device images that another request in flight also has) are staged in
  * server-owned device memory; admission waits until the staged images of the
  * requests in flight fit in hbm_budget_bytes and fewer than max_inflight are
  * admitted.  Wave descriptors live in per-stream buffers fixed at creation

@@ -164,6 +164,13 @@ hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_
                               hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t s);
+// What precedes a render's kernels, in one launch: clears n_clear words and, when
+// src is given, copies n_copy words of descriptors from pinned host memory.
+hipError_t launch_begin(unsigned long long *clear, size_t n_clear, void *dst, const void *src,
+                        size_t n_copy, hipStream_t s);
+// Totals of n views from their slots, written to pinned host memory: flux[n] (as
+// double bits), then steps[n].
+hipError_t launch_totals(const RenderSums &sums, int32_t n, void *host, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);
 // After a batched launch: adds up the parts of the tiles among the n_queued
 // queue positions that were queued by segment (parts null: there are none) and

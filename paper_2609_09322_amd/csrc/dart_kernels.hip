@@ -1457,6 +1457,36 @@ __global__ void __launch_bounds__(256) k_fill_u64(unsigned long long *p, uint64_
         p[i] = value;
 }
 
+// Descriptors come straight from pinned host memory: a copy command would bring
+// a DMA engine and its synchronisation with this queue into every new plan (a
+// light curve's calls of two small views: 115 -> 103 us each).
+__global__ void __launch_bounds__(256) k_begin(unsigned long long *__restrict__ clear,
+                                               size_t n_clear,
+                                               unsigned long long *__restrict__ dst,
+                                               const unsigned long long *__restrict__ src,
+                                               size_t n_copy) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = i0; i < n_copy; i += stride) dst[i] = src[i];
+    for (size_t i = i0; i < n_clear; i += stride) clear[i] = 0ull;
+}
+
+__global__ void __launch_bounds__(64) k_totals(RenderSums sums, int n, unsigned long long *host) {
+    const unsigned long long *p = sums.slots + (size_t)blockIdx.x * (sums.mask + 1u) * sums.stride;
+    double flux = 0.0;
+    unsigned long long steps = 0;
+    for (uint32_t k = threadIdx.x; k <= sums.mask; k += 64) {
+        flux += __longlong_as_double((long long)p[(size_t)k * sums.stride]);
+        steps += p[(size_t)k * sums.stride + 1];
+    }
+    flux = wave_sum(flux);
+    for (int off = 32; off > 0; off >>= 1) steps += __shfl_xor(steps, off, 64);
+    if (threadIdx.x == 0) {
+        host[blockIdx.x] = (unsigned long long)__double_as_longlong(flux);
+        host[n + blockIdx.x] = steps;
+    }
+}
+
 __global__ void __launch_bounds__(256) k_copy(float4 *__restrict__ dst,
                                               const float4 *__restrict__ src, uint64_t n) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -1907,6 +1937,20 @@ hipError_t launch_finish(const RayView *views, const Tile *tiles, uint32_t n_que
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t s) {
     hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(n, 4096)), dim3(256), 0, s, p, n, value);
+    return hipGetLastError();
+}
+
+hipError_t launch_begin(unsigned long long *clear, size_t n_clear, void *dst, const void *src,
+                        size_t n_copy, hipStream_t s) {
+    const size_t n = n_clear > n_copy ? n_clear : n_copy;
+    hipLaunchKernelGGL(k_begin, dim3(grid_for(n, 1024)), dim3(256), 0, s, clear, n_clear,
+                       (unsigned long long *)dst, (const unsigned long long *)src, n_copy);
+    return hipGetLastError();
+}
+
+hipError_t launch_totals(const RenderSums &sums, int32_t n, void *host, hipStream_t s) {
+    hipLaunchKernelGGL(k_totals, dim3((unsigned)n), dim3(64), 0, s, sums, n,
+                       (unsigned long long *)host);
     return hipGetLastError();
 }
 

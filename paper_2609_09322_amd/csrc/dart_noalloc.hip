@@ -136,9 +136,12 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
                                   hipMemcpyHostToDevice, stream),
                    "H2D descriptors");
     HIP_TRY_STATUS(hipStreamSynchronize(stream), "sync");
+    HIP_TRY_STATUS(launch_begin(acc, sums ? lay.words() : lay.heads_words(), nullptr, nullptr, 0,
+                                stream),
+                   "clear accumulators");
     HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, nullptr, dviews, dtiles, tun, device, stream),
                    "batch kernels");
-    for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
+    note_uses(stacks, n, stream);
     if (sums) {
         std::vector<unsigned long long> h(lay.sum_words());
         HIP_TRY_STATUS(hipMemcpyAsync(h.data(), acc + lay.heads_words(), h.size() * 8,

@@ -70,6 +70,7 @@ dart_status resolve_view(const dart_stack *s, const dart_view *v, RayView *rv);
 dart_status refresh_jplane(const dart_stack *s, hipStream_t stream, bool may_alloc);
 bool jplane_ready(const dart_stack *s);
 void note_use(const dart_stack *s, hipStream_t stream);
+void note_uses(const dart_stack *const *stacks, int32_t n, hipStream_t stream);  // each once
 bool stack_busy(const dart_stack *s);
 dart_tuning tuning_for(const dart_stack *s);
 // Vector stacks: repacks the components' emissivity on `stream` if any
@@ -110,6 +111,7 @@ struct SumLayout {
     uint32_t slots, stride, head_stride;  // slots per view; words; heads: 32-bit words
     SumLayout(size_t n_views, size_t n_groups, bool compact = false);
     size_t head_words() const { return MAX_QUEUES * (size_t)head_stride / 2; }
+    // (the start of a block: what is cleared before a launch)
     size_t heads_words() const { return groups * head_words(); }
     size_t sum_words() const { return n * slots * stride; }
     size_t words() const { return heads_words() + sum_words(); }
@@ -138,12 +140,12 @@ struct Workspace {
     std::mutex mu;
     unsigned long long *acc = nullptr;  // queue heads and sum slots (SumLayout)
     size_t acc_cap = 0;
-    void *sums_host = nullptr;          // pinned: the sum slots read back
+    void *sums_host = nullptr;          // pinned: the views' totals (launch_totals)
     size_t sums_host_cap = 0;
-    RayView *views = nullptr;
-    size_t views_cap = 0;
-    Tile *tiles = nullptr;
-    size_t tiles_cap = 0;
+    void *img_host = nullptr;           // pinned: a small host-destined image
+    size_t img_host_cap = 0;
+    unsigned char *desc = nullptr;      // the plan's view, then tile descriptors
+    size_t desc_cap = 0;
     double *parts = nullptr;            // BatchLaunch::parts
     size_t parts_cap = 0;
     unsigned long long *img = nullptr;  // staging for host-destined images
@@ -160,10 +162,12 @@ struct Workspace {
     bool plan_ready = false;
 };
 
+void read_totals(const void *host, int32_t n, double *flux, uint64_t *steps);
 Workspace *get_workspace(hipStream_t stream);
 hipError_t ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_u64,
                       size_t acc_words, size_t n_parts = 0);
-// sums: whether the launch adds up flux and cell-steps.
+// The kernels of a plan whose queue heads (and sums) launch_begin has cleared.
+// sums: whether they add up flux and cell-steps.
 hipError_t enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
                         unsigned long long *acc, bool sums, double *parts,
                         const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,

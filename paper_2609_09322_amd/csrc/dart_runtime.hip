@@ -318,6 +318,13 @@ void dart::note_use(const dart_stack *cs, hipStream_t stream) {
     s->uses.emplace_back(stream, ev);
 }
 
+void dart::note_uses(const dart_stack *const *stacks, int32_t n, hipStream_t stream) {
+    std::vector<const dart_stack *> s(stacks, stacks + n);
+    std::sort(s.begin(), s.end());
+    s.erase(std::unique(s.begin(), s.end()), s.end());
+    for (const dart_stack *p : s) note_use(p, stream);
+}
+
 bool dart::stack_busy(const dart_stack *cs) {
     dart_stack *s = const_cast<dart_stack *>(cs);
     std::lock_guard<std::mutex> g(s->mu);
@@ -880,16 +887,17 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
     // (also when a later buffer fails: an earlier one may have moved)
     struct Moved {
         Workspace *ws;
-        const void *before[5];
+        const void *before[4];
         ~Moved() {
-            const void *after[5] = {ws->acc, ws->views, ws->tiles, ws->img, ws->parts};
+            const void *after[4] = {ws->acc, ws->desc, ws->img, ws->parts};
             if (memcmp(before, after, sizeof(before)) != 0) drop_graph(ws);
         }
-    } moved{ws, {ws->acc, ws->views, ws->tiles, ws->img, ws->parts}};
+    } moved{ws, {ws->acc, ws->desc, ws->img, ws->parts}};
     if ((e = grow_dev(ws->acc, ws->acc_cap, acc_words)) != hipSuccess) return e;
-    if ((e = grow_host(ws->sums_host, ws->sums_host_cap, acc_words * 8)) != hipSuccess) return e;
-    if ((e = grow_dev(ws->views, ws->views_cap, std::max(n_views, (size_t)1))) != hipSuccess) return e;
-    if ((e = grow_dev(ws->tiles, ws->tiles_cap, std::max(n_tiles, (size_t)1))) != hipSuccess) return e;
+    if ((e = grow_host(ws->sums_host, ws->sums_host_cap, 16 * n_views)) != hipSuccess) return e;
+    if ((e = grow_dev(ws->desc, ws->desc_cap, n_views * sizeof(RayView) + n_tiles * sizeof(Tile))) !=
+        hipSuccess)
+        return e;
     if (img_bytes && (e = grow_dev(ws->img, ws->img_cap, img_bytes)) != hipSuccess) return e;
     const size_t stage = n_views * sizeof(RayView) + n_tiles * sizeof(Tile) + 64;
     if ((e = grow_host(ws->stage, ws->stage_cap, stage)) != hipSuccess) return e;
@@ -903,6 +911,14 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
 }
 
 // ------------------------------------------------------------------ plain render
+
+// flux[n] and steps[n] as launch_totals left them; either may be null.
+void dart::read_totals(const void *host, int32_t n, double *flux, uint64_t *steps) {
+    if (flux) memcpy(flux, host, n * sizeof(double));
+    if (steps) memcpy(steps, (const char *)host + n * sizeof(double), n * sizeof(uint64_t));
+}
+
+static constexpr size_t MAPPED_IMAGE = 256u << 10;
 
 extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void *image,
                                    double *flux_out, uint64_t *steps_out, void *hip_stream) {
@@ -921,21 +937,28 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     const size_t img_bytes = (size_t)rv.n_chan * v->width * v->height * (rv.out_f64 ? 8 : 4);
     const SumLayout lay(1, 0);
     const bool sums = flux_out || steps_out;
-    HIP_TRY(ws_reserve(ws, 1, 0, dev_img ? 0 : img_bytes / 8 + 1, lay.words()), "workspace");
-    rv.image = dev_img ? image : (void *)ws->img;
+    // A small host image is stored straight to pinned memory, over the bus, and
+    // copied on by the host (the 128^2 FP64 image with its sums: 69 us, 90 with
+    // copy commands for both).
+    const bool mapped = !dev_img && img_bytes <= MAPPED_IMAGE;
+    HIP_TRY(ws_reserve(ws, 1, 0, dev_img || mapped ? 0 : img_bytes / 8 + 1, lay.words()),
+            "workspace");
+    if (mapped) HIP_TRY(grow_host(ws->img_host, ws->img_host_cap, MAPPED_IMAGE), "image staging");
+    rv.image = dev_img ? image : mapped ? ws->img_host : (void *)ws->img;
     rv.acc_index = 0;
     rv.tile_w_log2 = 3;
-    if (sums) HIP_TRY(launch_fill_u64(ws->acc, lay.words(), 0ull, stream), "clear accumulators");
+    if (sums)
+        HIP_TRY(launch_begin(ws->acc, lay.words(), nullptr, nullptr, 0, stream),
+                "clear accumulators");
     HIP_TRY(launch_plain(rv, sums ? lay.sums(ws->acc) : RenderSums{}, stream), "render kernel");
     note_use(s, stream);
-    if (!dev_img)
+    if (!dev_img && !mapped)
         HIP_TRY(hipMemcpyAsync(image, ws->img, img_bytes, hipMemcpyDeviceToHost, stream), "D2H image");
-    if (sums)
-        HIP_TRY(hipMemcpyAsync(ws->sums_host, ws->acc, lay.sum_words() * 8, hipMemcpyDeviceToHost,
-                               stream), "D2H acc");
+    if (sums) HIP_TRY(launch_totals(lay.sums(ws->acc), 1, ws->sums_host, stream), "totals");
     if (sums || !dev_img) {
         HIP_TRY(hipStreamSynchronize(stream), "sync");
-        if (sums) lay.total((const unsigned long long *)ws->sums_host, 0, flux_out, steps_out);
+        if (mapped) memcpy(image, ws->img_host, img_bytes);
+        if (sums) read_totals(ws->sums_host, 1, flux_out, steps_out);
     }
     return DART_OK;
 }
@@ -1408,8 +1431,7 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout 
                               unsigned long long *acc, bool sums, double *parts,
                               const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,
                               int device, hipStream_t stream) {
-    hipError_t e = launch_fill_u64(acc, sums ? lay.words() : lay.heads_words(), 0ull, stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     const int cus = device_cus(device);
     const int blocks = std::max(1, cus * tun.waves_per_cu / 4);
     for (size_t gi = 0; gi < groups.size(); gi++) {
@@ -1547,6 +1569,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
 #ifndef DART_USE_GRAPH
 #define DART_USE_GRAPH 1
 #endif
+    size_t desc_words = 0;  // of a new plan
     const bool use_graph = DART_USE_GRAPH && stream != nullptr;
     const bool replay = ws->plan_ready && key == ws->plan_key;
     if (!replay) {
@@ -1574,25 +1597,31 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         // stage descriptors and upload
         char *h = (char *)ws->stage;
         pack_descriptors(groups, nv, h);
-        char *ht = h + nv * sizeof(RayView);
-        HIP_TRY(hipMemcpyAsync(ws->views, h, nv * sizeof(RayView), hipMemcpyHostToDevice, stream),
-                "H2D views");
-        HIP_TRY(hipMemcpyAsync(ws->tiles, ht, nt * sizeof(Tile), hipMemcpyHostToDevice, stream),
-                "H2D tiles");
-        HIP_TRY(hipEventRecord(ws->stage_done, stream), "event");
+        desc_words = (nv * sizeof(RayView) + nt * sizeof(Tile)) / 8;
         drop_graph(ws);
-        ws->plan_groups = groups;
+        ws->plan_groups.swap(groups);
         ws->plan_key = key;
         ws->plan_ready = true;
     }
     const SumLayout lay(n, ws->plan_groups.size());
     const bool sums = flux_out || steps_out;
     hipGraphExec_t &exec = ws->graph_exec[sums ? 1 : 0];
-    if (use_graph && !exec) {
+    size_t n_desc = 0;
+    for (const Group &gr : ws->plan_groups) n_desc += gr.views.size();
+    const size_t n_clear = sums ? lay.words() : lay.heads_words();
+    const RayView *dviews = (const RayView *)ws->desc;
+    const Tile *dtiles = (const Tile *)(ws->desc + n_desc * sizeof(RayView));
+    // A plan's first call launches its kernels one by one; the second captures
+    // them, and from then on one graph launch replays them.  (Capturing and
+    // instantiating on the first call cost a light curve, whose calls all differ,
+    // 14 of its 130 us per call.)
+    if (use_graph && !exec && replay) {
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
-        hipError_t e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, ws->views,
-                                    ws->tiles, tun, ws->device, stream);
+        hipError_t e = launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, stream);
+        if (e == hipSuccess)
+            e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles,
+                                    tun, ws->device, stream);
         hipError_t e2 = hipStreamEndCapture(stream, &graph);
         if (e != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -1606,13 +1635,17 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
             return hip_fail(e, "instantiate graph");
         }
     }
-    if (use_graph)
+    if (exec) {
         HIP_TRY(hipGraphLaunch(exec, stream), "graph launch");
-    else
-        HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, ws->views, ws->tiles, tun,
+    } else {
+        HIP_TRY(launch_begin(ws->acc, n_clear, ws->desc, ws->stage, replay ? 0 : desc_words, stream),
+                "begin");
+        if (!replay) HIP_TRY(hipEventRecord(ws->stage_done, stream), "event");
+        HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles, tun,
                              ws->device, stream),
                 "batch kernels");
-    for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
+    }
+    note_uses(stacks, n, stream);
     bool any_host = false;
     for (int32_t i = 0; i < n; i++) {
         if (!(views[i].flags & DART_DEVICE_PTRS)) {
@@ -1624,15 +1657,10 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
                     "D2H image");
         }
     }
-    if (sums)
-        HIP_TRY(hipMemcpyAsync(ws->sums_host, ws->acc + lay.heads_words(), lay.sum_words() * 8,
-                               hipMemcpyDeviceToHost, stream),
-                "D2H acc");
+    if (sums) HIP_TRY(launch_totals(lay.sums(ws->acc), n, ws->sums_host, stream), "totals");
     if (sums || any_host) {
         HIP_TRY(hipStreamSynchronize(stream), "sync");
-        for (int32_t i = 0; sums && i < n; i++)
-            lay.total((const unsigned long long *)ws->sums_host, i,
-                      flux_out ? flux_out + i : nullptr, steps_out ? steps_out + i : nullptr);
+        if (sums) read_totals(ws->sums_host, n, flux_out, steps_out);
     }
     return DART_OK;
 }

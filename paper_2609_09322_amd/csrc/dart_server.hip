@@ -21,6 +21,7 @@
 #include <mutex>
 #include <thread>
 #include <unordered_map>
+#include <unordered_set>
 #include <vector>
 
 #include "../../include/dart.h"
@@ -86,6 +87,7 @@ struct Req {
     dart_view view{};
     void *dest = nullptr;
     bool host_dest = false;
+    bool in_place = false;  // the wave renders into dest itself
     size_t img_bytes = 0;
     size_t desc_bound = 0;  // upper bound of the request's share of a wave's descriptors
     size_t dev_off = 0, host_off = 0;
@@ -103,7 +105,6 @@ struct Wave {
     std::vector<Req *> reqs;
     int stream_idx = 0;
     bool done = false;
-    bool compact = false;        // layout of its sums (SumLayout)
     Clock::time_point t_plan;    // the scheduler starts planning the wave
     Clock::time_point t_launch;  // its device work is enqueued
     Clock::time_point t_done;    // the completion callback ran
@@ -133,6 +134,7 @@ struct dart_server {
     Arena dev_arena, host_arena;
     std::mutex mu;
     std::condition_variable cv;
+    std::unordered_set<void *> dests;               // rendered in place by waves in flight
     std::deque<Req *> queue;                        // submitted, waiting for admission / a wave
     std::unordered_map<uint64_t, std::unique_ptr<Req>> reqs;
     std::vector<std::unique_ptr<Wave>> waves;       // in flight
@@ -175,12 +177,13 @@ static void retire(dart_server *srv, Wave *w) {
         srv->stream_waited[k] = !srv->queue.empty();
     }
     const unsigned long long *acc_h = (const unsigned long long *)srv->desc_host[w->stream_idx];
-    const SumLayout lay(n, 0, w->compact);
     for (size_t i = 0; i < n; i++) {
         Req *r = w->reqs[i];
-        lay.total(acc_h, i, &r->flux, &r->steps);
+        memcpy(&r->flux, &acc_h[i], sizeof(r->flux));
+        r->steps = acc_h[n + i];
         if (r->host_dest)
             memcpy(r->dest, (char *)srv->host_base + r->host_off, r->img_bytes);
+        if (r->in_place) srv->dests.erase(r->dest);
         r->latency_ms =
             std::chrono::duration<double, std::milli>(w->t_done - r->t_submit).count();
         r->state = 3;
@@ -199,6 +202,7 @@ static void fail_wave(dart_server *srv, Wave *w, dart_status st, const std::stri
         r->state = 4;
         r->err = st;
         r->err_msg = msg;
+        if (r->in_place) srv->dests.erase(r->dest);
         srv->dev_arena.release(r->dev_off, r->img_bytes);
         if (r->host_dest) srv->host_arena.release(r->host_off, r->img_bytes);
         const_cast<dart_stack *>(r->stack)->pinned--;
@@ -270,7 +274,11 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         stacks[i] = r->stack;
         views[i] = r->view;
         views[i].flags |= DART_DEVICE_PTRS;
-        imgs[i] = (char *)srv->dev_base + r->dev_off;
+        // Device destinations are rendered in place (a copy command per request
+        // took about 5 us of the wave's stream each); a destination that another
+        // request in flight also has is staged, so each gets a whole image.
+        r->in_place = !r->host_dest && srv->dests.insert(r->dest).second;
+        imgs[i] = r->in_place ? r->dest : (void *)((char *)srv->dev_base + r->dev_off);
     }
     dart_tuning tun = tuning_for(stacks[0]);
     // Every wave is planned here, on the scheduler thread, while the other
@@ -299,7 +307,6 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         if (parts == 0 || parts_off + parts * 8 <= srv->desc_cap) break;
     }
     if (acc_off + lay.words() * 8 > srv->desc_cap) {
-        w->compact = true;
         lay = SumLayout(n, groups.size(), true);
     }
     if (acc_off + lay.words() * 8 > srv->desc_cap) {
@@ -326,7 +333,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     lk.unlock();
     hipError_t e = hipEventRecord(srv->ev_begin[sidx], stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(ddesc, hstage, desc_bytes, hipMemcpyHostToDevice, stream);
+        e = launch_begin(dacc, lay.words(), ddesc, hstage, desc_bytes / 8, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kbegin[sidx], stream);
     if (e == hipSuccess)
         e = enqueue_plan(groups, lay, dacc, true, (double *)(ddesc + parts_off), (const RayView *)ddesc,
@@ -337,16 +344,14 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         if (r->host_dest)
             e = hipMemcpyAsync((char *)srv->host_base + r->host_off, imgs[i], r->img_bytes,
                                hipMemcpyDeviceToHost, stream);
-        else
+        else if (!r->in_place)
             e = hipMemcpyAsync(r->dest, imgs[i], r->img_bytes, hipMemcpyDeviceToDevice, stream);
     }
-    // the flux and step accumulators overwrite the (already consumed) descriptor staging
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(hstage, dacc + lay.heads_words(), lay.sum_words() * 8,
-                           hipMemcpyDeviceToHost, stream);
+    // flux and steps overwrite the (already consumed) descriptor staging
+    if (e == hipSuccess) e = launch_totals(lay.sums(dacc), n, hstage, stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_end[sidx], stream);
     if (e == hipSuccess) {
-        for (int32_t i = 0; i < n; i++) note_use(stacks[i], stream);
+        note_uses(stacks.data(), n, stream);
         e = hipLaunchHostFunc(stream, on_wave_done, wp);
     }
     const Clock::time_point t_enqueued = Clock::now();
