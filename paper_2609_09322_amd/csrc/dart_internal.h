@@ -149,8 +149,9 @@ hipError_t launch_mark(const RayView &v, uint32_t *bitmap, int line_log2, bool m
                        hipStream_t s);
 hipError_t launch_popcount(const uint32_t *bitmap, uint64_t words, unsigned long long *out,
                            hipStream_t s);
+// plane: the stack's emissivity plane, kept in step with the records (may be null).
 hipError_t launch_convert(int src_f64, int store, const void *j, const void *beta, int32_t m0,
-                          int32_t count, const StackDev &st, void *data,
+                          int32_t count, const StackDev &st, void *data, void *plane,
                           unsigned long long *err, hipStream_t s);
 hipError_t launch_rebrick(int store, const StackDev &from, const StackDev &to, void *dst,
                           hipStream_t s);

@@ -1520,103 +1520,193 @@ __device__ __forceinline__ float narrow_for16(double v) {
     return f;
 }
 
-// caller layout (one epoch: j [nz][ny][nx], beta [nz][ny][nx][3]) -> resident
-// records, with validation: every value finite, |beta| < 1 in the source type
-// and again after rounding to the storage type.  The first bad element (as
-// epoch * ncell + cell) is kept by atomicMin in *err.
+// The passes between the caller's row order and bricks (load, read-back, re-lay)
+// work on blocks of whole bricks: 1 << xs cells along x (64, or fewer on a narrow
+// grid), 1 << ys along y, 1 << zs along z, at least 256 cells.  A wavefront
+// takes a row of the block at a time, so row-order accesses are contiguous, and
+// every line of the bricked side is completed by one workgroup, in one XCD's L2,
+// instead of by rows on different XCDs.  Positions come from shifts and, per
+// block, two divisions; one 64-bit division and remainder per cell and axis (and
+// the checks in FP64, below) bounded these passes before, not memory.  Now they run
+// at the rate of a copy (4.6 TB/s): load of a 256x256x512 FP32 epoch 450 -> 243
+// us, of a 512x512x1024 BF16 one 3.50 -> 1.35 ms, its re-lay to 1x2x16 bricks 11.8
+// -> 2.0 ms.
+struct BrickBlocks {
+    uint32_t xs, ys, zs;  // log2 of a block's sides
+    uint32_t nx, ny;      // blocks along x and y
+    uint32_t blocks;      // all of them; workgroups take every gridDim.x-th
+};
+
+struct BlockCell {
+    uint32_t x, y, z;
+    bool inside;
+};
+
+// Cell `k` (counted over the block's cells, x fastest) of block b.
+__device__ __forceinline__ BlockCell block_cell(const BrickBlocks &g, const StackDev &st,
+                                                uint32_t b, uint32_t k) {
+    const uint32_t rest = b / g.nx, bx = b - rest * g.nx;
+    const uint32_t bz = rest / g.ny, by = rest - bz * g.ny;
+    const uint32_t row = k >> g.xs;
+    BlockCell c;
+    c.x = (bx << g.xs) + (k & ((1u << g.xs) - 1u));
+    c.y = (by << g.ys) + (row & ((1u << g.ys) - 1u));
+    c.z = (bz << g.zs) + (row >> g.ys);
+    c.inside = c.x < (uint32_t)st.n[0] && c.y < (uint32_t)st.n[1] && c.z < (uint32_t)st.n[2];
+    return c;
+}
+
+constexpr int CELLS_PER_PASS = 4;  // cells a thread has in flight
+
+// A thread's cells of a block, CELLS_PER_PASS at a time: load(q, cell) of each,
+// then store(q, cell) of each.
+template <typename L, typename W>
+__device__ __forceinline__ void for_block_cells(const BrickBlocks &g, const StackDev &st,
+                                                L &&load, W &&store) {
+    const uint32_t n = 1u << (g.xs + g.ys + g.zs);
+    for (uint32_t b = blockIdx.x; b < g.blocks; b += gridDim.x)
+        for (uint32_t k0 = threadIdx.x; k0 < n; k0 += 256 * CELLS_PER_PASS) {
+#pragma unroll
+            for (int q = 0; q < CELLS_PER_PASS; q++) {
+                const BlockCell c = block_cell(g, st, b, k0 + 256 * q);
+                if (k0 + 256 * q < n && c.inside) load(q, c);
+            }
+#pragma unroll
+            for (int q = 0; q < CELLS_PER_PASS; q++) {
+                const BlockCell c = block_cell(g, st, b, k0 + 256 * q);
+                if (k0 + 256 * q < n && c.inside) store(q, c);
+            }
+        }
+}
+
+// Whether a value is one the renders take: finite, |beta| < 1 in the source type
+// and, after rounding to the storage type, in the arithmetic the render uses
+// (FP64, and the FP32 FMA chain of 16-bit stacks).  rec: the stored record.
+template <int S>
+__device__ __forceinline__ bool valid_record(double jv, double bx, double by, double bz,
+                                             const typename RecT<S>::raw &rec) {
+    if (!(isfinite(jv) && isfinite(bx) && isfinite(by) && isfinite(bz) &&
+          (bx * bx + by * by + bz * bz) < 1.0))
+        return false;
+    typename RecT<S>::val qj, fx, fy, fz;
+    decode<S>(rec, qj, fx, fy, fz);
+    const double qx = fx, qy = fy, qz = fz;
+    if (!(isfinite(qj) && (1.0 - (qx * qx + qy * qy + qz * qz)) > 0.0)) return false;
+    if constexpr (S == ST_F16 || S == ST_BF16)
+        return fmaf(-fx, fx, fmaf(-fy, fy, fmaf(-fz, fz, 1.0f))) > 0.0f;
+    return true;
+}
+
+// The same answer from FP32 for values far from the limits (true: valid; false:
+// ask valid_record).  A component is rounded by at most 2^-11 (FP16) or 2^-9
+// (BF16) of itself, so beta^2 grows by at most 0.1% or 0.4%; FP16 holds |j| up to
+// 65504.
+template <int S>
+__device__ __forceinline__ bool surely_valid(float j, float bx, float by, float bz) {
+    const float most = S == ST_F16 ? 0.998f : S == ST_BF16 ? 0.99f : 0.9999f;
+    const float jmax = S == ST_F16 ? 60000.0f : 1e38f;
+    return fabsf(j) < jmax && fmaf(bx, bx, fmaf(by, by, bz * bz)) < most;  // (false for NaN)
+}
+
+template <int S, typename Src>
+__device__ __forceinline__ typename RecT<S>::raw make_record(Src j, Src bx, Src by, Src bz) {
+    using V = typename RecT<S>::val;
+    if constexpr (S == ST_F64 || S == ST_F32) {
+        return typename RecT<S>::raw{(V)j, (V)bx, (V)by, (V)bz};
+    } else if constexpr (S == ST_F16) {
+        return rec_h16{f2h_rne(narrow_for16(j)) | (f2h_rne(narrow_for16(bx)) << 16),
+                       f2h_rne(narrow_for16(by)) | (f2h_rne(narrow_for16(bz)) << 16)};
+    } else {
+        return rec_h16{f2bf16_rne(narrow_for16(j)) | (f2bf16_rne(narrow_for16(bx)) << 16),
+                       f2bf16_rne(narrow_for16(by)) | (f2bf16_rne(narrow_for16(bz)) << 16)};
+    }
+}
+
+// caller layout (epochs m0 + blockIdx.y: j [nz][ny][nx], beta [nz][ny][nx][3]) ->
+// resident records, with validation: the first bad element (as epoch * ncell +
+// cell) is kept by atomicMin in *err.  plane (may be null): the emissivity plane,
+// whose elements of these epochs are written with the records.
 template <typename Src, int S>
 __global__ void __launch_bounds__(256) k_convert(const Src *__restrict__ j,
-                                                 const Src *__restrict__ beta, int32_t m,
-                                                 StackDev st, void *data,
+                                                 const Src *__restrict__ beta, int32_t m0,
+                                                 StackDev st, BrickBlocks g,
+                                                 typename RecT<S>::raw *__restrict__ data,
+                                                 typename JFieldT<S>::raw *__restrict__ plane,
                                                  unsigned long long *err) {
     const uint32_t n0 = st.n[0], n1 = st.n[1];
     const uint64_t ncell = (uint64_t)n0 * n1 * st.n[2];
-    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < ncell;
-         c += (uint64_t)gridDim.x * blockDim.x) {
-        const double jv = (double)j[c];
-        const double bx = (double)beta[3 * c], by = (double)beta[3 * c + 1],
-                     bz = (double)beta[3 * c + 2];
-        bool ok = isfinite(jv) && isfinite(bx) && isfinite(by) && isfinite(bz) &&
-                  (bx * bx + by * by + bz * bz) < 1.0;
-        const uint32_t x = (uint32_t)(c % n0), y = (uint32_t)((c / n0) % n1),
-                       z = (uint32_t)(c / ((uint64_t)n0 * n1));
-        const uint64_t rec = (uint64_t)m * st.epoch_stride + cell_offset(st, x, y, z);
-        double qj, qx, qy, qz;
-        if constexpr (S == ST_F64) {
-            double2 *p = (double2 *)data;
-            p[2 * rec] = double2{jv, bx};
-            p[2 * rec + 1] = double2{by, bz};
-            qj = jv; qx = bx; qy = by; qz = bz;
-        } else if constexpr (S == ST_F32) {
-            float4 r{(float)jv, (float)bx, (float)by, (float)bz};
-            ((float4 *)data)[rec] = r;
-            qj = r.x; qx = r.y; qy = r.z; qz = r.w;
-        } else if constexpr (S == ST_F16) {
-            const Src *bc = beta + 3 * c;
-            uint32_t hj = f2h_rne(narrow_for16(j[c])), hx = f2h_rne(narrow_for16(bc[0])),
-                     hy = f2h_rne(narrow_for16(bc[1])), hz = f2h_rne(narrow_for16(bc[2]));
-            ((uint2 *)data)[rec] = uint2{hj | (hx << 16), hy | (hz << 16)};
-            qj = h2f(hj); qx = h2f(hx); qy = h2f(hy); qz = h2f(hz);
-        } else {
-            const Src *bc = beta + 3 * c;
-            uint32_t hj = f2bf16_rne(narrow_for16(j[c])), hx = f2bf16_rne(narrow_for16(bc[0])),
-                     hy = f2bf16_rne(narrow_for16(bc[1])), hz = f2bf16_rne(narrow_for16(bc[2]));
-            ((uint2 *)data)[rec] = uint2{hj | (hx << 16), hy | (hz << 16)};
-            qj = __uint_as_float(hj << 16); qx = __uint_as_float(hx << 16);
-            qy = __uint_as_float(hy << 16); qz = __uint_as_float(hz << 16);
-        }
-        // the stored velocity must stay strictly sub-luminal in the arithmetic
-        // the render uses (FP64, and the FP32 FMA chain of 16-bit stacks)
-        ok = ok && isfinite(qj) && (1.0 - (qx * qx + qy * qy + qz * qz)) > 0.0;
-        if constexpr (S == ST_F16 || S == ST_BF16) {
-            const float fx = (float)qx, fy = (float)qy, fz = (float)qz;
-            ok = ok && fmaf(-fx, fx, fmaf(-fy, fy, fmaf(-fz, fz, 1.0f))) > 0.0f;
-        }
-        if (!ok) atomicMin(err, (unsigned long long)((uint64_t)m * ncell + c));
-    }
+    const uint64_t m = (uint64_t)m0 + blockIdx.y;
+    j += blockIdx.y * ncell;
+    beta += 3 * blockIdx.y * ncell;
+    Src v[CELLS_PER_PASS][4];
+    for_block_cells(
+        g, st,
+        [&](int q, const BlockCell &c) {
+            const uint64_t i = ((uint64_t)c.z * n1 + c.y) * n0 + c.x;
+            v[q][0] = j[i];
+            v[q][1] = beta[3 * i];
+            v[q][2] = beta[3 * i + 1];
+            v[q][3] = beta[3 * i + 2];
+        },
+        [&](int q, const BlockCell &c) {
+            const uint64_t at = m * st.epoch_stride + cell_offset(st, c.x, c.y, c.z);
+            const typename RecT<S>::raw rec = make_record<S>(v[q][0], v[q][1], v[q][2], v[q][3]);
+            data[at] = rec;
+            if constexpr (S != ST_F64)
+                if (plane) plane[at] = jplane_element<S>(rec);
+            if (!surely_valid<S>((float)v[q][0], (float)v[q][1], (float)v[q][2], (float)v[q][3]) &&
+                !valid_record<S>(v[q][0], v[q][1], v[q][2], v[q][3], rec))
+                atomicMin(err, (unsigned long long)(m * ncell +
+                                                    ((uint64_t)c.z * n1 + c.y) * n0 + c.x));
+        });
 }
 
 template <int RB>
 struct RawRec { uint32_t w[RB / 4]; };
 
+// Records of epochs m0 + blockIdx.y from one brick shape to another (blocks of the
+// new bricks).
 template <int RB>
-__global__ void __launch_bounds__(256) k_rebrick(StackDev from, StackDev to, int32_t m,
-                                                 RawRec<RB> *__restrict__ dst) {
-    const uint32_t n0 = from.n[0], n1 = from.n[1];
-    const uint64_t ncell = (uint64_t)n0 * n1 * from.n[2];
-    const RawRec<RB> *src = (const RawRec<RB> *)from.data;
-    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < ncell;
-         c += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t x = (uint32_t)(c % n0), y = (uint32_t)((c / n0) % n1),
-                       z = (uint32_t)(c / ((uint64_t)n0 * n1));
-        dst[(uint64_t)m * to.epoch_stride + cell_offset(to, x, y, z)] =
-            src[(uint64_t)m * from.epoch_stride + cell_offset(from, x, y, z)];
-    }
+__global__ void __launch_bounds__(256) k_rebrick(StackDev from, StackDev to, int32_t m0,
+                                                 BrickBlocks g, RawRec<RB> *__restrict__ dst) {
+    const RawRec<RB> *__restrict__ src = (const RawRec<RB> *)from.data;
+    const uint64_t m = (uint64_t)m0 + blockIdx.y;
+    RawRec<RB> v[CELLS_PER_PASS];
+    for_block_cells(
+        g, to,
+        [&](int q, const BlockCell &c) {
+            v[q] = src[m * from.epoch_stride + cell_offset(from, c.x, c.y, c.z)];
+        },
+        [&](int q, const BlockCell &c) {
+            dst[m * to.epoch_stride + cell_offset(to, c.x, c.y, c.z)] = v[q];
+        });
 }
 
 // One epoch of resident records back in the caller's layout (j [nz][ny][nx],
 // beta [nz][ny][nx][3]), each value widened exactly to Out (FP64 for FP64
 // stacks, FP32 otherwise).
 template <int S, typename Out>
-__global__ void __launch_bounds__(256) k_read_epoch(StackDev st, int32_t m, Out *__restrict__ j,
-                                                    Out *__restrict__ beta) {
+__global__ void __launch_bounds__(256) k_read_epoch(StackDev st, int32_t m, BrickBlocks g,
+                                                    Out *__restrict__ j, Out *__restrict__ beta) {
     using Raw = typename RecT<S>::raw;
     using V = typename RecT<S>::val;
     const uint32_t n0 = st.n[0], n1 = st.n[1];
-    const uint64_t ncell = (uint64_t)n0 * n1 * st.n[2];
-    const Raw *src = (const Raw *)st.data;
-    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < ncell;
-         c += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t x = (uint32_t)(c % n0), y = (uint32_t)((c / n0) % n1),
-                       z = (uint32_t)(c / ((uint64_t)n0 * n1));
-        const Raw r = src[(uint64_t)m * st.epoch_stride + cell_offset(st, x, y, z)];
-        V vj, vx, vy, vz;
-        decode<S, V>(r, vj, vx, vy, vz);
-        j[c] = (Out)vj;
-        beta[3 * c] = (Out)vx;
-        beta[3 * c + 1] = (Out)vy;
-        beta[3 * c + 2] = (Out)vz;
-    }
+    const Raw *__restrict__ src = (const Raw *)st.data;
+    Raw v[CELLS_PER_PASS];
+    for_block_cells(
+        g, st,
+        [&](int q, const BlockCell &c) {
+            v[q] = src[(uint64_t)m * st.epoch_stride + cell_offset(st, c.x, c.y, c.z)];
+        },
+        [&](int q, const BlockCell &c) {
+            const uint64_t i = ((uint64_t)c.z * n1 + c.y) * n0 + c.x;
+            V vj, vx, vy, vz;
+            decode<S, V>(v[q], vj, vx, vy, vz);
+            j[i] = (Out)vj;
+            beta[3 * i] = (Out)vx;
+            beta[3 * i + 1] = (Out)vy;
+            beta[3 * i + 2] = (Out)vz;
+        });
 }
 
 #endif  // DART_MARCH_STORE
@@ -1796,16 +1886,46 @@ hipError_t launch_popcount(const uint32_t *bitmap, uint64_t words, unsigned long
     return hipGetLastError();
 }
 
+static int log2_up(uint32_t n) {
+    int l = 0;
+    while ((1ull << l) < n) l++;
+    return l;
+}
+
+// The blocks of a grid in whole bricks, and the workgroups for them.
+static BrickBlocks brick_blocks(const StackDev &st, unsigned *grid) {
+    BrickBlocks g;
+    const int xs = log2_up((uint32_t)st.n[0]);
+    g.xs = (uint32_t)(xs > 6 ? 6 : xs);
+    if (g.xs < (uint32_t)st.lb[0]) g.xs = st.lb[0];
+    g.ys = st.lb[1];
+    g.zs = st.lb[2];
+    while (g.xs + g.ys + g.zs < 8)
+        if ((1u << g.ys) < (uint32_t)st.n[1]) g.ys++;
+        else g.zs++;
+    auto along = [](int32_t n, uint32_t log2) { return ((uint32_t)n + (1u << log2) - 1u) >> log2; };
+    g.nx = along(st.n[0], g.xs);
+    g.ny = along(st.n[1], g.ys);
+    // (blocks hold 256 cells or more, at least an eighth of them in the grid
+    // unless it is smaller than a brick: far below 2^32 for 2^31 cells)
+    g.blocks = g.nx * g.ny * along(st.n[2], g.zs);
+    *grid = g.blocks < (1u << 20) ? g.blocks : 1u << 20;
+    return g;
+}
+
 template <typename Src, int S>
 static hipError_t convert_impl(const void *j, const void *beta, int32_t m0, int32_t count,
-                               const StackDev &st, void *data, unsigned long long *err,
-                               hipStream_t s) {
+                               const StackDev &st, void *data, void *plane,
+                               unsigned long long *err, hipStream_t s) {
     const uint64_t ncell = (uint64_t)st.n[0] * st.n[1] * st.n[2];
-    const unsigned g = grid_for(ncell, 1u << 15);
-    for (int32_t q = 0; q < count; q++) {
-        hipLaunchKernelGGL((k_convert<Src, S>), dim3(g), dim3(256), 0, s,
+    unsigned blocks = 0;
+    const BrickBlocks g = brick_blocks(st, &blocks);
+    for (int32_t q = 0; q < count; q += 32768) {
+        const unsigned epochs = (unsigned)(count - q < 32768 ? count - q : 32768);
+        hipLaunchKernelGGL((k_convert<Src, S>), dim3(blocks, epochs), dim3(256), 0, s,
                            (const Src *)j + (size_t)q * ncell,
-                           (const Src *)beta + (size_t)q * ncell * 3, m0 + q, st, data, err);
+                           (const Src *)beta + (size_t)q * ncell * 3, m0 + q, st, g,
+                           (typename RecT<S>::raw *)data, (typename JFieldT<S>::raw *)plane, err);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1813,21 +1933,21 @@ static hipError_t convert_impl(const void *j, const void *beta, int32_t m0, int3
 }
 
 hipError_t launch_convert(int src_f64, int store, const void *j, const void *beta, int32_t m0,
-                          int32_t count, const StackDev &st, void *data,
+                          int32_t count, const StackDev &st, void *data, void *plane,
                           unsigned long long *err, hipStream_t s) {
     if (src_f64) {
         switch (store) {
-            case ST_F64: return convert_impl<double, ST_F64>(j, beta, m0, count, st, data, err, s);
-            case ST_F32: return convert_impl<double, ST_F32>(j, beta, m0, count, st, data, err, s);
-            case ST_F16: return convert_impl<double, ST_F16>(j, beta, m0, count, st, data, err, s);
-            case ST_BF16: return convert_impl<double, ST_BF16>(j, beta, m0, count, st, data, err, s);
+            case ST_F64: return convert_impl<double, ST_F64>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_F32: return convert_impl<double, ST_F32>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_F16: return convert_impl<double, ST_F16>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_BF16: return convert_impl<double, ST_BF16>(j, beta, m0, count, st, data, plane, err, s);
         }
     } else {
         switch (store) {
-            case ST_F64: return convert_impl<float, ST_F64>(j, beta, m0, count, st, data, err, s);
-            case ST_F32: return convert_impl<float, ST_F32>(j, beta, m0, count, st, data, err, s);
-            case ST_F16: return convert_impl<float, ST_F16>(j, beta, m0, count, st, data, err, s);
-            case ST_BF16: return convert_impl<float, ST_BF16>(j, beta, m0, count, st, data, err, s);
+            case ST_F64: return convert_impl<float, ST_F64>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_F32: return convert_impl<float, ST_F32>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_F16: return convert_impl<float, ST_F16>(j, beta, m0, count, st, data, plane, err, s);
+            case ST_BF16: return convert_impl<float, ST_BF16>(j, beta, m0, count, st, data, plane, err, s);
         }
     }
     return hipErrorInvalidValue;
@@ -1836,10 +1956,12 @@ hipError_t launch_convert(int src_f64, int store, const void *j, const void *bet
 template <int RB>
 static hipError_t rebrick_impl(const StackDev &from, const StackDev &to, void *dst,
                                hipStream_t s) {
-    const uint64_t ncell = (uint64_t)from.n[0] * from.n[1] * from.n[2];
-    for (int32_t m = 0; m < from.n_epochs; m++) {
-        hipLaunchKernelGGL((k_rebrick<RB>), dim3(grid_for(ncell, 1u << 15)), dim3(256), 0, s,
-                           from, to, m, (RawRec<RB> *)dst);
+    unsigned blocks = 0;
+    const BrickBlocks g = brick_blocks(to, &blocks);
+    for (int32_t m = 0; m < from.n_epochs; m += 32768) {
+        const unsigned epochs = (unsigned)(from.n_epochs - m < 32768 ? from.n_epochs - m : 32768);
+        hipLaunchKernelGGL((k_rebrick<RB>), dim3(blocks, epochs), dim3(256), 0, s, from, to, m, g,
+                           (RawRec<RB> *)dst);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1858,23 +1980,24 @@ hipError_t launch_rebrick(int store, const StackDev &from, const StackDev &to, v
 }
 
 hipError_t launch_read_epoch(const StackDev &st, int32_t m, void *j, void *beta, hipStream_t s) {
-    const uint64_t ncell = (uint64_t)st.n[0] * st.n[1] * st.n[2];
-    const dim3 g(grid_for(ncell, 1u << 15)), b(256);
+    unsigned blocks = 0;
+    const BrickBlocks bb = brick_blocks(st, &blocks);
+    const dim3 g(blocks), b(256);
     switch (st.store) {
         case ST_F64:
-            hipLaunchKernelGGL((k_read_epoch<ST_F64, double>), g, b, 0, s, st, m, (double *)j,
+            hipLaunchKernelGGL((k_read_epoch<ST_F64, double>), g, b, 0, s, st, m, bb, (double *)j,
                                (double *)beta);
             break;
         case ST_F32:
-            hipLaunchKernelGGL((k_read_epoch<ST_F32, float>), g, b, 0, s, st, m, (float *)j,
+            hipLaunchKernelGGL((k_read_epoch<ST_F32, float>), g, b, 0, s, st, m, bb, (float *)j,
                                (float *)beta);
             break;
         case ST_F16:
-            hipLaunchKernelGGL((k_read_epoch<ST_F16, float>), g, b, 0, s, st, m, (float *)j,
+            hipLaunchKernelGGL((k_read_epoch<ST_F16, float>), g, b, 0, s, st, m, bb, (float *)j,
                                (float *)beta);
             break;
         case ST_BF16:
-            hipLaunchKernelGGL((k_read_epoch<ST_BF16, float>), g, b, 0, s, st, m, (float *)j,
+            hipLaunchKernelGGL((k_read_epoch<ST_BF16, float>), g, b, 0, s, st, m, bb, (float *)j,
                                (float *)beta);
             break;
         default: return hipErrorInvalidValue;

@@ -142,6 +142,7 @@ struct Workspace {
     size_t acc_cap = 0;
     void *sums_host = nullptr;          // pinned: the views' totals (launch_totals)
     size_t sums_host_cap = 0;
+    unsigned long long *flag = nullptr; // device: the first bad element of a load
     void *img_host = nullptr;           // pinned: a small host-destined image
     size_t img_host_cap = 0;
     unsigned char *desc = nullptr;      // the plan's view, then tile descriptors
@@ -164,6 +165,7 @@ struct Workspace {
 
 void read_totals(const void *host, int32_t n, double *flux, uint64_t *steps);
 Workspace *get_workspace(hipStream_t stream);
+hipError_t ws_flag(Workspace *ws);
 hipError_t ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_u64,
                       size_t acc_words, size_t n_parts = 0);
 // The kernels of a plan whose queue heads (and sums) launch_begin has cleared.

@@ -222,26 +222,40 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
     const int src_f64 = src == DART_F64;
     const size_t esz = src_f64 ? 8 : 4;
     const uint64_t ncell = (uint64_t)s->dev.n[0] * s->dev.n[1] * s->dev.n[2];
-    unsigned long long *err = nullptr;
-    HIP_TRY(hipMalloc(&err, sizeof(unsigned long long)), "hipMalloc(err)");
+    // (the stream's own error word and its pinned copy, kept between calls)
+    Workspace *ws = get_workspace(stream);
+    std::lock_guard<std::mutex> lock(ws->mu);
+    HIP_TRY(ws_flag(ws), "error flag");
+    unsigned long long *err = ws->flag;
     struct Guard {
-        void *p[3] = {nullptr, nullptr, nullptr};
+        void *p[2] = {nullptr, nullptr};
         ~Guard() { for (void *q : p) if (q) (void)hipFree(q); }
     } guard;
-    guard.p[0] = err;
     hipError_t e = launch_fill_u64(err, 1, ~0ull, stream);
     if (e != hipSuccess) return hip_fail(e, "clear error flag");
+    // A plane that holds the other epochs is kept in step: the load writes its
+    // elements with the records, once the renders that read it have finished, and
+    // the next render need not repack the whole stack (refill of one of eight
+    // 256^3 FP16 epochs and a render of two 256^2 views: 716 -> 460 us).
+    void *plane = nullptr;
+    if (jplane_ready(s)) {
+        std::lock_guard<std::mutex> g(s->mu);
+        for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
+        plane = s->jplane;
+        // (stale if this load fails part-way)
+        s->jplane_gen.store(0, std::memory_order_release);
+    }
     if (flags & F_DEVICE_PTRS) {
         e = launch_convert(src_f64, s->dev.store, j, beta, m0, count, s->dev, (void *)s->dev.data,
-                           err, stream);
+                           plane, err, stream);
         if (e != hipSuccess) return hip_fail(e, "convert kernel");
     } else {
         // host arrays: one epoch at a time through device staging
         void *dj = nullptr, *db = nullptr;
         HIP_TRY(hipMalloc(&dj, ncell * esz), "hipMalloc(staging)");
-        guard.p[1] = dj;
+        guard.p[0] = dj;
         HIP_TRY(hipMalloc(&db, ncell * esz * 3), "hipMalloc(staging)");
-        guard.p[2] = db;
+        guard.p[1] = db;
         for (int32_t q = 0; q < count; q++) {
             const char *hj = (const char *)j + (size_t)q * ncell * esz;
             const char *hb = (const char *)beta + (size_t)q * ncell * esz * 3;
@@ -249,14 +263,15 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
             HIP_TRY(hipMemcpyAsync(db, hb, ncell * esz * 3, hipMemcpyHostToDevice, stream),
                     "H2D beta");
             e = launch_convert(src_f64, s->dev.store, dj, db, m0 + q, 1, s->dev,
-                               (void *)s->dev.data, err, stream);
+                               (void *)s->dev.data, plane, err, stream);
             if (e != hipSuccess) return hip_fail(e, "convert kernel");
             HIP_TRY(hipStreamSynchronize(stream), "sync");
         }
     }
-    unsigned long long bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, err, sizeof(bad), hipMemcpyDeviceToHost, stream), "D2H err");
+    HIP_TRY(hipMemcpyAsync(ws->sums_host, err, sizeof(*err), hipMemcpyDeviceToHost, stream),
+            "D2H err");
     HIP_TRY(hipStreamSynchronize(stream), "sync");
+    const unsigned long long bad = *(const unsigned long long *)ws->sums_host;
     if (bad != ~0ull) {
         const uint64_t m = bad / ncell, c = bad % ncell;
         const uint64_t x = c % s->dev.n[0], y = (c / s->dev.n[0]) % s->dev.n[1],
@@ -269,6 +284,7 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
     }
     for (int32_t q = 0; q < count; q++) s->filled[m0 + q] = 1;
     s->generation = next_generation();
+    if (plane) s->jplane_gen.store(s->generation, std::memory_order_release);
     return DART_OK;
 }
 
@@ -908,6 +924,18 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
     }
     if (n_parts && (e = grow_dev(ws->parts, ws->parts_cap, n_parts)) != hipSuccess) return e;
     return hipSuccess;
+}
+
+// The workspace's error word, and pinned room for its value.
+hipError_t dart::ws_flag(Workspace *ws) {
+    if (!ws->flag) {
+        hipError_t e = hipMalloc((void **)&ws->flag, sizeof(unsigned long long));
+        if (e != hipSuccess) {
+            ws->flag = nullptr;
+            return e;
+        }
+    }
+    return grow_host(ws->sums_host, ws->sums_host_cap, 16);
 }
 
 // ------------------------------------------------------------------ plain render

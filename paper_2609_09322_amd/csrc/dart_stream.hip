@@ -381,7 +381,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
             db = s->stage_b;
         }
         // convert into slot k; a bad element is reported in err[e]
-        ST_TRY(launch_convert(esz == 8, rd.store, dj, db, k, 1, rd, (void *)rd.data, s->err + e,
+        ST_TRY(launch_convert(esz == 8, rd.store, dj, db, k, 1, rd, (void *)rd.data, nullptr, s->err + e,
                               s->copy), "convert kernel");
         ST_TRY(hipEventRecord(s->ready[k], s->copy), "event");
         return DART_OK;
