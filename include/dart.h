@@ -139,11 +139,12 @@ dart_status dart_stack_set_epochs(dart_stack *s, int32_t m0, int32_t count, dart
  * reads it is still running on the device. */
 dart_status dart_free_epochs(dart_stack *s);
 
-/* Emissivity plane.  A plain stack with FP32, FP16 or BF16 records also keeps
- * its emissivity alone, one value per record at the record's own index (a
+/* Emissivity plane.  A plain stack with FP32, FP16 or BF16 records, or with FP64
+ * records of more than 256 MiB in all, also keeps its emissivity alone, one value per record at the record's own index (a
  * quarter of the record bytes), packed on the device by the first render
  * after its records change (not inside a stream capture, and by
- * dart_render_batch_noalloc only into a plane already allocated).  The value's
+ * dart_render_batch_noalloc only into a plane already allocated); loads into a
+ * stack whose plane is packed keep it in step.  The value's
  * sign bit marks records that must be read whole: any velocity bit set, or a
  * negative (or -0) emissivity.  A render reads the plane, and whole records
  * only of the marked elements; a jet's volume at rest is then read at a
@@ -152,7 +153,7 @@ dart_status dart_free_epochs(dart_stack *s);
  * (DART_RECORDS_ONLY).  Without room for the plane (hipMalloc fails) renders
  * read whole records, as do views with DART_NO_KAHAN.  Planes of at most 4 GiB
  * are read through 32-bit offsets, larger ones through 64-bit addresses
- * (DART_PLANE_ADDR64 asks for those on any plane).  FP64, labelled, vector and
+ * (DART_PLANE_ADDR64 asks for those on any plane).  Labelled, vector and
  * streamed stacks have none. */
 typedef struct {
     int32_t dims[3];

@@ -163,20 +163,20 @@ __device__ __forceinline__ typename RecT<S>::val decode_j(typename JFieldT<S>::r
     else return __uint_as_float((uint32_t)w << 16);
 }
 
-// decode_j(b) - decode_j(a) in FP32, of two loaded plane elements (16-bit
+// decode_j(b) - decode_j(a) of two loaded plane elements (16-bit
 // elements as their bits zero-extended to 32, as the load leaves them).  FP16:
 // one mixed-precision fma, b * 1 - a with both operands converted exactly and
 // one rounding: the same value as the difference of the converted elements,
 // without the two conversions.
 template <int S, typename Q>
-__device__ __forceinline__ float plane_diff(Q a, Q b) {
+__device__ __forceinline__ typename RecT<S>::val plane_diff(Q a, Q b) {
     using JF = typename JFieldT<S>::raw;
     if constexpr (S == ST_F16) {
         float d;
         asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,1]" : "=v"(d) : "v"(b), "v"(a));
         return d;
     } else {
-        return (float)decode_j<S>((JF)b) - (float)decode_j<S>((JF)a);
+        return decode_j<S>((JF)b) - decode_j<S>((JF)a);
     }
 }
 
@@ -184,20 +184,26 @@ __device__ __forceinline__ float plane_diff(Q a, Q b) {
 // storage type, with its sign bit standing for "read the whole record": set
 // when the velocity bits are not all zero or j itself has its sign bit set
 // (negative, or -0).  An element without the mark is the record's j, exactly.
+// (jplane_bits of an FP64 element: its high word, which holds the sign.)
 template <int S>
 __device__ __forceinline__ uint32_t jplane_bits(typename JFieldT<S>::raw w) {
-    if constexpr (S == ST_F32) return __float_as_uint(w);
+    if constexpr (S == ST_F64) return (uint32_t)__double2hiint(w);
+    else if constexpr (S == ST_F32) return __float_as_uint(w);
     else return (uint32_t)w;
 }
 // the mark of an element, or of the OR of several elements' bits
 template <int S>
 __device__ __forceinline__ uint32_t jplane_mark(uint32_t bits) {
-    if constexpr (S == ST_F32) return bits >> 31;
+    if constexpr (S == ST_F64 || S == ST_F32) return bits >> 31;
     else return (bits >> 15) & 1u;
 }
 template <int S>
 __device__ __forceinline__ typename JFieldT<S>::raw jplane_element(const typename RecT<S>::raw &r) {
-    if constexpr (S == ST_F32) {
+    if constexpr (S == ST_F64) {
+        const uint64_t jb = (uint64_t)__double_as_longlong(r.x);
+        const uint64_t mark = (beta_bits<S>(r) != 0u || (jb >> 63)) ? 1u : 0u;
+        return __longlong_as_double((long long)((jb & ~(1ull << 63)) | (mark << 63)));
+    } else if constexpr (S == ST_F32) {
         const uint32_t jb = __float_as_uint(r.x);
         const uint32_t mark = (beta_bits<S>(r) != 0u || (jb >> 31)) ? 1u : 0u;
         return __uint_as_float((jb & 0x7fffffffu) | (mark << 31));
@@ -677,11 +683,7 @@ __device__ __forceinline__ void mark_ray(const RayView &v, int pi, int pj, uint3
             // (the whole-record mark of the sample of epoch m)
             auto whole = [&](int m) {
                 const Raw *rec = (const Raw *)st.data + ((int64_t)m * st.epoch_stride + r.off);
-                if constexpr (S == ST_F64) {
-                    return beta_bits<S>(*rec) != 0u || signbit(rec->x);
-                } else {
-                    return jplane_mark<S>(jplane_bits<S>(jplane_element<S>(*rec))) != 0u;
-                }
+                return jplane_mark<S>(jplane_bits<S>(jplane_element<S>(*rec))) != 0u;
             };
             if ((single || wt < (R)1) && (!moving_only || whole(m0))) {
                 const uint64_t b = ((uint64_t)m0 * stride + lin) >> sh;
@@ -734,6 +736,7 @@ __device__ __forceinline__ double lerp_w(double a, double b, double w) {
 // The same with the difference given (the emissivity plane's FP16 difference
 // is one mixed-precision fma).
 __device__ __forceinline__ float lerp_d(float a, float d, float w) { return fmaf(w, d, a); }
+__device__ __forceinline__ double lerp_d(double a, double d, double w) { return fma(w, d, a); }
 
 // Cells walked per batch (K): a lane walks K cells of its ray, then issues all
 // their record loads back to back, then consumes them.  The batched kernel
@@ -826,13 +829,14 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     using GRaw = const Raw __attribute__((address_space(1)));
     using JF = typename JFieldT<S>::raw;
     using GJ = const JF __attribute__((address_space(1)));
-    static_assert(!(JP && (VEC || S == ST_F64)), "no emissivity plane for these stacks");
+    static_assert(!(JP && VEC), "no emissivity plane for these stacks");
     // The walk addresses elements of the emissivity plane (JP) or records:
     // both have the record index space, so one offset serves either.
     using E = typename std::conditional<JP != 0, JF, Raw>::type;
     using GE = const E __attribute__((address_space(1)));
     constexpr bool O32 = JP == 2;
-    constexpr uint32_t ESH = sizeof(JF) == 2 ? 1u : 2u;  // log2 of the element size
+    // log2 of the element size
+    constexpr uint32_t ESH = sizeof(JF) == 2 ? 1u : sizeof(JF) == 4 ? 2u : 3u;
     using GB = const uint8_t __attribute__((address_space(1)));
     // a cell's element: its address, or (O32) its byte offset in the plane
     using Addr = typename std::conditional<O32, uint32_t, GE *>::type;
@@ -1652,8 +1656,7 @@ __global__ void __launch_bounds__(256) k_convert(const Src *__restrict__ j,
             const uint64_t at = m * st.epoch_stride + cell_offset(st, c.x, c.y, c.z);
             const typename RecT<S>::raw rec = make_record<S>(v[q][0], v[q][1], v[q][2], v[q][3]);
             data[at] = rec;
-            if constexpr (S != ST_F64)
-                if (plane) plane[at] = jplane_element<S>(rec);
+            if (plane) plane[at] = jplane_element<S>(rec);
             if (!surely_valid<S>((float)v[q][0], (float)v[q][1], (float)v[q][2], (float)v[q][3]) &&
                 !valid_record<S>(v[q][0], v[q][1], v[q][2], v[q][3], rec))
                 atomicMin(err, (unsigned long long)(m * ncell +
@@ -1661,24 +1664,25 @@ __global__ void __launch_bounds__(256) k_convert(const Src *__restrict__ j,
         });
 }
 
-template <int RB>
-struct RawRec { uint32_t w[RB / 4]; };
-
 // Records of epochs m0 + blockIdx.y from one brick shape to another (blocks of the
-// new bricks).
-template <int RB>
+// new bricks), with the emissivity plane in the new order (plane may be null).
+template <int S>
 __global__ void __launch_bounds__(256) k_rebrick(StackDev from, StackDev to, int32_t m0,
-                                                 BrickBlocks g, RawRec<RB> *__restrict__ dst) {
-    const RawRec<RB> *__restrict__ src = (const RawRec<RB> *)from.data;
+                                                 BrickBlocks g,
+                                                 typename RecT<S>::raw *__restrict__ dst,
+                                                 typename JFieldT<S>::raw *__restrict__ plane) {
+    const typename RecT<S>::raw *__restrict__ src = (const typename RecT<S>::raw *)from.data;
     const uint64_t m = (uint64_t)m0 + blockIdx.y;
-    RawRec<RB> v[CELLS_PER_PASS];
+    typename RecT<S>::raw v[CELLS_PER_PASS];
     for_block_cells(
         g, to,
         [&](int q, const BlockCell &c) {
             v[q] = src[m * from.epoch_stride + cell_offset(from, c.x, c.y, c.z)];
         },
         [&](int q, const BlockCell &c) {
-            dst[m * to.epoch_stride + cell_offset(to, c.x, c.y, c.z)] = v[q];
+            const uint64_t at = m * to.epoch_stride + cell_offset(to, c.x, c.y, c.z);
+            dst[at] = v[q];
+            if (plane) plane[at] = jplane_element<S>(v[q]);
         });
 }
 
@@ -1731,18 +1735,16 @@ hipError_t plain_impl(const RayView &v, const RenderSums &sums, hipStream_t s) {
     static_assert(MAX_SEG_LOG2 <= 2, "a workgroup of k_plain holds a tile's segments");
     const dim3 g((unsigned)((waves + 3) / 4)), b(256);
     const bool lab = v.n_blocks > 0, ex = (v.flags & F_EXACT) != 0;
-    if constexpr (S != ST_F64) {
-        // (the planner gives an emissivity plane only to plain stacks)
-        if (v.st.jplane && !lab && v.n_chan == 1) {
-            if (v.flags & F_PLANE32) {
-                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 2>), g, b, 0, s, v, sums);
-                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 2>), g, b, 0, s, v, sums);
-            } else {
-                if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 1>), g, b, 0, s, v, sums);
-                else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 1>), g, b, 0, s, v, sums);
-            }
-            return hipGetLastError();
+    // (the planner gives an emissivity plane only to plain stacks)
+    if (v.st.jplane && !lab && v.n_chan == 1) {
+        if (v.flags & F_PLANE32) {
+            if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 2>), g, b, 0, s, v, sums);
+            else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 2>), g, b, 0, s, v, sums);
+        } else {
+            if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 1>), g, b, 0, s, v, sums);
+            else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 1>), g, b, 0, s, v, sums);
         }
+        return hipGetLastError();
     }
     if (v.n_chan > 1) hipLaunchKernelGGL((k_plain<S, R, false, false, true>), g, b, 0, s, v, sums);
     else if (lab && ex) hipLaunchKernelGGL((k_plain<S, R, true, true>), g, b, 0, s, v, sums);
@@ -1778,27 +1780,25 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
                                bl.tiles);
         return hipGetLastError();
     }
-    if constexpr (S != ST_F64) {
-        if ((variant & KV_JP) && (variant & KV_JP32)) {
-            switch (variant & 7) {
-                case 0: batch_launch_k<S, R, 0, false, false, 2>(bl, k8, grid_blocks, s); break;
-                case 1: batch_launch_k<S, R, 1, false, false, 2>(bl, k8, grid_blocks, s); break;
-                case 4: batch_launch_k<S, R, 0, false, true, 2>(bl, k8, grid_blocks, s); break;
-                case 5: batch_launch_k<S, R, 1, false, true, 2>(bl, k8, grid_blocks, s); break;
-                default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
-            }
-            return hipGetLastError();
+    if ((variant & KV_JP) && (variant & KV_JP32)) {
+        switch (variant & 7) {
+            case 0: batch_launch_k<S, R, 0, false, false, 2>(bl, k8, grid_blocks, s); break;
+            case 1: batch_launch_k<S, R, 1, false, false, 2>(bl, k8, grid_blocks, s); break;
+            case 4: batch_launch_k<S, R, 0, false, true, 2>(bl, k8, grid_blocks, s); break;
+            case 5: batch_launch_k<S, R, 1, false, true, 2>(bl, k8, grid_blocks, s); break;
+            default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
         }
-        if (variant & KV_JP) {
-            switch (variant & 7) {
-                case 0: batch_launch_k<S, R, 0, false, false, 1>(bl, k8, grid_blocks, s); break;
-                case 1: batch_launch_k<S, R, 1, false, false, 1>(bl, k8, grid_blocks, s); break;
-                case 4: batch_launch_k<S, R, 0, false, true, 1>(bl, k8, grid_blocks, s); break;
-                case 5: batch_launch_k<S, R, 1, false, true, 1>(bl, k8, grid_blocks, s); break;
-                default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
-            }
-            return hipGetLastError();
+        return hipGetLastError();
+    }
+    if (variant & KV_JP) {
+        switch (variant & 7) {
+            case 0: batch_launch_k<S, R, 0, false, false, 1>(bl, k8, grid_blocks, s); break;
+            case 1: batch_launch_k<S, R, 1, false, false, 1>(bl, k8, grid_blocks, s); break;
+            case 4: batch_launch_k<S, R, 0, false, true, 1>(bl, k8, grid_blocks, s); break;
+            case 5: batch_launch_k<S, R, 1, false, true, 1>(bl, k8, grid_blocks, s); break;
+            default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
         }
+        return hipGetLastError();
     }
     switch (variant & 7) {
         case 0: batch_launch_k<S, R, 0, false, false>(bl, k8, grid_blocks, s); break;
@@ -1953,15 +1953,15 @@ hipError_t launch_convert(int src_f64, int store, const void *j, const void *bet
     return hipErrorInvalidValue;
 }
 
-template <int RB>
-static hipError_t rebrick_impl(const StackDev &from, const StackDev &to, void *dst,
+template <int S>
+static hipError_t rebrick_impl(const StackDev &from, const StackDev &to, void *dst, void *plane,
                                hipStream_t s) {
     unsigned blocks = 0;
     const BrickBlocks g = brick_blocks(to, &blocks);
     for (int32_t m = 0; m < from.n_epochs; m += 32768) {
         const unsigned epochs = (unsigned)(from.n_epochs - m < 32768 ? from.n_epochs - m : 32768);
-        hipLaunchKernelGGL((k_rebrick<RB>), dim3(blocks, epochs), dim3(256), 0, s, from, to, m, g,
-                           (RawRec<RB> *)dst);
+        hipLaunchKernelGGL((k_rebrick<S>), dim3(blocks, epochs), dim3(256), 0, s, from, to, m, g,
+                           (typename RecT<S>::raw *)dst, (typename JFieldT<S>::raw *)plane);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1969,12 +1969,12 @@ static hipError_t rebrick_impl(const StackDev &from, const StackDev &to, void *d
 }
 
 hipError_t launch_rebrick(int store, const StackDev &from, const StackDev &to, void *dst,
-                          hipStream_t s) {
+                          void *plane, hipStream_t s) {
     switch (store) {
-        case ST_F64: return rebrick_impl<32>(from, to, dst, s);
-        case ST_F32: return rebrick_impl<16>(from, to, dst, s);
-        case ST_F16:
-        case ST_BF16: return rebrick_impl<8>(from, to, dst, s);
+        case ST_F64: return rebrick_impl<ST_F64>(from, to, dst, plane, s);
+        case ST_F32: return rebrick_impl<ST_F32>(from, to, dst, plane, s);
+        case ST_F16: return rebrick_impl<ST_F16>(from, to, dst, plane, s);
+        case ST_BF16: return rebrick_impl<ST_BF16>(from, to, dst, plane, s);
     }
     return hipErrorInvalidValue;
 }
@@ -2031,6 +2031,10 @@ hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_
                               hipStream_t s) {
     const dim3 g(grid_for(n, 1u << 15)), b(256);
     switch (store) {
+        case ST_F64:
+            hipLaunchKernelGGL(k_pack_jplane<ST_F64>, g, b, 0, s, (const rec_f64 *)records,
+                               (double *)out, n);
+            break;
         case ST_F32:
             hipLaunchKernelGGL(k_pack_jplane<ST_F32>, g, b, 0, s, (const rec_f32 *)records,
                                (float *)out, n);

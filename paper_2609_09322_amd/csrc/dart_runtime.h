@@ -46,13 +46,14 @@ struct dart_stack {
     std::vector<dart_stack *> comps;
     void *packed = nullptr;             // emissivity of components 1.., packed (device)
     std::vector<uint64_t> packed_gen;   // the components' generations when packed
-    // emissivity plane (StackDev::jplane) of a plain FP32 / 16-bit stack: built
+    // emissivity plane (StackDev::jplane) of a plain stack: built
     // at the first render after the records change, when memory allows
     void *jplane = nullptr;
     uint64_t jplane_bytes = 0;
     // the generation it was packed from (0: never); read without the lock by
     // planners on other threads, so published after the pack has completed
     std::atomic<uint64_t> jplane_gen{0};
+    std::vector<char> plane_ok;         // epochs whose elements are those of the records
     uint64_t jplane_no_room = 0;        // a generation for which hipMalloc failed
     bool vector() const { return !comps.empty(); }
     int channels() const { return comps.empty() ? 1 : (int)comps.size(); }

@@ -133,6 +133,32 @@ static void default_brick(int store, int lb[3]) {
     lb[2] = 1;
 }
 
+// The emissivity plane serves plain stacks (labelled and vector stacks read their
+// parts' records; streamed windows have no plane).  FP64 stacks have one when
+// their records exceed the 256 MB of last-level cache: up to there the records are
+// near already, and a marked element's second, dependent load costs more than the
+// plane's smaller ones save.  One 128^2 / 256^2 / 512^2 image, plane against
+// records: 64^3 x 4 (34 MB) 45 / 58 / 102 against 41 / 56 / 106 us, 128^3 x 4 (268
+// MB) 84 / 104 / 187 against 79 / 101 / 190, 192^3 x 8 (1.8 GB) 124 / 154 / 284
+// against 128 / 264 / 360; four 256^2 views of 128^3 x 6 (403 MB) 294 against 349.
+static constexpr uint64_t F64_PLANE_BYTES = 256ull << 20;
+
+static bool jplane_eligible(const dart_stack *s) {
+    return s && !s->labelled() && !s->vector() && s->dev.epoch_stride > 0 &&
+           (s->dev.store != ST_F64 || s->bytes > F64_PLANE_BYTES);
+}
+
+// Bytes of the emissivity plane of the stack's layout, and whether every epoch's
+// elements in the allocated one are those of the records.
+static uint64_t plane_bytes(const dart_stack *s) {
+    return (uint64_t)s->dev.epoch_stride * s->dev.n_epochs * (record_bytes(s->dev.store) / 4);
+}
+static bool plane_in_step(const dart_stack *s) {
+    for (char ok : s->plane_ok)
+        if (!ok) return false;
+    return true;
+}
+
 static dart_status check_geometry(const int32_t dims[3], const double cell[3], int32_t M,
                                   const double *times) {
     if (!dims || !cell || !times) return fail(DART_E_INVAL, "null dims/cell/epoch_times");
@@ -203,6 +229,20 @@ extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cel
     s->dev.data = data;
     s->dev.times = (const double *)t;
     s->dev.inv_dt = (const double *)t + n_epochs;
+    s->plane_ok.assign(n_epochs, 0);
+    // An FP64 stack's plane is filled by its loads (a pack by the first render
+    // would cost that one more than it saves); only where it takes little of the
+    // memory that is left.
+    size_t room = 0, all = 0;
+    if (store == ST_F64 && s->bytes > F64_PLANE_BYTES &&
+        hipMemGetInfo(&room, &all) == hipSuccess && plane_bytes(s.get()) <= room / 16) {
+        if (hipMalloc(&s->jplane, plane_bytes(s.get())) == hipSuccess) {
+            s->jplane_bytes = plane_bytes(s.get());
+        } else {
+            s->jplane = nullptr;
+            (void)hipGetLastError();
+        }
+    }
     *out = s.release();
     return DART_OK;
 }
@@ -233,16 +273,17 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
     } guard;
     hipError_t e = launch_fill_u64(err, 1, ~0ull, stream);
     if (e != hipSuccess) return hip_fail(e, "clear error flag");
-    // A plane that holds the other epochs is kept in step: the load writes its
-    // elements with the records, once the renders that read it have finished, and
-    // the next render need not repack the whole stack (refill of one of eight
-    // 256^3 FP16 epochs and a render of two 256^2 views: 716 -> 460 us).
+    // An allocated plane is kept in step: the load writes its elements with the
+    // records, once the renders that read it have finished, and the next render
+    // need not repack the whole stack (refill of one of eight 256^3 FP16 epochs and
+    // a render of two 256^2 views: 716 -> 460 us).
     void *plane = nullptr;
-    if (jplane_ready(s)) {
+    if (s->jplane && s->jplane_bytes == plane_bytes(s)) {
         std::lock_guard<std::mutex> g(s->mu);
         for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
         plane = s->jplane;
-        // (stale if this load fails part-way)
+        // (out of step if this load fails part-way)
+        for (int32_t q = 0; q < count; q++) s->plane_ok[m0 + q] = 0;
         s->jplane_gen.store(0, std::memory_order_release);
     }
     if (flags & F_DEVICE_PTRS) {
@@ -284,7 +325,10 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
     }
     for (int32_t q = 0; q < count; q++) s->filled[m0 + q] = 1;
     s->generation = next_generation();
-    if (plane) s->jplane_gen.store(s->generation, std::memory_order_release);
+    if (plane) {
+        for (int32_t q = 0; q < count; q++) s->plane_ok[m0 + q] = 1;
+        if (plane_in_step(s)) s->jplane_gen.store(s->generation, std::memory_order_release);
+    }
     return DART_OK;
 }
 
@@ -312,6 +356,7 @@ extern "C" dart_status dart_load_epochs(const int32_t dims[3], const double cell
         std::string keep = g_err;
         (void)hipFree((void *)s->dev.data);
         (void)hipFree((void *)s->dev.times);
+        if (s->jplane) (void)hipFree(s->jplane);
         delete s;
         g_err = keep;
         return st;
@@ -614,7 +659,7 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
             from.data = (const char *)s->dev.data + (uint64_t)m * eb;
             from.n_epochs = to.n_epochs = 1;
             to.data = one;
-            e = launch_rebrick(s->dev.store, from, to, one, stream);
+            e = launch_rebrick(s->dev.store, from, to, one, nullptr, stream);
             if (e == hipSuccess)
                 e = hipMemcpyAsync((char *)s->dev.data + (uint64_t)m * eb, one, eb,
                                    hipMemcpyDeviceToDevice, stream);
@@ -629,13 +674,21 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
         }
         tmp.dev.data = s->dev.data;
         s->dev = tmp.dev;
+        s->plane_ok.assign(s->plane_ok.size(), 0);
         s->generation = next_generation();
         return DART_OK;
     }
     HIP_TRY(em, "hipMalloc(rebrick)");
     tmp.dev.data = data;
-    hipError_t e = launch_rebrick(s->dev.store, s->dev, tmp.dev, data, stream);
+    // the plane follows in the same pass when it keeps its size (no render reads it:
+    // the stack is not busy)
+    std::lock_guard<std::mutex> g(s->mu);
+    const bool in_step = plane_in_step(s);
+    void *plane = s->jplane && s->jplane_bytes == plane_bytes(&tmp) && in_step ? s->jplane : nullptr;
+    s->jplane_gen.store(0, std::memory_order_release);
+    hipError_t e = launch_rebrick(s->dev.store, s->dev, tmp.dev, data, plane, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e != hipSuccess || !plane) s->plane_ok.assign(s->plane_ok.size(), 0);
     if (e != hipSuccess) {
         (void)hipFree(data);
         return hip_fail(e, "rebrick");
@@ -644,6 +697,7 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
     s->dev = tmp.dev;
     s->bytes = bytes;
     s->generation = next_generation();
+    if (plane) s->jplane_gen.store(s->generation, std::memory_order_release);
     return DART_OK;
 }
 
@@ -1044,14 +1098,6 @@ dart_status dart::refresh_vector(const dart_stack *cs, hipStream_t stream) {
     return DART_OK;
 }
 
-// The emissivity plane serves plain stacks with FP32 or 16-bit records (FP64
-// records stay whole; labelled and vector stacks read their parts' records;
-// streamed windows have no plane).
-static bool jplane_eligible(const dart_stack *s) {
-    return s && !s->labelled() && !s->vector() && s->dev.store != ST_F64 &&
-           s->dev.epoch_stride > 0;
-}
-
 bool dart::jplane_ready(const dart_stack *s) {
     return jplane_eligible(s) && s->jplane_gen.load(std::memory_order_acquire) == s->generation;
 }
@@ -1071,7 +1117,12 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
     if (cap != hipStreamCaptureStatusNone) return DART_OK;
     const uint64_t n = (uint64_t)s->dev.epoch_stride * s->dev.n_epochs;
-    const uint64_t need = n * (record_bytes(s->dev.store) / 4);
+    const uint64_t need = plane_bytes(s);
+    if (s->jplane && s->jplane_bytes == need && plane_in_step(s)) {
+        // (the records are the packed ones: re-placed, say)
+        s->jplane_gen.store(s->generation, std::memory_order_release);
+        return DART_OK;
+    }
     if (s->jplane_bytes != need && !may_alloc) return DART_OK;
     // renders still reading the old plane must finish first
     for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
@@ -1080,6 +1131,7 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
         if (s->jplane) (void)hipFree(s->jplane);
         s->jplane = nullptr;
         s->jplane_bytes = 0;
+        s->plane_ok.assign(s->dev.n_epochs, 0);
         void *p = nullptr;
         if (hipMalloc(&p, need) != hipSuccess) {
             (void)hipGetLastError();  // no room: renders read whole records
@@ -1093,6 +1145,7 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
             "pack emissivity plane");
     // complete before a render on any stream reads it
     HIP_TRY(hipStreamSynchronize(stream), "sync");
+    s->plane_ok.assign(s->dev.n_epochs, 1);
     s->jplane_gen.store(s->generation, std::memory_order_release);
     return DART_OK;
 }
