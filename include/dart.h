@@ -153,8 +153,9 @@ dart_status dart_free_epochs(dart_stack *s);
  * (DART_RECORDS_ONLY).  Without room for the plane (hipMalloc fails) renders
  * read whole records, as do views with DART_NO_KAHAN.  Planes of at most 4 GiB
  * are read through 32-bit offsets, larger ones through 64-bit addresses
- * (DART_PLANE_ADDR64 asks for those on any plane).  Labelled, vector and
- * streamed stacks have none. */
+ * (DART_PLANE_ADDR64 asks for those on any plane).  From its second render on, a
+ * labelled stack reads its sub-domains' planes, and a vector stack reads
+ * component 0's; streamed windows have none. */
 typedef struct {
     int32_t dims[3];
     int32_t n_epochs;

@@ -134,10 +134,10 @@ hipError_t launch_plain(const RayView &v, const RenderSums &sums, hipStream_t s)
 // Kernel variant bits: 1 depth-synchronous wavefronts, 2 the launch's views are
 // labelled stacks (block loop), 4 exact temporal integration, 8 eight cells per
 // batch (else four), 16 vector stacks (only alone: no other bit but 8), 32 the
-// views' stacks have an emissivity plane (not with 2 or 16).
+// views' stacks have an emissivity plane.
 enum : int {
     KV_SYNC = 1, KV_LABELLED = 2, KV_EXACT = 4, KV_K8 = 8, KV_VEC = 16, KV_JP = 32,
-    KV_JP32 = 64,  // with KV_JP: the plane through 32-bit byte offsets (F_PLANE32)
+    KV_JP32 = 64,  // with KV_JP: the plane through 32-bit byte offsets (F_PLANE32; not with 2)
 };
 hipError_t launch_batch(int store, bool f64_dda, int variant, const BatchLaunch &bl,
                         int grid_blocks, hipStream_t s);

@@ -829,7 +829,6 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     using GRaw = const Raw __attribute__((address_space(1)));
     using JF = typename JFieldT<S>::raw;
     using GJ = const JF __attribute__((address_space(1)));
-    static_assert(!(JP && VEC), "no emissivity plane for these stacks");
     // The walk addresses elements of the emissivity plane (JP) or records:
     // both have the record index space, so one offset serves either.
     using E = typename std::conditional<JP != 0, JF, Raw>::type;
@@ -1031,6 +1030,24 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
                     q0[k] = (QJ)addr[k][0];
                     q1[k] = (QJ)addr[k][second];
                 }
+                if constexpr (VEC) {
+                    // the same element of the other components
+#pragma unroll
+                    for (int c = 0; c < NX; c++) {
+                        j0[k][c] = j1[k][c] = (JF)0;
+                        if (c < nx) {
+                            GB *cb = (GB *)v.chan_data[c];
+                            if constexpr (O32) {
+                                j0[k][c] = *(GJ *)(cb + addr[k]);
+                                j1[k][c] = *(GJ *)(cb + second * (int64_t)sizeof(E) + addr[k]);
+                            } else {
+                                GJ *cd = (GJ *)cb + (addr[k] - wdata);
+                                j0[k][c] = cd[0];
+                                j1[k][c] = cd[second];
+                            }
+                        }
+                    }
+                }
             }
             uint32_t any_bits = 0u;
 #pragma unroll
@@ -1042,6 +1059,16 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
                     const A val = lerp_d((A)decode_j<S>((JF)q0[k]), plane_diff<S>(q0[k], q1[k]), cw[k]);
                     const A term = cds[k] * val;
                     kahan_add(sum, comp, term, kahan);
+                    if constexpr (VEC) {
+#pragma unroll
+                        for (int c = 0; c < NX; c++)
+                            if (c < nx) {
+                                const A xv = lerp_w((A)decode_j<S>(j0[k][c]),
+                                                    (A)decode_j<S>(j1[k][c]), cw[k]);
+                                const A xt = cds[k] * xv;
+                                kahan_add(xsum[c], xcomp[c], xt, kahan);
+                            }
+                    }
                 }
                 continue;
             }
@@ -1065,8 +1092,33 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
             }
 #pragma unroll
             for (int k = 0; k < K; k++) {
-                const A b0 = mk0[k] ? (A)boosted<S>(r0[k], v, beaming) : (A)decode_j<S>((JF)q0[k]);
-                const A b1 = mk1[k] ? (A)boosted<S>(r1[k], v, beaming) : (A)decode_j<S>((JF)q1[k]);
+                V f0 = V(1), f1 = V(1);
+                A b0, b1;
+                if constexpr (VEC) {
+                    V jj0, jj1;
+                    b0 = (A)decode_j<S>((JF)q0[k]);
+                    b1 = (A)decode_j<S>((JF)q1[k]);
+                    if (mk0[k]) {
+                        f0 = boost_factor<S>(r0[k], v, beaming, jj0);
+                        b0 = (A)(jj0 * f0);
+                    }
+                    if (mk1[k]) {
+                        f1 = boost_factor<S>(r1[k], v, beaming, jj1);
+                        b1 = (A)(jj1 * f1);
+                    }
+#pragma unroll
+                    for (int c = 0; c < NX; c++)
+                        if (c < nx) {
+                            A xv = (A)(decode_j<S>(j0[k][c]) * f0);
+                            const A xb = (A)(decode_j<S>(j1[k][c]) * f1);
+                            xv = lerp_w(xv, xb, cw[k]);
+                            const A xt = cds[k] * xv;
+                            kahan_add(xsum[c], xcomp[c], xt, kahan);
+                        }
+                } else {
+                    b0 = mk0[k] ? (A)boosted<S>(r0[k], v, beaming) : (A)decode_j<S>((JF)q0[k]);
+                    b1 = mk1[k] ? (A)boosted<S>(r1[k], v, beaming) : (A)decode_j<S>((JF)q1[k]);
+                }
                 const A val = lerp_w(b0, b1, cw[k]);
                 const A term = cds[k] * val;
                 kahan_add(sum, comp, term, kahan);
@@ -1189,15 +1241,14 @@ __device__ __forceinline__ double pixel_value(const RayView &v, int pi, int pj, 
     // otherwise raise the register count, and lower the occupancy, of every
     // plain render)
     static_assert(!(LAB && VEC), "vector stacks are not labelled");
-    static_assert(!(LAB && JP), "labelled stacks read whole records");
     if constexpr (!LAB) {
         return march<S, R, SYNC, EX, K, VEC, JP>(v, v.st, v.centre, pi, pj, in_image, seg, tab,
                                                  nsteps, ext);
     } else {
         double acc = 0.0;
         for (int b = 0; b < v.n_blocks; b++)
-            acc += march<S, R, SYNC, EX, K>(v, v.blocks[b].st, v.blocks[b].centre, pi, pj,
-                                         in_image, seg, tab, nsteps);
+            acc += march<S, R, SYNC, EX, K, false, JP>(v, v.blocks[b].st, v.blocks[b].centre, pi,
+                                                     pj, in_image, seg, tab, nsteps);
         return acc;
     }
 }
@@ -1735,22 +1786,30 @@ hipError_t plain_impl(const RayView &v, const RenderSums &sums, hipStream_t s) {
     static_assert(MAX_SEG_LOG2 <= 2, "a workgroup of k_plain holds a tile's segments");
     const dim3 g((unsigned)((waves + 3) / 4)), b(256);
     const bool lab = v.n_blocks > 0, ex = (v.flags & F_EXACT) != 0;
-    // (the planner gives an emissivity plane only to plain stacks)
-    if (v.st.jplane && !lab && v.n_chan == 1) {
-        if (v.flags & F_PLANE32) {
-            if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 2>), g, b, 0, s, v, sums);
-            else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 2>), g, b, 0, s, v, sums);
-        } else {
-            if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true, false, 1>), g, b, 0, s, v, sums);
-            else hipLaunchKernelGGL((k_plain<S, R, false, false, false, 1>), g, b, 0, s, v, sums);
-        }
-        return hipGetLastError();
+    const bool vec = v.n_chan > 1;
+    const int jp = !v.st.jplane ? 0 : (v.flags & F_PLANE32) ? 2 : 1;
+#define DART_PLAIN(LAB, EX, VEC, JP) \
+    hipLaunchKernelGGL((k_plain<S, R, LAB, EX, VEC, JP>), g, b, 0, s, v, sums)
+    if (vec) {
+        if (jp == 2) DART_PLAIN(false, false, true, 2);
+        else if (jp == 1) DART_PLAIN(false, false, true, 1);
+        else DART_PLAIN(false, false, true, 0);
+    } else if (lab) {  // (planes of sub-domains through 64-bit addresses)
+        if (jp && ex) DART_PLAIN(true, true, false, 1);
+        else if (jp) DART_PLAIN(true, false, false, 1);
+        else if (ex) DART_PLAIN(true, true, false, 0);
+        else DART_PLAIN(true, false, false, 0);
+    } else if (jp == 2) {
+        if (ex) DART_PLAIN(false, true, false, 2);
+        else DART_PLAIN(false, false, false, 2);
+    } else if (jp == 1) {
+        if (ex) DART_PLAIN(false, true, false, 1);
+        else DART_PLAIN(false, false, false, 1);
+    } else {
+        if (ex) DART_PLAIN(false, true, false, 0);
+        else DART_PLAIN(false, false, false, 0);
     }
-    if (v.n_chan > 1) hipLaunchKernelGGL((k_plain<S, R, false, false, true>), g, b, 0, s, v, sums);
-    else if (lab && ex) hipLaunchKernelGGL((k_plain<S, R, true, true>), g, b, 0, s, v, sums);
-    else if (lab) hipLaunchKernelGGL((k_plain<S, R, true, false>), g, b, 0, s, v, sums);
-    else if (ex) hipLaunchKernelGGL((k_plain<S, R, false, true>), g, b, 0, s, v, sums);
-    else hipLaunchKernelGGL((k_plain<S, R, false, false>), g, b, 0, s, v, sums);
+#undef DART_PLAIN
     return hipGetLastError();
 }
 
@@ -1772,12 +1831,20 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
         // vector stacks: own marching mode only (no depth sync, labels or
         // exact time)
         const dim3 g((unsigned)grid_blocks), b(256);
-        if (k8)
-            hipLaunchKernelGGL((k_batch<S, R, 0, false, false, 8, true>), g, b, 0, s, bl, bl.views,
-                               bl.tiles);
-        else
-            hipLaunchKernelGGL((k_batch<S, R, 0, false, false, 4, true>), g, b, 0, s, bl, bl.views,
-                               bl.tiles);
+        const int jp = !(variant & KV_JP) ? 0 : (variant & KV_JP32) ? 2 : 1;
+#define DART_VEC(K, JP)                                                                      \
+    hipLaunchKernelGGL((k_batch<S, R, 0, false, false, K, true, JP>), g, b, 0, s, bl, bl.views, \
+                       bl.tiles)
+        if (k8) {
+            if (jp == 2) DART_VEC(8, 2);
+            else if (jp == 1) DART_VEC(8, 1);
+            else DART_VEC(8, 0);
+        } else {
+            if (jp == 2) DART_VEC(4, 2);
+            else if (jp == 1) DART_VEC(4, 1);
+            else DART_VEC(4, 0);
+        }
+#undef DART_VEC
         return hipGetLastError();
     }
     if ((variant & KV_JP) && (variant & KV_JP32)) {
@@ -1786,7 +1853,7 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
             case 1: batch_launch_k<S, R, 1, false, false, 2>(bl, k8, grid_blocks, s); break;
             case 4: batch_launch_k<S, R, 0, false, true, 2>(bl, k8, grid_blocks, s); break;
             case 5: batch_launch_k<S, R, 1, false, true, 2>(bl, k8, grid_blocks, s); break;
-            default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
+            default: return hipErrorInvalidValue;  // (labelled stacks: 64-bit addresses)
         }
         return hipGetLastError();
     }
@@ -1794,9 +1861,12 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
         switch (variant & 7) {
             case 0: batch_launch_k<S, R, 0, false, false, 1>(bl, k8, grid_blocks, s); break;
             case 1: batch_launch_k<S, R, 1, false, false, 1>(bl, k8, grid_blocks, s); break;
+            case 2: batch_launch_k<S, R, 0, true, false, 1>(bl, k8, grid_blocks, s); break;
+            case 3: batch_launch_k<S, R, 1, true, false, 1>(bl, k8, grid_blocks, s); break;
             case 4: batch_launch_k<S, R, 0, false, true, 1>(bl, k8, grid_blocks, s); break;
             case 5: batch_launch_k<S, R, 1, false, true, 1>(bl, k8, grid_blocks, s); break;
-            default: return hipErrorInvalidValue;  // (labelled stacks read whole records)
+            case 6: batch_launch_k<S, R, 0, true, true, 1>(bl, k8, grid_blocks, s); break;
+            default: batch_launch_k<S, R, 1, true, true, 1>(bl, k8, grid_blocks, s); break;
         }
         return hipGetLastError();
     }

@@ -95,10 +95,10 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     }
     hipStream_t stream = (hipStream_t)hip_stream;
     dart_status st = DART_OK;
-    for (int32_t i = 0; i < n; i++) {
-        st = refresh_vector(stacks[i], stream);
+    for (const dart_stack *s : each_stack(stacks, n)) {
+        st = refresh_vector(s, stream);
         // (an emissivity plane is repacked in place, never allocated here)
-        if (st == DART_OK) st = refresh_jplane(stacks[i], stream, false);
+        if (st == DART_OK) st = refresh_jplane(s, stream, false);
         if (st != DART_OK) return st;
     }
     const dart_tuning tun = tuning_for(stacks[0]);

@@ -40,6 +40,9 @@ struct dart_stack {
     std::vector<dart_stack *> parts;
     dart::Block *dev_blocks = nullptr;
     std::atomic<int> refs{0};
+    std::atomic<bool> rendered{false};       // (labelled) by a call before this one
+    std::vector<const void *> block_planes;  // the sub-domains' planes in dev_blocks
+    std::vector<dart_stack *> holders;       // labelled and vector stacks that hold this one
     bool labelled() const { return !parts.empty(); }
     // vector stack: its components (owned by the caller, counted in refs);
     // dev is component 0's
@@ -71,6 +74,7 @@ dart_status resolve_view(const dart_stack *s, const dart_view *v, RayView *rv);
 dart_status refresh_jplane(const dart_stack *s, hipStream_t stream, bool may_alloc);
 bool jplane_ready(const dart_stack *s);
 void note_use(const dart_stack *s, hipStream_t stream);
+std::vector<const dart_stack *> each_stack(const dart_stack *const *stacks, int32_t n);  // once
 void note_uses(const dart_stack *const *stacks, int32_t n, hipStream_t stream);  // each once
 bool stack_busy(const dart_stack *s);
 dart_tuning tuning_for(const dart_stack *s);

@@ -247,6 +247,8 @@ extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cel
     return DART_OK;
 }
 
+static hipError_t wait_renders(dart_stack *s);
+
 static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dart_dtype src,
                                    const void *j, const void *beta, uint32_t flags,
                                    hipStream_t stream) {
@@ -280,7 +282,7 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
     void *plane = nullptr;
     if (s->jplane && s->jplane_bytes == plane_bytes(s)) {
         std::lock_guard<std::mutex> g(s->mu);
-        for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
+        HIP_TRY(wait_renders(s), "wait for renders");
         plane = s->jplane;
         // (out of step if this load fails part-way)
         for (int32_t q = 0; q < count; q++) s->plane_ok[m0 + q] = 0;
@@ -379,11 +381,15 @@ void dart::note_use(const dart_stack *cs, hipStream_t stream) {
     s->uses.emplace_back(stream, ev);
 }
 
-void dart::note_uses(const dart_stack *const *stacks, int32_t n, hipStream_t stream) {
+std::vector<const dart_stack *> dart::each_stack(const dart_stack *const *stacks, int32_t n) {
     std::vector<const dart_stack *> s(stacks, stacks + n);
     std::sort(s.begin(), s.end());
     s.erase(std::unique(s.begin(), s.end()), s.end());
-    for (const dart_stack *p : s) note_use(p, stream);
+    return s;
+}
+
+void dart::note_uses(const dart_stack *const *stacks, int32_t n, hipStream_t stream) {
+    for (const dart_stack *p : each_stack(stacks, n)) note_use(p, stream);
 }
 
 bool dart::stack_busy(const dart_stack *cs) {
@@ -393,6 +399,36 @@ bool dart::stack_busy(const dart_stack *cs) {
     for (auto &u : s->uses)
         if (hipEventQuery(u.second) == hipErrorNotReady) return true;
     return false;
+}
+
+// A labelled or vector stack takes hold of a part, and lets go of it.
+static void hold(dart_stack *holder, dart_stack *part) {
+    std::lock_guard<std::mutex> g(part->mu);
+    part->refs++;
+    part->holders.push_back(holder);
+}
+static void release(dart_stack *holder, dart_stack *part) {
+    std::lock_guard<std::mutex> g(part->mu);
+    part->refs--;
+    auto &h = part->holders;
+    h.erase(std::find(h.begin(), h.end(), holder));
+}
+
+// Waits for the renders that read the stack, its holders' among them.  Caller
+// holds s->mu.
+static hipError_t wait_renders(dart_stack *s) {
+    for (auto &u : s->uses) {
+        hipError_t e = hipEventSynchronize(u.second);
+        if (e != hipSuccess) return e;
+    }
+    for (dart_stack *h : s->holders) {
+        std::lock_guard<std::mutex> g(h->mu);
+        for (auto &u : h->uses) {
+            hipError_t e = hipEventSynchronize(u.second);
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
 }
 
 extern "C" dart_status dart_free_epochs(dart_stack *s) {
@@ -405,10 +441,10 @@ extern "C" dart_status dart_free_epochs(dart_stack *s) {
     if (s->labelled()) {
         // the grids belong to the sub-domains
         (void)hipFree(s->dev_blocks);
-        for (dart_stack *p : s->parts) p->refs--;
+        for (dart_stack *p : s->parts) release(s, p);
     } else if (s->vector()) {
         (void)hipFree(s->packed);
-        for (dart_stack *c : s->comps) c->refs--;
+        for (dart_stack *c : s->comps) release(s, c);
     } else {
         (void)hipFree((void *)s->dev.data);
         (void)hipFree((void *)s->dev.times);
@@ -416,6 +452,16 @@ extern "C" dart_status dart_free_epochs(dart_stack *s) {
     }
     delete s;
     return DART_OK;
+}
+
+// A sub-domain as the kernels see it (the plane it has now, if any).
+static Block block_of(const dart_stack *b) {
+    Block k;
+    k.st = b->dev;
+    k.st.jplane = b->jplane;
+    for (int a = 0; a < 3; a++)
+        k.centre[a] = b->placed ? b->centre[a] - b->origin[a] : 0.5 * b->dev.n[a] * b->dev.cell[a];
+    return k;
 }
 
 extern "C" dart_status dart_labelled_create(dart_stack *const *blocks, int32_t n_blocks,
@@ -443,12 +489,7 @@ extern "C" dart_status dart_labelled_create(dart_stack *const *blocks, int32_t n
                 return fail(DART_E_INVAL, "blocks[%d]: another domain centre", i);
     }
     std::vector<Block> hb(n_blocks);
-    for (int32_t i = 0; i < n_blocks; i++) {
-        const dart_stack *b = blocks[i];
-        hb[i].st = b->dev;
-        for (int a = 0; a < 3; a++)
-            hb[i].centre[a] = b->placed ? b->centre[a] - b->origin[a] : 0.5 * b->dev.n[a] * b->dev.cell[a];
-    }
+    for (int32_t i = 0; i < n_blocks; i++) hb[i] = block_of(blocks[i]);
     HIP_TRY(hipSetDevice(b0->device), "hipSetDevice");
     Block *d = nullptr;
     HIP_TRY(hipMalloc(&d, hb.size() * sizeof(Block)), "hipMalloc(blocks)");
@@ -467,7 +508,7 @@ extern "C" dart_status dart_labelled_create(dart_stack *const *blocks, int32_t n
     for (int32_t i = 0; i < n_blocks; i++) {
         s->parts.push_back(blocks[i]);
         s->bytes += blocks[i]->bytes;
-        blocks[i]->refs++;
+        hold(s, blocks[i]);
     }
     *out = s;
     return DART_OK;
@@ -545,7 +586,7 @@ extern "C" dart_status dart_vector_create(dart_stack *const *components, int32_t
     s->bytes = (n - 1) * packed_bytes(s);
     for (int32_t i = 0; i < n; i++) {
         s->bytes += components[i]->bytes;
-        components[i]->refs++;
+        hold(s, components[i]);
     }
     *out = s;
     return DART_OK;
@@ -560,6 +601,8 @@ extern "C" dart_status dart_stack_get_info(const dart_stack *s, dart_stack_info 
     info->n_epochs = s->dev.n_epochs;
     info->storage = s->storage;
     info->device_bytes = s->bytes + s->jplane_bytes;
+    for (const dart_stack *p : s->parts) info->device_bytes += p->jplane_bytes;
+    for (const dart_stack *c : s->comps) info->device_bytes += c->jplane_bytes;
     return DART_OK;
 }
 
@@ -831,11 +874,15 @@ dart_status dart::resolve_view(const dart_stack *s, const dart_view *v, RayView 
     rv->st = s->dev;
     // (the plane kernels always compensate their sums: views without
     // compensation read whole records)
+    // (a labelled stack's planes are its blocks': here the first one's stands for all)
+    const dart_stack *owner = s->vector() ? s->comps[0] : geo;
     rv->st.jplane = (!(v->flags & (DART_RECORDS_ONLY | DART_NO_KAHAN)) && jplane_ready(s))
-                        ? s->jplane
+                        ? owner->jplane
                         : nullptr;
-    // a plane of at most 4 GiB is read through 32-bit byte offsets
-    if (rv->st.jplane && s->jplane_bytes <= (1ull << 32) && !(v->flags & DART_PLANE_ADDR64))
+    // a plane of at most 4 GiB is read through 32-bit byte offsets (a labelled
+    // stack's through 64-bit addresses)
+    if (rv->st.jplane && !s->labelled() && owner->jplane_bytes <= (1ull << 32) &&
+        !(v->flags & DART_PLANE_ADDR64))
         rv->flags |= F_PLANE32;
     rv->blocks = s->dev_blocks;
     rv->n_blocks = (int32_t)s->parts.size();
@@ -964,7 +1011,6 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
         }
     } moved{ws, {ws->acc, ws->desc, ws->img, ws->parts}};
     if ((e = grow_dev(ws->acc, ws->acc_cap, acc_words)) != hipSuccess) return e;
-    if ((e = grow_host(ws->sums_host, ws->sums_host_cap, 16 * n_views)) != hipSuccess) return e;
     if ((e = grow_dev(ws->desc, ws->desc_cap, n_views * sizeof(RayView) + n_tiles * sizeof(Tile))) !=
         hipSuccess)
         return e;
@@ -1029,9 +1075,11 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     rv.image = dev_img ? image : mapped ? ws->img_host : (void *)ws->img;
     rv.acc_index = 0;
     rv.tile_w_log2 = 3;
-    if (sums)
+    if (sums) {
+        HIP_TRY(grow_host(ws->sums_host, ws->sums_host_cap, 16), "totals");
         HIP_TRY(launch_begin(ws->acc, lay.words(), nullptr, nullptr, 0, stream),
                 "clear accumulators");
+    }
     HIP_TRY(launch_plain(rv, sums ? lay.sums(ws->acc) : RenderSums{}, stream), "render kernel");
     note_use(s, stream);
     if (!dev_img && !mapped)
@@ -1098,14 +1146,28 @@ dart_status dart::refresh_vector(const dart_stack *cs, hipStream_t stream) {
     return DART_OK;
 }
 
-bool dart::jplane_ready(const dart_stack *s) {
+static bool own_plane_ready(const dart_stack *s) {
     return jplane_eligible(s) && s->jplane_gen.load(std::memory_order_acquire) == s->generation;
 }
 
-dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool may_alloc) {
-    if (!jplane_eligible(cs)) return DART_OK;
-    dart_stack *s = const_cast<dart_stack *>(cs);
-    std::lock_guard<std::mutex> g(s->mu);
+// Whether renders of the stack read planes: its own; component 0's for a vector
+// stack (the other components' emissivity is packed anyway); every sub-domain's,
+// as dev_blocks names them, for a labelled one.
+bool dart::jplane_ready(const dart_stack *s) {
+    if (!s) return false;
+    if (s->vector()) return own_plane_ready(s->comps[0]);
+    if (!s->labelled()) return own_plane_ready(s);
+    std::lock_guard<std::mutex> g(const_cast<dart_stack *>(s)->mu);
+    if (s->block_planes.size() != s->parts.size()) return false;
+    for (size_t k = 0; k < s->parts.size(); k++)
+        if (!own_plane_ready(s->parts[k]) || s->parts[k]->jplane != s->block_planes[k]) return false;
+    return true;
+}
+
+// Enqueues the pack of a plain stack's plane if it is missing or stale; *packed:
+// it is to be published once `stream` has come that far (caller holds s->mu).
+static dart_status pack_plane(dart_stack *s, hipStream_t stream, bool may_alloc, bool *packed) {
+    *packed = false;
     if (s->jplane_gen.load(std::memory_order_relaxed) == s->generation) return DART_OK;
     // (no second attempt to allocate for records that have not changed)
     if (s->jplane_no_room == s->generation) return DART_OK;
@@ -1125,7 +1187,7 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
     }
     if (s->jplane_bytes != need && !may_alloc) return DART_OK;
     // renders still reading the old plane must finish first
-    for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
+    HIP_TRY(wait_renders(s), "wait for renders");
     s->jplane_gen.store(0, std::memory_order_release);
     if (s->jplane_bytes != need) {
         if (s->jplane) (void)hipFree(s->jplane);
@@ -1143,10 +1205,69 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
     }
     HIP_TRY(launch_pack_jplane(s->dev.store, s->dev.data, s->jplane, n, stream),
             "pack emissivity plane");
-    // complete before a render on any stream reads it
-    HIP_TRY(hipStreamSynchronize(stream), "sync");
+    *packed = true;
+    return DART_OK;
+}
+
+static void publish_plane(dart_stack *s) {
     s->plane_ok.assign(s->dev.n_epochs, 1);
     s->jplane_gen.store(s->generation, std::memory_order_release);
+}
+
+// Sub-domains' planes, and dev_blocks with their addresses: one wait for all.
+// The first render of a labelled stack reads whole records: packing the planes
+// costs what about ten renders gain (seven sub-domains of a 128x128x256 FP32 jet:
+// 0.5 ms; four 512^2 views 519 -> 467 us), so only a stack that is rendered again
+// has them.
+static dart_status refresh_blocks(dart_stack *s, hipStream_t stream, bool may_alloc) {
+    if (!s->rendered.exchange(true)) return DART_OK;
+    std::vector<dart_stack *> packed;
+    for (dart_stack *p : s->parts) {
+        if (!jplane_eligible(p)) return DART_OK;  // (whole records then)
+        std::lock_guard<std::mutex> g(p->mu);
+        bool pk = false;
+        dart_status st = pack_plane(p, stream, may_alloc, &pk);
+        if (st != DART_OK) return st;
+        if (pk) packed.push_back(p);
+    }
+    if (!packed.empty()) HIP_TRY(hipStreamSynchronize(stream), "sync");
+    for (dart_stack *p : packed) {
+        std::lock_guard<std::mutex> g(p->mu);
+        publish_plane(p);
+    }
+    std::lock_guard<std::mutex> g(s->mu);
+    std::vector<const void *> planes;
+    for (dart_stack *p : s->parts) {
+        if (!own_plane_ready(p)) return DART_OK;
+        planes.push_back(p->jplane);
+    }
+    if (planes == s->block_planes) return DART_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
+    if (cap != hipStreamCaptureStatusNone) return DART_OK;
+    for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
+    s->block_planes.clear();
+    std::vector<Block> hb(s->parts.size());
+    for (size_t k = 0; k < hb.size(); k++) hb[k] = block_of(s->parts[k]);
+    HIP_TRY(hipMemcpyAsync(s->dev_blocks, hb.data(), hb.size() * sizeof(Block),
+                           hipMemcpyHostToDevice, stream), "upload blocks");
+    HIP_TRY(hipStreamSynchronize(stream), "sync");
+    s->block_planes.swap(planes);
+    return DART_OK;
+}
+
+dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool may_alloc) {
+    if (cs && cs->vector()) return refresh_jplane(cs->comps[0], stream, may_alloc);
+    if (cs && cs->labelled()) return refresh_blocks(const_cast<dart_stack *>(cs), stream, may_alloc);
+    if (!jplane_eligible(cs)) return DART_OK;
+    dart_stack *s = const_cast<dart_stack *>(cs);
+    std::lock_guard<std::mutex> g(s->mu);
+    bool packed = false;
+    dart_status st = pack_plane(s, stream, may_alloc, &packed);
+    if (st != DART_OK || !packed) return st;
+    // complete before a render on any stream reads it
+    HIP_TRY(hipStreamSynchronize(stream), "sync");
+    publish_plane(s);
     return DART_OK;
 }
 
@@ -1527,7 +1648,8 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout 
         for (uint32_t q = 0; q <= g.n_queues; q++) bl.q_begin[q] = g.q_begin[q];
         bl.sums = sums ? lay.sums(acc) : RenderSums{};
         bl.parts = g.parts ? parts : nullptr;
-        const int variant = g.vec ? (KV_VEC | (tun.cells_per_batch == 8 ? KV_K8 : 0))
+        const int variant = g.vec ? (KV_VEC | (g.jp ? KV_JP : 0) | (g.jp32 ? KV_JP32 : 0) |
+                                     (tun.cells_per_batch == 8 ? KV_K8 : 0))
                                   : (tun.depth_sync > 0 ? KV_SYNC : 0) |
                                         (g.labelled ? KV_LABELLED : 0) | (g.exact ? KV_EXACT : 0) |
                                         (g.jp ? KV_JP : 0) | (g.jp32 ? KV_JP32 : 0) |
@@ -1609,9 +1731,9 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         }
         return DART_OK;
     }
-    for (int32_t i = 0; i < n; i++) {
-        dart_status st = refresh_vector(stacks[i], stream);
-        if (st == DART_OK) st = refresh_jplane(stacks[i], stream, true);
+    for (const dart_stack *s : each_stack(stacks, n)) {
+        dart_status st = refresh_vector(s, stream);
+        if (st == DART_OK) st = refresh_jplane(s, stream, true);
         if (st != DART_OK) return st;
     }
     const dart_tuning tun = tuning_for(stacks[0]);
@@ -1690,6 +1812,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     size_t n_desc = 0;
     for (const Group &gr : ws->plan_groups) n_desc += gr.views.size();
     const size_t n_clear = sums ? lay.words() : lay.heads_words();
+    if (sums) HIP_TRY(grow_host(ws->sums_host, ws->sums_host_cap, 16 * (size_t)n), "totals");
     const RayView *dviews = (const RayView *)ws->desc;
     const Tile *dtiles = (const Tile *)(ws->desc + n_desc * sizeof(RayView));
     // A plan's first call launches its kernels one by one; the second captures
@@ -2008,7 +2131,8 @@ extern "C" dart_status dart_count_bytes(const dart_stack *s, const dart_view *v,
         while ((elem << (l + 1)) <= 128u) l++;
         return l;
     };
-    const bool plane = !(v->flags & (DART_RECORDS_ONLY | DART_NO_KAHAN)) && jplane_ready(s);
+    const bool plane =
+        !(v->flags & (DART_RECORDS_ONLY | DART_NO_KAHAN)) && own_plane_ready(s);
     uint64_t samples = 0, lines = 0;
     st = count_marked(s, v, -1, false, &samples, hip_stream);
     if (st == DART_OK && line_bytes_out)
