@@ -96,6 +96,15 @@ struct Tile {
     uint16_t tx, ty;
 };
 
+// A row of tiles as the planner lays it out: `count` tiles from (tx, ty) on, each
+// once per depth segment (1 << seg_log2 places side by side), at places `first`
+// on of the tile descriptors.  launch_begin writes the descriptors.
+struct Run {
+    uint32_t first, view, count_seg;  // count | seg_log2 << RUN_SEG_SHIFT
+    uint16_t tx, ty;
+};
+constexpr int RUN_SEG_SHIFT = 24;
+
 constexpr int MAX_QUEUES = 8;
 
 // Where a render adds its flux and cell-steps: view i has slots (flux as double
@@ -165,10 +174,12 @@ hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_
                               hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t s);
-// What precedes a render's kernels, in one launch: clears n_clear words and, when
-// src is given, copies n_copy words of descriptors from pinned host memory.
+// What precedes a render's kernels, in one launch: clears n_clear words, copies
+// n_copy words (descriptors in pinned host memory, src) and writes the tile
+// descriptors of n_runs rows (runs: pinned too).
 hipError_t launch_begin(unsigned long long *clear, size_t n_clear, void *dst, const void *src,
-                        size_t n_copy, hipStream_t s);
+                        size_t n_copy, const Run *runs, size_t n_runs, Tile *tiles,
+                        hipStream_t s);
 // Totals of n views from their slots, written to pinned host memory: flux[n] (as
 // double bits), then steps[n].
 hipError_t launch_totals(const RenderSums &sums, int32_t n, void *host, hipStream_t s);

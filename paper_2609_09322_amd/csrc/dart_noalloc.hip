@@ -103,7 +103,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     }
     const dart_tuning tun = tuning_for(stacks[0]);
     std::vector<Group> groups;
-    st = plan_batch(stacks, views, n, images, tun, 0, groups);
+    st = plan_batch(stacks, views, n, images, tun, 0, false, groups);
     if (st != DART_OK) return st;
     size_t nv = 0, nt = 0;
     assign_offsets(groups, &nv, &nt);
@@ -125,7 +125,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     if (st != DART_OK) return st;
     std::lock_guard<std::mutex> g(sc->mu);
     std::vector<unsigned char> host(desc_bytes);
-    pack_descriptors(groups, nv, host.data());
+    pack_descriptors(groups, host.data());
     unsigned long long *acc = (unsigned long long *)sc->ptr;
     const bool sums = flux_out || steps_out;
     const RayView *dviews = (const RayView *)(sc->ptr + desc_off);
@@ -137,7 +137,7 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
                    "H2D descriptors");
     HIP_TRY_STATUS(hipStreamSynchronize(stream), "sync");
     HIP_TRY_STATUS(launch_begin(acc, sums ? lay.words() : lay.heads_words(), nullptr, nullptr, 0,
-                                stream),
+                                nullptr, 0, nullptr, stream),
                    "clear accumulators");
     HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, nullptr, dviews, dtiles, tun, device, stream),
                    "batch kernels");

@@ -93,15 +93,18 @@ struct Group {
     bool jp = false;        // views that read their stacks' emissivity planes
     bool jp32 = false;      // ... through 32-bit offsets (planes of at most 4 GiB)
     std::vector<RayView> views;
-    // queued tiles [0, q_begin[n_queues]), then n_clear tiles whose rays all
-    // miss the grid (their pixels are set to 0 by a fill kernel)
+    // n_tiles tiles: the queued ones [0, q_begin[n_queues]), then n_clear tiles
+    // whose rays all miss the grid (k_finish sets their pixels to 0).  As rows
+    // (their tiles are written on the device), or one by one where the queue's
+    // order does not keep rows or the caller asked for it.
+    uint32_t n_tiles = 0;
+    std::vector<Run> runs;
     std::vector<Tile> tiles;
-    std::vector<Tile> clear;  // (planner scratch)
     size_t parts = 0;         // values of BatchLaunch::parts (0: no tile is queued by segment)
     uint32_t n_clear = 0;
     size_t view_off = 0, tile_off = 0;  // offsets in the uploaded descriptor arrays
     uint32_t n_queues = 8;
-    uint32_t q_begin[MAX_QUEUES + 1] = {};  // chunk bounds in `tiles`
+    uint32_t q_begin[MAX_QUEUES + 1] = {};  // chunk bounds
 };
 
 // Queue heads and sum slots of a launch of n views in some groups, in 64-bit
@@ -131,9 +134,10 @@ struct SumLayout {
 };
 
 // max_parts: the most values of BatchLaunch::parts the caller has room for.
+// as_runs: the caller uploads with begin_plan (else every tile is listed).
 dart_status plan_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
                        void *const *images, const dart_tuning &tun, size_t max_parts,
-                       std::vector<Group> &groups);
+                       bool as_runs, std::vector<Group> &groups);
 // The launches of a plan share one parts array (they run one after the other).
 size_t parts_of(const std::vector<Group> &groups);
 
@@ -148,6 +152,7 @@ struct Workspace {
     void *sums_host = nullptr;          // pinned: the views' totals (launch_totals)
     size_t sums_host_cap = 0;
     unsigned long long *flag = nullptr; // device: the first bad element of a load
+    bool flag_clear = false;            // it holds ~0
     void *img_host = nullptr;           // pinned: a small host-destined image
     size_t img_host_cap = 0;
     unsigned char *desc = nullptr;      // the plan's view, then tile descriptors
@@ -171,7 +176,7 @@ struct Workspace {
 void read_totals(const void *host, int32_t n, double *flux, uint64_t *steps);
 Workspace *get_workspace(hipStream_t stream);
 hipError_t ws_flag(Workspace *ws);
-hipError_t ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_u64,
+hipError_t ws_reserve(Workspace *ws, size_t staged, size_t resident, size_t img_u64,
                       size_t acc_words, size_t n_parts = 0);
 // The kernels of a plan whose queue heads (and sums) launch_begin has cleared.
 // sums: whether they add up flux and cell-steps.
@@ -180,6 +185,14 @@ hipError_t enqueue_plan(const std::vector<Group> &groups, const SumLayout &lay,
                         const RayView *dviews, const Tile *dtiles, const dart_tuning &tun,
                         int device, hipStream_t stream);
 void assign_offsets(std::vector<Group> &groups, size_t *n_views, size_t *n_tiles);
-void pack_descriptors(const std::vector<Group> &groups, size_t n_views, void *dst);
+// Bytes of a plan's descriptors on the host (views, then runs or tiles) and on the
+// device (views, then tiles).
+size_t staged_bytes(const std::vector<Group> &groups);
+size_t resident_bytes(const std::vector<Group> &groups);
+void pack_descriptors(const std::vector<Group> &groups, void *dst);
+// Clears n_clear words and makes the device's descriptors from the packed ones in
+// pinned memory.
+hipError_t begin_plan(const std::vector<Group> &groups, const void *packed, void *dev,
+                      unsigned long long *clear, size_t n_clear, hipStream_t stream);
 
 }  // namespace dart

@@ -273,8 +273,10 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
         void *p[2] = {nullptr, nullptr};
         ~Guard() { for (void *q : p) if (q) (void)hipFree(q); }
     } guard;
-    hipError_t e = launch_fill_u64(err, 1, ~0ull, stream);
+    // (it keeps its clear value from load to load)
+    hipError_t e = ws->flag_clear ? hipSuccess : launch_fill_u64(err, 1, ~0ull, stream);
     if (e != hipSuccess) return hip_fail(e, "clear error flag");
+    ws->flag_clear = false;
     // An allocated plane is kept in step: the load writes its elements with the
     // records, once the renders that read it have finished, and the next render
     // need not repack the whole stack (refill of one of eight 256^3 FP16 epochs and
@@ -311,10 +313,11 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
             HIP_TRY(hipStreamSynchronize(stream), "sync");
         }
     }
-    HIP_TRY(hipMemcpyAsync(ws->sums_host, err, sizeof(*err), hipMemcpyDeviceToHost, stream),
-            "D2H err");
+    HIP_TRY(launch_begin(nullptr, 0, ws->sums_host, err, 1, nullptr, 0, nullptr, stream),
+            "read error flag");
     HIP_TRY(hipStreamSynchronize(stream), "sync");
     const unsigned long long bad = *(const unsigned long long *)ws->sums_host;
+    ws->flag_clear = bad == ~0ull;
     if (bad != ~0ull) {
         const uint64_t m = bad / ncell, c = bad % ncell;
         const uint64_t x = c % s->dev.n[0], y = (c / s->dev.n[0]) % s->dev.n[1],
@@ -993,7 +996,7 @@ void SumLayout::total(const unsigned long long *h, size_t view, double *flux,
     if (steps) *steps = c;
 }
 
-hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_t img_bytes,
+hipError_t dart::ws_reserve(Workspace *ws, size_t staged, size_t resident, size_t img_bytes,
                             size_t acc_words, size_t n_parts) {
     hipError_t e;
     if (ws->stage_ready) {
@@ -1011,12 +1014,9 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t n_views, size_t n_tiles, size_
         }
     } moved{ws, {ws->acc, ws->desc, ws->img, ws->parts}};
     if ((e = grow_dev(ws->acc, ws->acc_cap, acc_words)) != hipSuccess) return e;
-    if ((e = grow_dev(ws->desc, ws->desc_cap, n_views * sizeof(RayView) + n_tiles * sizeof(Tile))) !=
-        hipSuccess)
-        return e;
+    if (resident && (e = grow_dev(ws->desc, ws->desc_cap, resident)) != hipSuccess) return e;
     if (img_bytes && (e = grow_dev(ws->img, ws->img_cap, img_bytes)) != hipSuccess) return e;
-    const size_t stage = n_views * sizeof(RayView) + n_tiles * sizeof(Tile) + 64;
-    if ((e = grow_host(ws->stage, ws->stage_cap, stage)) != hipSuccess) return e;
+    if (staged && (e = grow_host(ws->stage, ws->stage_cap, staged)) != hipSuccess) return e;
     if (!ws->stage_ready) {
         if ((e = hipEventCreateWithFlags(&ws->stage_done, hipEventDisableTiming)) != hipSuccess)
             return e;
@@ -1069,7 +1069,7 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     // copied on by the host (the 128^2 FP64 image with its sums: 69 us, 90 with
     // copy commands for both).
     const bool mapped = !dev_img && img_bytes <= MAPPED_IMAGE;
-    HIP_TRY(ws_reserve(ws, 1, 0, dev_img || mapped ? 0 : img_bytes / 8 + 1, lay.words()),
+    HIP_TRY(ws_reserve(ws, 0, 0, dev_img || mapped ? 0 : img_bytes / 8 + 1, lay.words()),
             "workspace");
     if (mapped) HIP_TRY(grow_host(ws->img_host, ws->img_host_cap, MAPPED_IMAGE), "image staging");
     rv.image = dev_img ? image : mapped ? ws->img_host : (void *)ws->img;
@@ -1077,7 +1077,7 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     rv.tile_w_log2 = 3;
     if (sums) {
         HIP_TRY(grow_host(ws->sums_host, ws->sums_host_cap, 16), "totals");
-        HIP_TRY(launch_begin(ws->acc, lay.words(), nullptr, nullptr, 0, stream),
+        HIP_TRY(launch_begin(ws->acc, lay.words(), nullptr, nullptr, 0, nullptr, 0, nullptr, stream),
                 "clear accumulators");
     }
     HIP_TRY(launch_plain(rv, sums ? lay.sums(ws->acc) : RenderSums{}, stream), "render kernel");
@@ -1405,12 +1405,59 @@ static double tile_cost(const RayView &rv, int tx, int ty, int tw, int th) {
     return 1.0 + 64.0 * (s_out - s_in) * per_len;
 }
 
+// One row of a view's tiles that rays of the grid can reach: tiles [a, b).
+struct TileRow {
+    uint32_t view;
+    int32_t ty, a, b;
+    double cost;  // (queue order 4) its longest estimated tile
+};
+
+// The tiles of row ty that the row's part of the footprint can meet, as
+// [a, b): u1(tx) < u_lo or u0(tx) > u_hi marks one that it cannot, and both are
+// monotonic in tx, so the ends are found from an estimate settled by those tests.
+static void row_span(const RayView &rv, const Footprint &fp, int ty, int tw, int th, int ntx,
+                     int32_t *a_out, int32_t *b_out) {
+    const double w0 = (ty * th + 0.5 - 0.5 * rv.height) * rv.ps;
+    const double w1 = ((ty + 1) * th - 0.5 - 0.5 * rv.height) * rv.ps;
+    double u_lo, u_hi;
+    *a_out = *b_out = 0;
+    if (!band_span(fp, w0, w1, &u_lo, &u_hi)) return;
+    auto u0 = [&](int tx) { return ((double)tx * tw + 0.5 - 0.5 * rv.width) * rv.ps; };
+    auto u1 = [&](int tx) { return ((double)(tx + 1) * tw - 0.5 - 0.5 * rv.width) * rv.ps; };
+    auto guess = [&](double u) {
+        const double t = floor((u / rv.ps + 0.5 * rv.width) / tw);
+        return t < 0.0 ? 0 : t > (double)ntx ? ntx : (int)t;
+    };
+    int a = guess(u_lo), b = guess(u_hi);
+    while (a > 0 && !(u1(a - 1) < u_lo)) a--;
+    while (a < ntx && u1(a) < u_lo) a++;
+    while (b < ntx && !(u0(b) > u_hi)) b++;
+    while (b > a && u0(b - 1) > u_hi) b--;
+    *a_out = a;
+    *b_out = std::max(a, b);
+}
+
+// The tiles of a run, appended to `tiles`.
+static void expand_run(const Run &r, std::vector<Tile> &tiles) {
+    const uint32_t seg = r.count_seg >> RUN_SEG_SHIFT;
+    const uint32_t n = (r.count_seg & ((1u << RUN_SEG_SHIFT) - 1u)) << seg;
+    for (uint32_t i = 0; i < n; i++) {
+        Tile t;
+        t.view = r.view | (i & ((1u << seg) - 1u)) << TILE_SEG_SHIFT;
+        t.tx = (uint16_t)(r.tx + (i >> seg));
+        t.ty = r.ty;
+        tiles.push_back(t);
+    }
+}
+
 dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
                              void *const *images, const dart_tuning &tun, size_t max_parts,
-                             std::vector<Group> &groups) {
+                             bool as_runs, std::vector<Group> &groups) {
     groups.clear();
     const int lw0 = ilog2_exact(tun.tile_w);
     std::map<int, size_t> gindex;
+    std::vector<std::vector<TileRow>> all_rows;   // per group: rows of queued tiles
+    std::vector<std::vector<TileRow>> all_clear;  // per group: tiles to clear
     for (int32_t i = 0; i < n; i++) {
         RayView rv;
         dart_status st = resolve_view(stacks[i], &views[i], &rv);
@@ -1426,6 +1473,8 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
         if (it == gindex.end()) {
             it = gindex.emplace(key, groups.size()).first;
             groups.emplace_back();
+            all_rows.emplace_back();
+            all_clear.emplace_back();
             groups.back().store = rv.st.store;
             groups.back().f64 = (rv.flags & F_F64_DDA) != 0;
             groups.back().labelled = rv.n_blocks > 0;
@@ -1435,6 +1484,7 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
             groups.back().jp32 = (rv.flags & F_PLANE32) != 0;
         }
         Group &g = groups[it->second];
+        std::vector<TileRow> &rows = all_rows[it->second], &clear = all_clear[it->second];
         const uint32_t vi = (uint32_t)g.views.size();
         const int lw = orient_flips(rv, tun) ? 6 - lw0 : lw0;
         rv.tile_w_log2 = lw;
@@ -1453,176 +1503,205 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
         const bool skip = rv.n_blocks == 0;
         const Footprint fp = footprint(rv);
         for (int ty = 0; ty < nty; ty++) {
-            double u_lo = -INFINITY, u_hi = INFINITY;
-            bool row_hits = true;
-            if (skip) {
-                const double w0 = (ty * th + 0.5 - 0.5 * rv.height) * rv.ps;
-                const double w1 = ((ty + 1) * th - 0.5 - 0.5 * rv.height) * rv.ps;
-                row_hits = band_span(fp, w0, w1, &u_lo, &u_hi);
-            }
-            for (int tx = 0; tx < ntx; tx++) {
-                Tile t;
-                t.view = vi;
-                t.tx = (uint16_t)tx;
-                t.ty = (uint16_t)ty;
-                const double u0 = (tx * tw + 0.5 - 0.5 * rv.width) * rv.ps;
-                const double u1 = ((tx + 1) * tw - 0.5 - 0.5 * rv.width) * rv.ps;
-                if (skip && (!row_hits || u1 < u_lo || u0 > u_hi)) {
-                    // cleared by a fill kernel; an adding view keeps its values
-                    if (!(rv.flags & F_ACCUMULATE)) g.clear.push_back(t);
-                } else {
-                    g.tiles.push_back(t);
-                }
+            int32_t a = 0, b = ntx;
+            if (skip) row_span(rv, fp, ty, tw, th, ntx, &a, &b);
+            if (a < b) rows.push_back({vi, ty, a, b, 0.0});
+            // cleared by k_finish; an adding view keeps its values
+            if (rv.flags & F_ACCUMULATE) continue;
+            if (a == b) {
+                clear.push_back({vi, ty, 0, ntx, 0.0});
+            } else {
+                if (a > 0) clear.push_back({vi, ty, 0, a, 0.0});
+                if (b < ntx) clear.push_back({vi, ty, b, ntx, 0.0});
             }
         }
     }
-    // Tiles of views with depth segments are queued segment by segment, view by
-    // view while their sums fit (the tiles of the others are marched segment
-    // after segment by one wave, without the parallel parts: FP16 batch 9.25 ->
-    // 9.6 ms if all are).
-    for (Group &g : groups) {
-        std::vector<size_t> tiles(g.views.size(), 0);
-        for (const Tile &t : g.tiles) tiles[t.view]++;
+    for (size_t gi = 0; gi < groups.size(); gi++) {
+        Group &g = groups[gi];
+        std::vector<TileRow> &rows = all_rows[gi];
+        const size_t nq = MAX_QUEUES;
+        g.n_queues = (uint32_t)nq;
+        uint64_t queued = 0, cleared = 0;
+        std::vector<size_t> tiles_of(g.views.size(), 0);
+        for (const TileRow &r : rows) {
+            tiles_of[r.view] += r.b - r.a;
+            queued += r.b - r.a;
+        }
+        for (const TileRow &r : all_clear[gi]) cleared += r.b - r.a;
+        // Tiles of views with depth segments are queued segment by segment, view by
+        // view while their sums fit (the tiles of the others are marched segment
+        // after segment by one wave, without the parallel parts: FP16 batch 9.25
+        // -> 9.6 ms if all are).
         const size_t per_item = 64 * (g.vec ? 4 : 1);
         size_t room = std::min(max_parts, (size_t)UINT32_MAX) / per_item;  // queue positions
-        room -= std::min(room, g.tiles.size());
+        room -= std::min(room, (size_t)queued);
+        uint64_t items = queued;
         for (size_t v = 0; v < g.views.size() && g.views.size() <= (1u << TILE_SEG_SHIFT); v++) {
-            const size_t more = tiles[v] * ((1u << g.views[v].seg_log2) - 1);
+            const size_t more = tiles_of[v] * ((1u << g.views[v].seg_log2) - 1);
             if (more == 0 || more > room) continue;
             room -= more;
+            items += more;
             g.views[v].seg_items = 1;
-            g.parts = per_item;  // (sized once the queue is laid out)
+            g.parts = per_item;
         }
-    }
-    for (Group &g : groups) {
-        const size_t nq = MAX_QUEUES;
-        bool bounds_set = false;
+        if (items + cleared > UINT32_MAX)
+            return fail(DART_E_INVAL, "more than 2^32 tiles in one call");
+        g.parts *= items;
+        g.n_clear = (uint32_t)cleared;
+        g.n_tiles = (uint32_t)(items + cleared);
+        auto seg_of = [&g](uint32_t view) {
+            return g.views[view].seg_items ? (uint32_t)g.views[view].seg_log2 : 0u;
+        };
+        if (tun.order == 1 || tun.order == 2) {
+            // orders of single tiles
+            std::vector<Tile> tiles;
+            tiles.reserve(queued);
+            for (const TileRow &r : rows)
+                for (int32_t tx = r.a; tx < r.b; tx++)
+                    tiles.push_back(Tile{r.view, (uint16_t)tx, (uint16_t)r.ty});
+            if (tun.order == 2) {
+                // Z-order (Morton) of the tile coordinates inside each view: tiles
+                // that are close in the queue form compact 2D patches
+                auto morton = [](uint32_t x, uint32_t y) {
+                    uint64_t k = 0;
+                    for (int b = 0; b < 16; b++)
+                        k |= (uint64_t)((x >> b) & 1u) << (2 * b) | (uint64_t)((y >> b) & 1u) << (2 * b + 1);
+                    return k;
+                };
+                std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile &a, const Tile &b) {
+                    if (a.view != b.view) return a.view < b.view;
+                    return morton(a.tx, a.ty) < morton(b.tx, b.ty);
+                });
+            } else {
+                // longest estimated tile first; the queue chunks interleave so each
+                // XCD's chunk also runs longest first
+                std::vector<std::pair<double, uint32_t>> cost(tiles.size());
+                for (size_t k = 0; k < tiles.size(); k++) {
+                    const Tile &t = tiles[k];
+                    const RayView &tv = g.views[t.view];
+                    cost[k] = {tile_cost(tv, t.tx, t.ty, 1 << tv.tile_w_log2, 64 >> tv.tile_w_log2),
+                               (uint32_t)k};
+                }
+                std::stable_sort(cost.begin(), cost.end(),
+                                 [](const std::pair<double, uint32_t> &a,
+                                    const std::pair<double, uint32_t> &b) { return a.first > b.first; });
+                const size_t nt = tiles.size();
+                std::vector<Tile> out(nt);
+                // rank r goes to chunk r % nq, position r / nq inside it
+                std::vector<size_t> chunk_begin(nq + 1);
+                for (size_t q = 0; q <= nq; q++) chunk_begin[q] = nt * q / nq;
+                std::vector<size_t> fill(nq, 0);
+                size_t q = 0;
+                for (size_t r = 0; r < nt; r++) {
+                    // next chunk with room, round robin
+                    for (size_t tries = 0; tries < nq; tries++) {
+                        if (chunk_begin[q] + fill[q] < chunk_begin[q + 1]) break;
+                        q = (q + 1) % nq;
+                    }
+                    out[chunk_begin[q] + fill[q]++] = tiles[cost[r].second];
+                    q = (q + 1) % nq;
+                }
+                tiles.swap(out);
+            }
+            // each tile's segments at consecutive places of its queue
+            g.tiles.reserve(g.n_tiles);
+            uint32_t q = 0;
+            for (uint64_t k = 0; k <= tiles.size(); k++) {
+                while (q <= nq && (uint64_t)tiles.size() * q / nq == k)
+                    g.q_begin[q++] = (uint32_t)g.tiles.size();
+                if (k == tiles.size()) break;
+                const Tile &t = tiles[k];
+                expand_run(Run{0, t.view, 1u | seg_of(t.view) << RUN_SEG_SHIFT, t.tx, t.ty}, g.tiles);
+            }
+            for (const TileRow &r : all_clear[gi])
+                expand_run(Run{0, r.view, (uint32_t)(r.b - r.a), (uint16_t)r.a, (uint16_t)r.ty},
+                           g.tiles);
+            continue;
+        }
+        std::vector<size_t> row_chunk;  // (order 4) where each chunk's rows begin
         if (tun.order == 4) {
             // whole tile rows, the row with the longest estimated tile first,
             // dealt round robin to the queue chunks: every chunk starts on
             // heavy rows and ends on light ones, and a row's tiles stay
             // together
-            struct Row { double cost; uint32_t view; uint16_t ty; std::vector<Tile> tiles; };
-            std::vector<Row> rows;
-            std::map<std::pair<uint32_t, uint16_t>, size_t> at;
-            for (const Tile &t : g.tiles) {
-                auto key = std::make_pair(t.view, t.ty);
-                auto it = at.find(key);
-                if (it == at.end()) {
-                    it = at.emplace(key, rows.size()).first;
-                    rows.push_back(Row{0.0, t.view, t.ty, {}});
-                }
-                const RayView &tv = g.views[t.view];
-                Row &r = rows[it->second];
-                r.cost = std::max(r.cost, tile_cost(tv, t.tx, t.ty, 1 << tv.tile_w_log2,
-                                                    64 >> tv.tile_w_log2));
-                r.tiles.push_back(t);
+            for (TileRow &r : rows) {
+                const RayView &tv = g.views[r.view];
+                for (int32_t tx = r.a; tx < r.b; tx++)
+                    r.cost = std::max(r.cost, tile_cost(tv, tx, r.ty, 1 << tv.tile_w_log2,
+                                                        64 >> tv.tile_w_log2));
             }
             std::stable_sort(rows.begin(), rows.end(),
-                             [](const Row &a, const Row &b) { return a.cost > b.cost; });
-            std::vector<std::vector<Tile>> chunk(nq);
+                             [](const TileRow &a, const TileRow &b) { return a.cost > b.cost; });
+            std::vector<std::vector<TileRow>> chunk(nq);
             std::vector<size_t> load(nq, 0);
-            for (const Row &r : rows) {
+            for (const TileRow &r : rows) {
                 // the chunk with the fewest tiles so far (ties: the lowest index)
                 size_t q = 0;
                 for (size_t k = 1; k < nq; k++)
                     if (load[k] < load[q]) q = k;
-                chunk[q].insert(chunk[q].end(), r.tiles.begin(), r.tiles.end());
-                load[q] += r.tiles.size();
+                chunk[q].push_back(r);
+                load[q] += r.b - r.a;
             }
-            g.tiles.clear();
+            rows.clear();
             for (size_t q = 0; q < nq; q++) {
-                g.q_begin[q] = (uint32_t)g.tiles.size();
-                g.tiles.insert(g.tiles.end(), chunk[q].begin(), chunk[q].end());
+                row_chunk.push_back(rows.size());
+                rows.insert(rows.end(), chunk[q].begin(), chunk[q].end());
             }
-            g.q_begin[nq] = (uint32_t)g.tiles.size();
-            bounds_set = true;
+            row_chunk.push_back(rows.size());
         } else if (tun.order == 3) {
             // rows from the middle outward: the upper half from its last row
             // up, then the lower half down.  Rows stay whole and in sequence
             // (neighbouring tiles still run together), but the rows through
             // the middle of the grid, whose rays are longest, start first and
             // each queue chunk ends with short or empty rows.
-            auto row_key = [&g](const Tile &t) {
-                const RayView &tv = g.views[t.view];
+            auto row_key = [&g](const TileRow &r) {
+                const RayView &tv = g.views[r.view];
                 const int th = 64 >> tv.tile_w_log2;
                 const int nty = (tv.height + th - 1) / th, half = nty / 2;
-                return t.ty < half ? half - 1 - t.ty : t.ty;
+                return r.ty < half ? half - 1 - r.ty : r.ty;
             };
-            std::stable_sort(g.tiles.begin(), g.tiles.end(), [&](const Tile &a, const Tile &b) {
+            std::stable_sort(rows.begin(), rows.end(), [&](const TileRow &a, const TileRow &b) {
                 if (a.view != b.view) return a.view < b.view;
                 return row_key(a) < row_key(b);
             });
-        } else if (tun.order == 2) {
-            // Z-order (Morton) of the tile coordinates inside each view: tiles
-            // that are close in the queue form compact 2D patches
-            auto morton = [](uint32_t x, uint32_t y) {
-                uint64_t k = 0;
-                for (int b = 0; b < 16; b++)
-                    k |= (uint64_t)((x >> b) & 1u) << (2 * b) | (uint64_t)((y >> b) & 1u) << (2 * b + 1);
-                return k;
-            };
-            std::stable_sort(g.tiles.begin(), g.tiles.end(), [&](const Tile &a, const Tile &b) {
-                if (a.view != b.view) return a.view < b.view;
-                return morton(a.tx, a.ty) < morton(b.tx, b.ty);
-            });
-        } else if (tun.order == 1) {
-            // longest estimated tile first; the queue chunks interleave so each
-            // XCD's chunk also runs longest first
-            std::vector<std::pair<double, uint32_t>> cost(g.tiles.size());
-            for (size_t k = 0; k < g.tiles.size(); k++) {
-                const Tile &t = g.tiles[k];
-                const RayView &tv = g.views[t.view];
-                cost[k] = {tile_cost(tv, t.tx, t.ty, 1 << tv.tile_w_log2, 64 >> tv.tile_w_log2),
-                           (uint32_t)k};
-            }
-            std::stable_sort(cost.begin(), cost.end(),
-                             [](const std::pair<double, uint32_t> &a,
-                                const std::pair<double, uint32_t> &b) { return a.first > b.first; });
-            const size_t nt = g.tiles.size();
-            std::vector<Tile> out(nt);
-            // rank r goes to chunk r % nq, position r / nq inside it
-            std::vector<size_t> chunk_begin(nq + 1);
-            for (size_t q = 0; q <= nq; q++) chunk_begin[q] = nt * q / nq;
-            std::vector<size_t> fill(nq, 0);
-            size_t q = 0;
-            for (size_t r = 0; r < nt; r++) {
-                // next chunk with room, round robin
-                for (size_t tries = 0; tries < nq; tries++) {
-                    if (chunk_begin[q] + fill[q] < chunk_begin[q + 1]) break;
-                    q = (q + 1) % nq;
-                }
-                out[chunk_begin[q] + fill[q]++] = g.tiles[cost[r].second];
-                q = (q + 1) % nq;
-            }
-            g.tiles.swap(out);
         }
-        g.n_queues = (uint32_t)nq;
-        if (!bounds_set)
-            for (size_t q = 0; q <= nq; q++)
-                g.q_begin[q] = (uint32_t)(((uint64_t)g.tiles.size() * q) / nq);
-        if (g.parts) {
-            // each tile's segments at consecutive places of its queue
-            std::vector<Tile> items;
-            uint32_t q = 0;
-            for (uint32_t k = 0; k <= g.tiles.size(); k++) {
-                while (q <= nq && g.q_begin[q] == k) g.q_begin[q++] = (uint32_t)items.size();
-                if (k == g.tiles.size()) break;
-                Tile t = g.tiles[k];
-                const RayView &tv = g.views[t.view];
-                const uint32_t n_seg = tv.seg_items ? 1u << tv.seg_log2 : 1u;
-                for (uint32_t s = 0; s < n_seg; s++) {
-                    items.push_back(t);
-                    items.back().view |= s << TILE_SEG_SHIFT;
+        // the runs in queue order, and the chunk bounds: at equal shares of the
+        // tiles, or (order 4) between the dealt rows
+        uint64_t tile = 0;
+        uint32_t place = 0, q = 0;
+        g.runs.reserve(rows.size() + all_clear[gi].size());
+        for (size_t k = 0; k <= rows.size(); k++) {
+            const bool end = k == rows.size();
+            const uint32_t count = end ? 0 : (uint32_t)(rows[k].b - rows[k].a);
+            const uint32_t seg = end ? 0 : seg_of(rows[k].view);
+            for (; q <= nq; q++) {
+                if (tun.order == 4) {
+                    if (row_chunk[q] != k) break;
+                    g.q_begin[q] = place;
+                } else {
+                    const uint64_t bound = queued * q / nq;
+                    if (bound >= tile + count && !end) break;
+                    g.q_begin[q] = place + ((uint32_t)(bound - tile) << seg);
                 }
             }
-            g.tiles.swap(items);
-            g.parts *= g.tiles.size();
+            if (end) break;
+            const TileRow &r = rows[k];
+            g.runs.push_back(Run{place, r.view, count | seg << RUN_SEG_SHIFT, (uint16_t)r.a,
+                                 (uint16_t)r.ty});
+            tile += count;
+            place += count << seg;
         }
         // the tiles to clear follow the queued ones in the same array
-        g.n_clear = (uint32_t)g.clear.size();
-        g.tiles.insert(g.tiles.end(), g.clear.begin(), g.clear.end());
-        g.clear.clear();
+        for (const TileRow &r : all_clear[gi]) {
+            g.runs.push_back(Run{place, r.view, (uint32_t)(r.b - r.a), (uint16_t)r.a,
+                                 (uint16_t)r.ty});
+            place += r.b - r.a;
+        }
+        if (!as_runs) {
+            g.tiles.reserve(g.n_tiles);
+            for (const Run &r : g.runs) expand_run(r, g.tiles);
+            g.runs.clear();
+        }
     }
     return DART_OK;
 }
@@ -1679,19 +1758,58 @@ void dart::assign_offsets(std::vector<Group> &groups, size_t *n_views, size_t *n
         gr.view_off = nv;
         gr.tile_off = nt;
         nv += gr.views.size();
-        nt += gr.tiles.size();
+        nt += gr.n_tiles;
     }
     *n_views = nv;
     *n_tiles = nt;
 }
 
-void dart::pack_descriptors(const std::vector<Group> &groups, size_t n_views, void *dst) {
+size_t dart::staged_bytes(const std::vector<Group> &groups) {
+    size_t b = 0;
+    for (const Group &gr : groups)
+        b += gr.views.size() * sizeof(RayView) + gr.runs.size() * sizeof(Run) +
+             gr.tiles.size() * sizeof(Tile);
+    return b;
+}
+
+size_t dart::resident_bytes(const std::vector<Group> &groups) {
+    size_t b = 0;
+    for (const Group &gr : groups)
+        b += gr.views.size() * sizeof(RayView) + gr.n_tiles * sizeof(Tile);
+    return b;
+}
+
+// Views first, then runs or tiles: the groups of a plan all have the one or the
+// other (one queue order for the whole plan).
+void dart::pack_descriptors(const std::vector<Group> &groups, void *dst) {
     char *h = (char *)dst;
-    char *ht = h + n_views * sizeof(RayView);
     for (const Group &gr : groups) {
-        memcpy(h + gr.view_off * sizeof(RayView), gr.views.data(), gr.views.size() * sizeof(RayView));
-        memcpy(ht + gr.tile_off * sizeof(Tile), gr.tiles.data(), gr.tiles.size() * sizeof(Tile));
+        memcpy(h, gr.views.data(), gr.views.size() * sizeof(RayView));
+        h += gr.views.size() * sizeof(RayView);
     }
+    for (const Group &gr : groups) {
+        Run *runs = (Run *)h;
+        for (size_t k = 0; k < gr.runs.size(); k++) {
+            runs[k] = gr.runs[k];
+            runs[k].first += (uint32_t)gr.tile_off;
+        }
+        h += gr.runs.size() * sizeof(Run);
+        memcpy(h, gr.tiles.data(), gr.tiles.size() * sizeof(Tile));
+        h += gr.tiles.size() * sizeof(Tile);
+    }
+}
+
+hipError_t dart::begin_plan(const std::vector<Group> &groups, const void *packed, void *dev,
+                            unsigned long long *clear, size_t n_clear, hipStream_t stream) {
+    size_t views = 0, runs = 0, tiles = 0;
+    for (const Group &gr : groups) {
+        views += gr.views.size() * sizeof(RayView);
+        runs += gr.runs.size();
+        tiles += gr.tiles.size() * sizeof(Tile);
+    }
+    return launch_begin(clear, n_clear, dev, packed, (views + tiles) / 8,
+                        (const Run *)((const char *)packed + views), runs,
+                        (Tile *)((char *)dev + views), stream);
 }
 
 // Segment sums a batch's workspace holds at most: 256 MiB, the 512 bytes per
@@ -1772,7 +1890,6 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
 #ifndef DART_USE_GRAPH
 #define DART_USE_GRAPH 1
 #endif
-    size_t desc_words = 0;  // of a new plan
     const bool use_graph = DART_USE_GRAPH && stream != nullptr;
     const bool replay = ws->plan_ready && key == ws->plan_key;
     if (!replay) {
@@ -1783,11 +1900,12 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
             tmp_images[i] = images[i];
         size_t nv = 0, nt = 0;
         for (size_t max_parts : {MAX_PARTS, (size_t)0}) {
-            dart_status st = plan_batch(stacks, views, n, tmp_images.data(), tun, max_parts, groups);
+            dart_status st = plan_batch(stacks, views, n, tmp_images.data(), tun, max_parts, true,
+                                        groups);
             if (st != DART_OK) return st;
             assign_offsets(groups, &nv, &nt);
-            hipError_t e = ws_reserve(ws, std::max(nv, (size_t)n), nt, img_bytes / 8 + 1,
-                                      SumLayout(n, groups.size()).words(), parts_of(groups));
+            hipError_t e = ws_reserve(ws, staged_bytes(groups), resident_bytes(groups),
+                                      img_bytes ? img_bytes / 8 + 1 : 0, SumLayout(n, groups.size()).words(), parts_of(groups));
             if (e == hipSuccess) break;
             // (without room for the segments' sums: no tile queued by segment)
             if (e != hipErrorOutOfMemory || parts_of(groups) == 0) return hip_fail(e, "workspace");
@@ -1798,9 +1916,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
                 if (!(views[rv.acc_index].flags & DART_DEVICE_PTRS))
                     rv.image = (char *)ws->img + img_off[rv.acc_index];
         // stage descriptors and upload
-        char *h = (char *)ws->stage;
-        pack_descriptors(groups, nv, h);
-        desc_words = (nv * sizeof(RayView) + nt * sizeof(Tile)) / 8;
+        pack_descriptors(groups, ws->stage);
         drop_graph(ws);
         ws->plan_groups.swap(groups);
         ws->plan_key = key;
@@ -1822,7 +1938,8 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (use_graph && !exec && replay) {
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
-        hipError_t e = launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, stream);
+        hipError_t e = launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, nullptr, 0, nullptr,
+                                    stream);
         if (e == hipSuccess)
             e = enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles,
                                     tun, ws->device, stream);
@@ -1842,9 +1959,15 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (exec) {
         HIP_TRY(hipGraphLaunch(exec, stream), "graph launch");
     } else {
-        HIP_TRY(launch_begin(ws->acc, n_clear, ws->desc, ws->stage, replay ? 0 : desc_words, stream),
-                "begin");
-        if (!replay) HIP_TRY(hipEventRecord(ws->stage_done, stream), "event");
+        hipError_t e = replay ? launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, nullptr, 0,
+                                             nullptr, stream)
+                              : begin_plan(ws->plan_groups, ws->stage, ws->desc, ws->acc, n_clear,
+                                           stream);
+        if (e == hipSuccess && !replay) e = hipEventRecord(ws->stage_done, stream);
+        if (e != hipSuccess) {
+            drop_graph(ws);  // (no descriptors to replay)
+            return hip_fail(e, "begin");
+        }
         HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles, tun,
                              ws->device, stream),
                 "batch kernels");

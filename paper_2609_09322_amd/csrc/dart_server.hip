@@ -291,9 +291,14 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     size_t nv = 0, nt = 0, desc_bytes = 0, acc_off = 0, parts_off = 0;
     SumLayout lay(n, 0);
     // (tiles queued by depth segment when the buffer holds their parts too)
-    for (size_t max_parts : {srv->desc_cap / 8 * 3 / 4, srv->desc_cap / 8 / 4, (size_t)0}) {
+    // (and tiles as rows unless those take more staging, as on an image of one
+    // column)
+    const size_t values = srv->desc_cap / 8;
+    const std::pair<size_t, bool> tries[] = {{values * 3 / 4, true}, {values / 4, true}, {0, true},
+                                             {0, false}};
+    for (const auto &[max_parts, as_runs] : tries) {
         dart_status st = plan_batch(stacks.data(), views.data(), n, imgs.data(), tun, max_parts,
-                                    groups);
+                                    as_runs, groups);
         if (st != DART_OK) {
             fail_wave(srv, w.get(), st, dart_last_error());
             return;
@@ -304,12 +309,14 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         lay = SumLayout(n, groups.size());
         parts_off = (acc_off + lay.words() * 8 + 511) & ~(size_t)511;
         const size_t parts = parts_of(groups);
-        if (parts == 0 || parts_off + parts * 8 <= srv->desc_cap) break;
+        if (staged_bytes(groups) <= srv->desc_cap &&
+            (parts == 0 || parts_off + parts * 8 <= srv->desc_cap))
+            break;
     }
     if (acc_off + lay.words() * 8 > srv->desc_cap) {
         lay = SumLayout(n, groups.size(), true);
     }
-    if (acc_off + lay.words() * 8 > srv->desc_cap) {
+    if (acc_off + lay.words() * 8 > srv->desc_cap || staged_bytes(groups) > srv->desc_cap) {
         // cannot happen: the per-request bounds cover the plan
         fail_wave(srv, w.get(), DART_E_INTERNAL, "wave descriptors exceed their buffer");
         return;
@@ -322,7 +329,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     char *hstage = (char *)srv->desc_host[sidx];
     char *ddesc = (char *)srv->desc_dev[sidx];
     unsigned long long *dacc = (unsigned long long *)(ddesc + acc_off);
-    pack_descriptors(groups, nv, hstage);
+    pack_descriptors(groups, hstage);
     hipStream_t stream = srv->streams[sidx];
     const Clock::time_point t_planned = Clock::now();
     // the stream's idle time before this wave while requests were waiting:
@@ -333,7 +340,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     lk.unlock();
     hipError_t e = hipEventRecord(srv->ev_begin[sidx], stream);
     if (e == hipSuccess)
-        e = launch_begin(dacc, lay.words(), ddesc, hstage, desc_bytes / 8, stream);
+        e = begin_plan(groups, hstage, ddesc, dacc, lay.words(), stream);
     if (e == hipSuccess) e = hipEventRecord(srv->ev_kbegin[sidx], stream);
     if (e == hipSuccess)
         e = enqueue_plan(groups, lay, dacc, true, (double *)(ddesc + parts_off), (const RayView *)ddesc,

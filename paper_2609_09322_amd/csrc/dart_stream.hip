@@ -41,12 +41,10 @@ struct dart_streamer {
     void *stage_j = nullptr, *stage_b = nullptr;  // one epoch of host source (b inside j's block)
     size_t stage_bytes = 0;
     unsigned long long *err = nullptr;    // [M] first bad element per loaded epoch
-    unsigned long long *acc = nullptr;    // flux[n], steps[n], queue heads
+    unsigned long long *acc = nullptr;    // queue heads and sum slots (SumLayout)
     size_t acc_cap = 0;
-    RayView *d_views = nullptr;
-    size_t views_cap = 0;
-    Tile *d_tiles = nullptr;
-    size_t tiles_cap = 0;
+    char *d_desc = nullptr;               // view and tile descriptors
+    size_t desc_cap = 0;
     void *h_desc = nullptr;               // pinned descriptor staging
     size_t h_desc_cap = 0;
     hipEvent_t desc_done{};
@@ -144,7 +142,7 @@ extern "C" dart_status dart_streamer_destroy(dart_streamer *s) {
     }
     // (stage_b points into stage_j's allocation)
     for (void *p : {(void *)s->d_times, (void *)s->d_invdt, s->stage_j, (void *)s->err,
-                    (void *)s->acc, (void *)s->d_views, (void *)s->d_tiles, (void *)s->img_stage})
+                    (void *)s->acc, (void *)s->d_desc, (void *)s->img_stage})
         if (p) (void)hipFree(p);
     if (s->h_desc) (void)hipHostFree(s->h_desc);
     delete s;
@@ -300,7 +298,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
                 gidx.push_back(i);
             }
         std::vector<Group> g;
-        dart_status st = plan_batch(sts.data(), vv.data(), (int32_t)vv.size(), im.data(), tun, 0, g);
+        dart_status st = plan_batch(sts.data(), vv.data(), (int32_t)vv.size(), im.data(), tun, 0, true, g);
         if (st != DART_OK) return st;
         const bool lo_open = M > 1 && m + 1 < M - 1;
         for (Group &gr : g)
@@ -319,7 +317,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     gbegin.push_back(groups.size());
     size_t nv = 0, nt = 0;
     assign_offsets(groups, &nv, &nt);
-    const size_t desc = nv * sizeof(RayView) + nt * sizeof(Tile);
+    const size_t desc = staged_bytes(groups);
     if (s->desc_pending) {
         ST_TRY(hipEventSynchronize(s->desc_done), "descriptor staging");
         s->desc_pending = false;
@@ -331,21 +329,17 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
         ST_TRY(hipHostMalloc(&s->h_desc, std::max<size_t>(desc, 4096), hipHostMallocDefault), "pinned staging");
         s->h_desc_cap = std::max<size_t>(desc, 4096);
     }
-    ST_TRY(grow((void **)&s->d_views, &s->views_cap, std::max<size_t>(nv, 1) * sizeof(RayView)), "views");
-    ST_TRY(grow((void **)&s->d_tiles, &s->tiles_cap, std::max<size_t>(nt, 1) * sizeof(Tile)), "tiles");
+    ST_TRY(grow((void **)&s->d_desc, &s->desc_cap, std::max<size_t>(resident_bytes(groups), 8)), "descriptors");
+    const RayView *d_views = (const RayView *)s->d_desc;
+    const Tile *d_tiles = (const Tile *)(s->d_desc + nv * sizeof(RayView));
     const SumLayout lay(n, groups.size());
     const size_t acc_n = lay.words();
     const bool sums = flux_out || steps_out;
     ST_TRY(grow((void **)&s->acc, &s->acc_cap, acc_n * 8), "accumulators");
-    if (nv > 0) {
-        pack_descriptors(groups, nv, s->h_desc);
-        ST_TRY(hipMemcpyAsync(s->d_views, s->h_desc, nv * sizeof(RayView), hipMemcpyHostToDevice, stream), "H2D views");
-        ST_TRY(hipMemcpyAsync(s->d_tiles, (char *)s->h_desc + nv * sizeof(RayView), nt * sizeof(Tile),
-                              hipMemcpyHostToDevice, stream), "H2D tiles");
-        ST_TRY(hipEventRecord(s->desc_done, stream), "event");
-        s->desc_pending = true;
-    }
-    ST_TRY(launch_fill_u64(s->acc, acc_n, 0ull, stream), "clear accumulators");
+    pack_descriptors(groups, s->h_desc);
+    ST_TRY(begin_plan(groups, s->h_desc, s->d_desc, s->acc, acc_n, stream), "descriptors");
+    ST_TRY(hipEventRecord(s->desc_done, stream), "event");
+    s->desc_pending = true;
     ST_TRY(launch_fill_u64(s->err, M, ~0ull, stream), "clear error flags");
     for (int32_t i = 0; i < n; i++)
         if (!(views[i].flags & DART_ACCUMULATE))
@@ -400,8 +394,8 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
         for (size_t gi = gbegin[k]; gi < gbegin[k + 1]; gi++) {
             const Group &g = groups[gi];
             BatchLaunch bl;
-            bl.views = s->d_views + g.view_off;
-            bl.tiles = s->d_tiles + g.tile_off;
+            bl.views = d_views + g.view_off;
+            bl.tiles = d_tiles + g.tile_off;
             bl.n_tiles = g.q_begin[g.n_queues];
             bl.head = lay.head(s->acc, gi);
             bl.head_stride = lay.head_stride;
