@@ -72,7 +72,8 @@ typedef enum { DART_F64 = 0, DART_F32 = 1, DART_F16 = 2, DART_BF16 = 3 } dart_dt
                                    whole records, not the emissivity plane) */
 #define DART_FORCE_F64_DDA 0x10u /* FP64 ray parameters (DDA crossings, retarded times) for
                                     16-bit stacks too; FP64 and FP32 stacks always use them,
-                                    16-bit stacks when a ray may cross more than 4096 cells */
+                                    16-bit stacks when a ray may cross more than 4096 cells
+                                    or an axis has more than 2048 */
 #define DART_DEVICE_PTRS 0x20u  /* load: field pointers are device pointers;
                                    view: the image pointer is a device pointer */
 #define DART_KERNEL_PLAIN 0x40u /* dart_render_batch: force the one-launch-per-image kernel */

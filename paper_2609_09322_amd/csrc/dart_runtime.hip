@@ -866,11 +866,17 @@ dart_status dart::resolve_view(const dart_stack *s, const dart_view *v, RayView 
     // cross more than ~4k cells, and for FP32 stacks: FP32 crossings of
     // magnitude ~L/2 carry ~1e-5 absolute rounding, which chords at jumps of
     // the emissivity (a jet surface) turn into ~1e-5 relative pixel errors,
-    // the size of the FP32 tolerance.  16-bit stacks keep FP32 crossings.
-    int64_t most_cells = (int64_t)s->dev.n[0] + s->dev.n[1] + s->dev.n[2];
-    for (const dart_stack *p : s->parts)
-        most_cells = std::max(most_cells, (int64_t)p->dev.n[0] + p->dev.n[1] + p->dev.n[2]);
-    if (most_cells > 4096 || s->dev.store == ST_F32) rv->flags |= F_F64_DDA;
+    // the size of the FP32 tolerance.  16-bit stacks keep FP32 crossings, whose
+    // counts reach 2048 and whose scaled plane spacings 2^104.
+    bool f64_rays = s->dev.store == ST_F32;
+    auto needs_f64 = [](const StackDev &d) {
+        bool need = (int64_t)d.n[0] + d.n[1] + d.n[2] > 4096;
+        for (int a = 0; a < 3; a++) need |= d.n[a] > 2048 || d.n[a] * d.cell[a] > 0x1p100;
+        return need;
+    };
+    f64_rays |= needs_f64(s->dev);
+    for (const dart_stack *p : s->parts) f64_rays |= needs_f64(p->dev);
+    if (f64_rays) rv->flags |= F_F64_DDA;
     rv->width = v->width;
     rv->height = v->height;
     rv->out_f64 = v->out_dtype == DART_F64;
