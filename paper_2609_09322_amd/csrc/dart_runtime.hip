@@ -379,7 +379,7 @@ void dart::note_use(const dart_stack *cs, hipStream_t stream) {
             return;
         }
     hipEvent_t ev;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return;
+    if (hipEventCreateWithFlags(&ev, READ_EVENT) != hipSuccess) return;
     (void)hipEventRecord(ev, stream);
     s->uses.emplace_back(stream, ev);
 }
@@ -1024,7 +1024,7 @@ hipError_t dart::ws_reserve(Workspace *ws, size_t staged, size_t resident, size_
     if (img_bytes && (e = grow_dev(ws->img, ws->img_cap, img_bytes)) != hipSuccess) return e;
     if (staged && (e = grow_host(ws->stage, ws->stage_cap, staged)) != hipSuccess) return e;
     if (!ws->stage_ready) {
-        if ((e = hipEventCreateWithFlags(&ws->stage_done, hipEventDisableTiming)) != hipSuccess)
+        if ((e = hipEventCreateWithFlags(&ws->stage_done, READ_EVENT)) != hipSuccess)
             return e;
         ws->stage_ready = true;
     }

@@ -47,6 +47,8 @@ struct dart_streamer {
     size_t desc_cap = 0;
     void *h_desc = nullptr;               // pinned descriptor staging
     size_t h_desc_cap = 0;
+    unsigned long long *h_res = nullptr;  // pinned: a call's totals and error words
+    size_t h_res_cap = 0;
     hipEvent_t desc_done{};
     bool desc_pending = false;
     char *img_stage = nullptr;            // device images for host-destined views
@@ -112,12 +114,12 @@ extern "C" dart_status dart_streamer_create(const int32_t dims[3], const double 
     if (e == hipSuccess)
         e = hipMemcpy(s->d_invdt, inv.data(), n_epochs * sizeof(double), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->desc_done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->desc_done, READ_EVENT);
     s->ready.resize(ring_epochs);
     s->freed.resize(ring_epochs);
     for (int32_t k = 0; k < ring_epochs && e == hipSuccess; k++) {
         e = hipEventCreateWithFlags(&s->ready[k], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->freed[k], hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->freed[k], READ_EVENT);
     }
     if (e != hipSuccess) {
         dart_streamer *raw = s.release();
@@ -144,6 +146,7 @@ extern "C" dart_status dart_streamer_destroy(dart_streamer *s) {
     for (void *p : {(void *)s->d_times, (void *)s->d_invdt, s->stage_j, (void *)s->err,
                     (void *)s->acc, (void *)s->d_desc, (void *)s->img_stage})
         if (p) (void)hipFree(p);
+    if (s->h_res) (void)hipHostFree(s->h_res);
     if (s->h_desc) (void)hipHostFree(s->h_desc);
     delete s;
     return DART_OK;
@@ -261,6 +264,63 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     for (int32_t i = 0; i < n; i++)
         dimg[i] = (views[i].flags & DART_DEVICE_PTRS) ? images[i] : (void *)(s->img_stage + img_off[i]);
 
+    // The first epochs are converted while the host plans the render: a conversion
+    // needs no descriptor, and planning the intervals of two 512^2 views kept the
+    // GPU idle for 100 of a call's 1370 us.  (The copy stream starts after the
+    // caller's earlier work on `stream`, which may produce the source arrays; a
+    // call that fails from here on waits for what it has enqueued there.)
+    struct Drain {
+        hipStream_t copy;
+        ~Drain() { if (copy) (void)hipStreamSynchronize(copy); }
+    } drain{s->copy};
+    hipEvent_t start;
+    ST_TRY(hipEventCreateWithFlags(&start, hipEventDisableTiming), "event");
+    (void)hipEventRecord(start, stream);
+    (void)hipStreamWaitEvent(s->copy, start, 0);
+    (void)hipEventDestroy(start);
+    ST_TRY(launch_fill_u64(s->err, M, ~0ull, s->copy), "clear error flags");
+    if (!dev_src) {
+        ST_TRY(grow(&s->stage_j, &s->stage_bytes, ncell * esz * 4), "source staging");
+        s->stage_b = (char *)s->stage_j + ncell * esz;
+    }
+    std::vector<char> slot_used(R, 0);
+    size_t next = 0;
+    uint64_t uploaded = 0;
+    auto load = [&](int32_t e) -> dart_status {
+        const int32_t k = slot[e];
+        if (slot_used[k]) ST_TRY(hipStreamWaitEvent(s->copy, s->freed[k], 0), "wait slot");
+        slot_used[k] = 1;
+        const char *hj = (const char *)emissivity + (size_t)e * ncell * esz;
+        const char *hb = (const char *)velocity + (size_t)e * ncell * esz * 3;
+        const void *dj = hj, *db = hb;
+        if (!dev_src) {
+            ST_TRY(hipMemcpyAsync(s->stage_j, hj, ncell * esz, hipMemcpyHostToDevice, s->copy), "H2D j");
+            ST_TRY(hipMemcpyAsync(s->stage_b, hb, ncell * esz * 3, hipMemcpyHostToDevice, s->copy), "H2D beta");
+            uploaded += ncell * esz * 4;
+            dj = s->stage_j;
+            db = s->stage_b;
+        }
+        // convert into slot k; a bad element is reported in err[e]
+        ST_TRY(launch_convert(esz == 8, rd.store, dj, db, k, 1, rd, (void *)rd.data, nullptr, s->err + e,
+                              s->copy), "convert kernel");
+        ST_TRY(hipEventRecord(s->ready[k], s->copy), "event");
+        return DART_OK;
+    };
+    // every epoch up to R - 2 ahead of interval k's later epoch
+    auto load_ahead = [&](size_t k) -> dart_status {
+        const int32_t hi = M > 1 ? iv[k] + 1 : iv[k];
+        while (next < order.size() && rank[order[next]] <= rank[hi] + (R - 2)) {
+            dart_status st = load(order[next]);
+            if (st != DART_OK) return st;
+            next++;
+        }
+        return DART_OK;
+    };
+    if (!iv.empty()) {
+        dart_status st = load_ahead(0);
+        if (st != DART_OK) return st;
+    }
+
     // one descriptor set for every interval: interval stacks over ring slots
     const dart_tuning tun = tuning_for(nullptr);
     std::vector<std::unique_ptr<dart_stack>> istacks;
@@ -340,55 +400,16 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     ST_TRY(begin_plan(groups, s->h_desc, s->d_desc, s->acc, acc_n, stream), "descriptors");
     ST_TRY(hipEventRecord(s->desc_done, stream), "event");
     s->desc_pending = true;
-    ST_TRY(launch_fill_u64(s->err, M, ~0ull, stream), "clear error flags");
     for (int32_t i = 0; i < n; i++)
         if (!(views[i].flags & DART_ACCUMULATE))
             ST_TRY(hipMemsetAsync(dimg[i], 0, img_bytes[i], stream), "clear image");
-    // the copy stream starts after everything above (buffers of the last call)
-    hipEvent_t start;
-    ST_TRY(hipEventCreateWithFlags(&start, hipEventDisableTiming), "event");
-    (void)hipEventRecord(start, stream);
-    (void)hipStreamWaitEvent(s->copy, start, 0);
-    (void)hipEventDestroy(start);
-
-    if (!dev_src) {
-        ST_TRY(grow(&s->stage_j, &s->stage_bytes, ncell * esz * 4), "source staging");
-        s->stage_b = (char *)s->stage_j + ncell * esz;
-    }
-    std::vector<char> slot_used(R, 0);
-    size_t next = 0;
-    uint64_t uploaded = 0;
     const int cus = device_cus(s->device);
     const int blocks = std::max(1, cus * tun.waves_per_cu / 4);
-    auto load = [&](int32_t e) -> dart_status {
-        const int32_t k = slot[e];
-        if (slot_used[k]) ST_TRY(hipStreamWaitEvent(s->copy, s->freed[k], 0), "wait slot");
-        slot_used[k] = 1;
-        const char *hj = (const char *)emissivity + (size_t)e * ncell * esz;
-        const char *hb = (const char *)velocity + (size_t)e * ncell * esz * 3;
-        const void *dj = hj, *db = hb;
-        if (!dev_src) {
-            ST_TRY(hipMemcpyAsync(s->stage_j, hj, ncell * esz, hipMemcpyHostToDevice, s->copy), "H2D j");
-            ST_TRY(hipMemcpyAsync(s->stage_b, hb, ncell * esz * 3, hipMemcpyHostToDevice, s->copy), "H2D beta");
-            uploaded += ncell * esz * 4;
-            dj = s->stage_j;
-            db = s->stage_b;
-        }
-        // convert into slot k; a bad element is reported in err[e]
-        ST_TRY(launch_convert(esz == 8, rd.store, dj, db, k, 1, rd, (void *)rd.data, nullptr, s->err + e,
-                              s->copy), "convert kernel");
-        ST_TRY(hipEventRecord(s->ready[k], s->copy), "event");
-        return DART_OK;
-    };
     for (size_t k = 0; k < iv.size(); k++) {
         const int32_t m = iv[k];
         const int32_t hi = M > 1 ? m + 1 : m;
-        // load every epoch up to R - 2 ahead of this interval's later epoch
-        while (next < order.size() && rank[order[next]] <= rank[hi] + (R - 2)) {
-            dart_status st = load(order[next]);
-            if (st != DART_OK) return st;
-            next++;
-        }
+        dart_status st = load_ahead(k);
+        if (st != DART_OK) return st;
         ST_TRY(hipStreamWaitEvent(stream, s->ready[slot[m]], 0), "wait epoch");
         if (hi != m) ST_TRY(hipStreamWaitEvent(stream, s->ready[slot[hi]], 0), "wait epoch");
         for (size_t gi = gbegin[k]; gi < gbegin[k + 1]; gi++) {
@@ -414,13 +435,24 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
     for (int32_t i = 0; i < n; i++)
         if (!(views[i].flags & DART_DEVICE_PTRS))
             ST_TRY(hipMemcpyAsync(images[i], dimg[i], img_bytes[i], hipMemcpyDeviceToHost, stream), "D2H image");
-    std::vector<unsigned long long> acc(lay.sum_words()), bad(M);
-    if (sums)
-        ST_TRY(hipMemcpyAsync(acc.data(), s->acc + lay.heads_words(), acc.size() * 8,
-                              hipMemcpyDeviceToHost, stream), "D2H acc");
-    ST_TRY(hipStreamSynchronize(s->copy), "sync copy stream");
-    ST_TRY(hipMemcpyAsync(bad.data(), s->err, M * 8, hipMemcpyDeviceToHost, stream), "D2H err");
+    // Totals and error words go to pinned memory behind the last interval (whose
+    // epochs were the last conversions, so every one has ended by then): one wait
+    // per call.  (Pageable copies of the two stopped the host twice, 55 us apart.)
+    const size_t h_words = 2 * (size_t)n + M;
+    if (h_words > s->h_res_cap) {
+        if (s->h_res) (void)hipHostFree(s->h_res);
+        s->h_res = nullptr;
+        s->h_res_cap = 0;
+        ST_TRY(hipHostMalloc((void **)&s->h_res, h_words * 8, hipHostMallocDefault), "results");
+        s->h_res_cap = h_words;
+    }
+    unsigned long long *const bad = s->h_res + 2 * (size_t)n;
+    if (sums) ST_TRY(launch_totals(lay.sums(s->acc), n, s->h_res, stream), "totals");
+    if (iv.empty()) ST_TRY(hipStreamSynchronize(s->copy), "sync copy stream");
+    ST_TRY(hipMemcpyAsync(bad, s->err, M * 8, hipMemcpyDeviceToHost, stream), "D2H err");
     ST_TRY(hipStreamSynchronize(stream), "sync");
+    ST_TRY(hipStreamSynchronize(s->copy), "sync copy stream");
+    drain.copy = nullptr;
     for (int32_t e = 0; e < M; e++)
         if (bad[e] != ~0ull) {
             const uint64_t c = bad[e] % ncell;
@@ -429,9 +461,7 @@ extern "C" dart_status dart_streamer_render(dart_streamer *s, dart_dtype src_dty
                         (unsigned long long)((c / rd.n[0]) % rd.n[1]),
                         (unsigned long long)(c / ((uint64_t)rd.n[0] * rd.n[1])));
         }
-    for (int32_t i = 0; sums && i < n; i++)
-        lay.total(acc.data(), i, flux_out ? flux_out + i : nullptr,
-                  steps_out ? steps_out + i : nullptr);
+    if (sums) read_totals(s->h_res, n, flux_out, steps_out);
     s->last.epochs_loaded = (int32_t)order.size();
     s->last.epochs_skipped = M - (int32_t)order.size();
     s->last.intervals = (int32_t)iv.size();
