@@ -141,9 +141,9 @@ dart_status dart_stack_set_epochs(dart_stack *s, int32_t m0, int32_t count, dart
 dart_status dart_free_epochs(dart_stack *s);
 
 /* Emissivity plane.  A plain stack with FP32, FP16 or BF16 records, or with FP64
- * records of more than 256 MiB in all, also keeps its emissivity alone, one value per record at the record's own index (a
- * quarter of the record bytes), packed on the device by the first render
- * after its records change (not inside a stream capture, and by
+ * records of more than 256 MiB in all, also keeps its emissivity alone, one
+ * value per record at the record's own index (a quarter of the record bytes),
+ * packed on the device by the first render after its records change (not inside a stream capture, and by
  * dart_render_batch_noalloc only into a plane already allocated); loads into a
  * stack whose plane is packed keep it in step.  The value's
  * sign bit marks records that must be read whole: any velocity bit set, or a
@@ -156,13 +156,19 @@ dart_status dart_free_epochs(dart_stack *s);
  * are read through 32-bit offsets, larger ones through 64-bit addresses
  * (DART_PLANE_ADDR64 asks for those on any plane).  From its second render on, a
  * labelled stack reads its sub-domains' planes, and a vector stack reads
- * component 0's; streamed windows have none. */
+ * component 0's; streamed windows have none.
+ * Batches and served requests of a plain FP16 or BF16 stack read the plane's values
+ * in pairs, a record's and the next epoch's side by side, once batches of the same
+ * records have walked some 4e9 cells and 16 more per record (half the record bytes,
+ * at most 8 GiB and a sixteenth of the free memory; not views of one epoch per cell,
+ * with DART_EXACT_TIME or DART_PLANE_ADDR64). */
 typedef struct {
     int32_t dims[3];
     int32_t n_epochs;
     dart_dtype storage;
     int32_t brick[3];      /* resident brick shape (cells) */
-    uint64_t device_bytes; /* resident bytes: records, and the emissivity plane once packed */
+    uint64_t device_bytes; /* resident bytes: records, and the emissivity plane (and pairs)
+                              once packed */
 } dart_stack_info;
 dart_status dart_stack_get_info(const dart_stack *s, dart_stack_info *info);
 
@@ -234,9 +240,9 @@ dart_status dart_vector_create(dart_stack *const *components, int32_t n, dart_st
 
 /* Re-lays the resident stack with a new brick shape (powers of two, each
  * 1..16, at most 4096 cells per brick); the current shape returns at once.
- * Uses a second copy of the stack when device memory allows, else (when the
- * epoch size does not change) re-lays one epoch at a time in place through a
- * one-epoch buffer.  If that in-place pass fails part-way the stack reports
+ * Uses a second copy of the stack when it is at most 8 GiB and device memory
+ * allows, else (when the epoch size does not change) re-lays one epoch at a
+ * time in place through a one-epoch buffer.  If that in-place pass fails part-way the stack reports
  * its epochs as unfilled and renders on it return DART_E_INVAL until they are
  * loaded again.  Synchronises the stream. */
 dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3], void *hip_stream);

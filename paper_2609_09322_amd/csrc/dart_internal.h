@@ -17,6 +17,7 @@ enum : uint32_t {
     F_ACCUMULATE = 0x80u,
     F_EXACT = 0x100u,
     F_PLANE32 = 0x1000u,  // the view's emissivity plane is read through 32-bit offsets
+    F_PAIRS = 0x2000u,    // jplane holds pairs: a record's element and the next epoch's
 };
 
 // Resident stack as the kernels see it.  Records (j, bx, by, bz) are stored
@@ -147,6 +148,7 @@ hipError_t launch_plain(const RayView &v, const RenderSums &sums, hipStream_t s)
 enum : int {
     KV_SYNC = 1, KV_LABELLED = 2, KV_EXACT = 4, KV_K8 = 8, KV_VEC = 16, KV_JP = 32,
     KV_JP32 = 64,  // with KV_JP: the plane through 32-bit byte offsets (F_PLANE32; not with 2)
+    KV_PAIRS = 128,  // with KV_JP: the plane as pairs (F_PAIRS; with KV_SYNC and KV_K8 only)
 };
 hipError_t launch_batch(int store, bool f64_dda, int variant, const BatchLaunch &bl,
                         int grid_blocks, hipStream_t s);
@@ -172,6 +174,10 @@ hipError_t launch_pack_j(int store, const void *records, void *out, uint64_t n, 
 // The emissivity plane of n records (StackDev::jplane).
 hipError_t launch_pack_jplane(int store, const void *records, void *out, uint64_t n,
                               hipStream_t s);
+// Pairs of a plane of m epochs of `stride` elements: element i and element i + stride
+// (0 in the last epoch) side by side.  16-bit elements.
+hipError_t launch_pack_pairs(const void *plane, void *out, uint64_t stride, int32_t m,
+                             hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, uint64_t n, unsigned long long value,
                            hipStream_t s);
 // What precedes a render's kernels, in one launch: clears n_clear words, copies

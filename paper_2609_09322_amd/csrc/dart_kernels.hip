@@ -215,6 +215,46 @@ __device__ __forceinline__ typename JFieldT<S>::raw jplane_element(const typenam
     }
 }
 
+// Pairs of 16-bit plane elements (F_PAIRS): word i holds element i and the same
+// cell's of the next epoch, the two that a cell of bracket m reads, so that one
+// load brings both.  What bounds the dense views is the L1's lookups, one per
+// cache line and wave load (22 to 26 of them): a load of pairs touches more lines
+// than one of elements, but there is one of it instead of two.  64 FP16 views of
+// 128^2 to 1024^2 on 32 epochs of 384^3: 8.23 -> 7.15 ms a batch.  (FP32 pairs: four
+// 512^2 views of the jet 438 -> 427 us, which does not pay for 1.5 ms of packing.)
+typedef int v4int __attribute__((ext_vector_type(4)));
+constexpr uint32_t PAIR_MARKS = 0x80008000u;
+
+// llvm.amdgcn.struct.buffer.load: the word at index * stride, both from the
+// descriptor's base and record (0 past its end).
+__device__ uint32_t struct_buffer_load(v4int rsrc, int index, int offset, int soffset, int aux)
+    __asm("llvm.amdgcn.struct.buffer.load.i32");
+
+__device__ __forceinline__ v4int pair_buffer(const StackDev &st) {
+    const uint64_t a = (uint64_t)st.jplane;
+    v4int r;
+    r.x = (int)(uint32_t)a;
+    r.y = (int)(((uint32_t)(a >> 32) & 0xffffu) | 4u << 16);  // (words of 4 bytes)
+    r.z = (int)(uint32_t)(st.epoch_stride * st.n_epochs);      // (fewer than 2^32)
+    r.w = 0x00020000;                                          // (32-bit data, raw)
+    return r;
+}
+// decode_j of the first element, and the difference plane_diff gives for the two
+template <int S>
+__device__ __forceinline__ float pair_first(uint32_t w) {
+    return (float)decode_j<S>((typename JFieldT<S>::raw)w);
+}
+template <int S>
+__device__ __forceinline__ float pair_diff(uint32_t w) {
+    if constexpr (S == ST_F16) {
+        float d;
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(w));
+        return d;
+    } else {
+        return __uint_as_float(w & 0xffff0000u) - __uint_as_float(w << 16);
+    }
+}
+
 // ------------------------------------------------------------------ one ray
 
 // DDA state of one ray.  Per axis the plane crossings ahead of the ray form the
@@ -904,7 +944,9 @@ __device__ __forceinline__ double wave_min(double x) {
 // JP: 0 whole records; 1 the emissivity plane through 64-bit addresses; 2 the
 // plane through 32-bit byte offsets from its start (planes of at most 4 GiB):
 // a cell's offset is one add and a shift, and the elements of its two epochs
-// are loaded at that offset from two wavefront-uniform bases.
+// are loaded at that offset from two wavefront-uniform bases; 3 pairs of 16-bit
+// elements (j_m and j_{m+1} side by side), one load per cell by record index
+// through a structured buffer descriptor, which multiplies the index.
 template <int S, typename R, int SYNC, bool EX, int K, bool VEC, bool SINGLE, int JP>
 __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &st,
                                              const double *centre, int pi, int pj, bool in_image,
@@ -920,12 +962,13 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     // both have the record index space, so one offset serves either.
     using E = typename std::conditional<JP != 0, JF, Raw>::type;
     using GE = const E __attribute__((address_space(1)));
-    constexpr bool O32 = JP == 2;
+    constexpr bool O32 = JP == 2, PAIR = JP == 3;
     // log2 of the element size
     constexpr uint32_t ESH = sizeof(JF) == 2 ? 1u : sizeof(JF) == 4 ? 2u : 3u;
     using GB = const uint8_t __attribute__((address_space(1)));
     // a cell's element: its address, or (O32) its byte offset in the plane
-    using Addr = typename std::conditional<O32, uint32_t, GE *>::type;
+    // (PAIR) its record index
+    using Addr = typename std::conditional<O32 || PAIR, uint32_t, GE *>::type;
     constexpr int NX = VEC ? 3 : 1;  // extra component slots
     if constexpr (VEC) {
 #pragma unroll
@@ -968,15 +1011,17 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     doubled_of(br, dbl);
     // elements of epoch br.m: their address, or (O32) the index of the first
     Addr abase;
-    if constexpr (O32) abase = 0u;
+    if constexpr (O32 || PAIR) abase = 0u;
     else abase = wdata;
+    v4int pairs{};
+    if constexpr (PAIR) pairs = pair_buffer(st);
     Addr ebase = abase + (int64_t)br.m * estride;
     int ebase_m = br.m;
     // (O32) the two epochs' loads: one byte offset from two bases
     GB *pb0 = (GB *)wdata, *pb1 = pb0 + second * (int64_t)sizeof(E);
     auto cell_addr = [&](Addr e) -> Addr {
         if constexpr (O32) return (e + r.off) << ESH;
-        else return e + r.off;
+        else return e + r.off;  // (an index, or an address)
     };
     RaySum<A> sum, xsum[NX];
     const int nx = VEC ? v.n_chan - 1 : 0;
@@ -1114,6 +1159,28 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
             // (16-bit elements held zero-extended, as loaded)
             using QJ = typename std::conditional<sizeof(JF) == 2, uint32_t, JF>::type;
             QJ q0[K], q1[K];
+            if constexpr (PAIR) {
+                uint32_t w[K];
+#pragma unroll
+                for (int k = 0; k < K; k++)
+                    w[k] = struct_buffer_load(pairs, (int)addr[k], 0, 0, 0);
+                uint32_t any_bits = 0u;
+#pragma unroll
+                for (int k = 0; k < K; k++) any_bits |= w[k];
+                if (!__any((any_bits & PAIR_MARKS) != 0u)) {
+#pragma unroll
+                    for (int k = 0; k < K; k++) {
+                        const A val = lerp_d((A)pair_first<S>(w[k]), pair_diff<S>(w[k]), cw[k]);
+                        sum.add(cds[k] * val, kahan);
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int k = 0; k < K; k++) {
+                    q0[k] = (QJ)(w[k] & 0xffffu);
+                    q1[k] = (QJ)(w[k] >> 16);
+                }
+            } else {
 #pragma unroll
             for (int k = 0; k < K; k++) {
                 if constexpr (O32) {
@@ -1142,11 +1209,12 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
                     }
                 }
             }
+            }
             uint32_t any_bits = 0u;
 #pragma unroll
             for (int k = 0; k < K; k++)
                 any_bits |= jplane_bits<S>((JF)q0[k]) | jplane_bits<S>((JF)q1[k]);
-            if (!__any(jplane_mark<S>(any_bits) != 0u)) {
+            if (!PAIR && !__any(jplane_mark<S>(any_bits) != 0u)) {
 #pragma unroll
                 for (int k = 0; k < K; k++) {
                     const A val = lerp_d((A)decode_j<S>((JF)q0[k]), plane_diff<S>(q0[k], q1[k]), cw[k]);
@@ -1177,6 +1245,7 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
                 mk1[k] = jplane_mark<S>(jplane_bits<S>((JF)q1[k])) != 0u;
                 GRaw *ra;
                 if constexpr (O32) ra = gdata + (addr[k] >> ESH);
+                else if constexpr (PAIR) ra = gdata + addr[k];
                 else ra = gdata + (addr[k] - wdata);
                 r0[k] = Raw{};
                 r1[k] = Raw{};
@@ -1312,6 +1381,10 @@ __device__ __forceinline__ double march(const RayView &v, const StackDev &st,
                                         const double *centre, int pi, int pj, bool in_image,
                                         int seg, const ldsdouble *tab, uint32_t &nsteps,
                                         double *ext = nullptr) {
+    // (views that take one epoch per cell never read pairs)
+    if constexpr (JP == 3)
+        return march_walk<S, R, SYNC, EX, K, VEC, false, JP>(v, st, centre, pi, pj, in_image, seg,
+                                                              tab, nsteps, ext);
     // uniform over the launch's view (flags, epoch count): a scalar branch
     if ((v.flags & F_NEAREST) || st.n_epochs == 1)
         return march_walk<S, R, SYNC, EX, K, VEC, true, JP>(v, st, centre, pi, pj, in_image, seg,
@@ -1596,6 +1669,28 @@ __global__ void __launch_bounds__(256) k_pack_jplane(const typename RecT<S>::raw
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x)
         out[i] = jplane_element<S>(rec[i]);
+}
+
+// Pairs (F_PAIRS) of the plane's n elements.  Four per thread and pass where an
+// epoch is a whole number of fours: two 8-byte loads and a 16-byte store (3.6 GB of
+// plane in 2.8 ms, 5.2 TB/s).
+__global__ void __launch_bounds__(256) k_pack_pairs(const uint16_t *__restrict__ plane,
+                                                    uint32_t *__restrict__ out, uint64_t stride,
+                                                    uint64_t n) {
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t at = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (stride % 4 == 0) {
+        for (uint64_t i = at; i < n / 4; i += step) {
+            const uint2 a = ((const uint2 *)plane)[i];
+            const uint2 b = 4 * i + stride < n ? ((const uint2 *)plane)[i + stride / 4]
+                                               : make_uint2(0u, 0u);
+            ((uint4 *)out)[i] = make_uint4((a.x & 0xffffu) | b.x << 16, a.x >> 16 | (b.x & 0xffff0000u),
+                                           (a.y & 0xffffu) | b.y << 16, a.y >> 16 | (b.y & 0xffff0000u));
+        }
+    } else {
+        for (uint64_t i = at; i < n; i += step)
+            out[i] = plane[i] | (i + stride < n ? (uint32_t)plane[i + stride] : 0u) << 16;
+    }
 }
 
 __global__ void __launch_bounds__(256) k_fill_u64(unsigned long long *p, uint64_t n,
@@ -1957,6 +2052,17 @@ hipError_t batch_impl(const BatchLaunch &bl, int variant, int grid_blocks, hipSt
 #undef DART_VEC
         return hipGetLastError();
     }
+    if (variant & KV_PAIRS) {
+        if constexpr (S == ST_F16 || S == ST_BF16) {
+            switch (variant & 7) {
+                case 0: batch_launch_k<S, R, 0, false, false, 3>(bl, k8, grid_blocks, s); break;
+                case 1: batch_launch_k<S, R, 1, false, false, 3>(bl, k8, grid_blocks, s); break;
+                default: return hipErrorInvalidValue;
+            }
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     if ((variant & KV_JP) && (variant & KV_JP32)) {
         switch (variant & 7) {
             case 0: batch_launch_k<S, R, 0, false, false, 2>(bl, k8, grid_blocks, s); break;
@@ -2204,6 +2310,14 @@ hipError_t launch_pack_j(int store, const void *records, void *out, uint64_t n, 
             break;
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_pairs(const void *plane, void *out, uint64_t stride, int32_t m,
+                             hipStream_t s) {
+    const uint64_t n = stride * (uint64_t)m;
+    hipLaunchKernelGGL(k_pack_pairs, dim3(grid_for((n + 3) / 4, 1u << 15)), dim3(256), 0, s,
+                       (const uint16_t *)plane, (uint32_t *)out, stride, n);
     return hipGetLastError();
 }
 

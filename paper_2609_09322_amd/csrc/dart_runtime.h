@@ -58,6 +58,15 @@ struct dart_stack {
     std::atomic<uint64_t> jplane_gen{0};
     std::vector<char> plane_ok;         // epochs whose elements are those of the records
     uint64_t jplane_no_room = 0;        // a generation for which hipMalloc failed
+    // the plane's elements in pairs (F_PAIRS), for batches of a large 16-bit stack
+    // that is rendered again and again; published like the plane
+    void *pairs = nullptr;
+    uint64_t pairs_bytes = 0;
+    std::atomic<uint64_t> pairs_gen{0};
+    uint64_t pairs_no_room = 0;
+    uint64_t walked_gen = 0;            // the generation whose batches `walked` counts
+    double walked = 0;                  // cells walked by them, as refresh_pairs estimates
+    bool tuning_now = false;            // (inside dart_autotune)
     bool vector() const { return !comps.empty(); }
     int channels() const { return comps.empty() ? 1 : (int)comps.size(); }
 };
@@ -72,6 +81,16 @@ dart_status resolve_view(const dart_stack *s, const dart_view *v, RayView *rv);
 // Packs the stack's emissivity plane when it is missing or stale (allocating it
 // only if may_alloc); a stack without one is rendered from whole records.
 dart_status refresh_jplane(const dart_stack *s, hipStream_t stream, bool may_alloc);
+// Counts a batch's rays through the stack and packs its pairs when they are due.
+dart_status refresh_pairs(const dart_stack *s, double rays, hipStream_t stream);
+bool pairs_ready(const dart_stack *s);
+// Rays of a view that pairs serve: views of one epoch per cell, of exact time, of
+// whole records or of 64-bit plane addresses do not read them.
+inline double view_rays(const dart_view &v) {
+    const uint32_t other = DART_NEAREST_EPOCH | DART_EXACT_TIME | DART_RECORDS_ONLY |
+                           DART_NO_KAHAN | DART_PLANE_ADDR64;
+    return (v.flags & other) || v.width < 1 || v.height < 1 ? 0.0 : (double)v.width * v.height;
+}
 bool jplane_ready(const dart_stack *s);
 void note_use(const dart_stack *s, hipStream_t stream);
 std::vector<const dart_stack *> each_stack(const dart_stack *const *stacks, int32_t n);  // once
@@ -92,6 +111,7 @@ struct Group {
     bool exact = false;     // views with exact temporal integration
     bool jp = false;        // views that read their stacks' emissivity planes
     bool jp32 = false;      // ... through 32-bit offsets (planes of at most 4 GiB)
+    bool pairs = false;     // ... as pairs
     std::vector<RayView> views;
     // n_tiles tiles: the queued ones [0, q_begin[n_queues]), then n_clear tiles
     // whose rays all miss the grid (k_finish sets their pixels to 0).  As rows

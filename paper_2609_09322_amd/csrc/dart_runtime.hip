@@ -143,6 +143,18 @@ static void default_brick(int store, int lb[3]) {
 // against 128 / 264 / 360; four 256^2 views of 128^3 x 6 (403 MB) 294 against 349.
 static constexpr uint64_t F64_PLANE_BYTES = 256ull << 20;
 
+// The largest copy that is made of a stack's data where there is a way without: the
+// driver clears memory that goes round, at 28 ms per GB, once the processes on the
+// card have taken all of it, so a larger one costs more there than its use gains.
+static constexpr uint64_t SECOND_COPY_BYTES = 8ull << 30;
+
+static void drop_pairs(dart_stack *s) {
+    s->pairs_gen.store(0, std::memory_order_release);
+    if (s->pairs) (void)hipFree(s->pairs);
+    s->pairs = nullptr;
+    s->pairs_bytes = 0;
+}
+
 static bool jplane_eligible(const dart_stack *s) {
     return s && !s->labelled() && !s->vector() && s->dev.epoch_stride > 0 &&
            (s->dev.store != ST_F64 || s->bytes > F64_PLANE_BYTES);
@@ -452,6 +464,7 @@ extern "C" dart_status dart_free_epochs(dart_stack *s) {
         (void)hipFree((void *)s->dev.data);
         (void)hipFree((void *)s->dev.times);
         if (s->jplane) (void)hipFree(s->jplane);
+        if (s->pairs) (void)hipFree(s->pairs);
     }
     delete s;
     return DART_OK;
@@ -603,9 +616,9 @@ extern "C" dart_status dart_stack_get_info(const dart_stack *s, dart_stack_info 
     }
     info->n_epochs = s->dev.n_epochs;
     info->storage = s->storage;
-    info->device_bytes = s->bytes + s->jplane_bytes;
-    for (const dart_stack *p : s->parts) info->device_bytes += p->jplane_bytes;
-    for (const dart_stack *c : s->comps) info->device_bytes += c->jplane_bytes;
+    info->device_bytes = s->bytes + s->jplane_bytes + s->pairs_bytes;
+    for (const dart_stack *p : s->parts) info->device_bytes += p->jplane_bytes + p->pairs_bytes;
+    for (const dart_stack *c : s->comps) info->device_bytes += c->jplane_bytes + c->pairs_bytes;
     return DART_OK;
 }
 
@@ -684,18 +697,34 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
     if (stack_busy(s)) return fail(DART_E_BUSY, "renders that read this stack are in flight");
     if (lb[0] == s->dev.lb[0] && lb[1] == s->dev.lb[1] && lb[2] == s->dev.lb[2]) return DART_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
+    // (of the old layout: their memory may be the new layout's)
+    if (s->pairs) {
+        std::lock_guard<std::mutex> g(s->mu);
+        drop_pairs(s);
+    }
     dart_stack tmp;
     tmp.dev = s->dev;
     layout(&tmp, lb);
     const uint64_t rb = record_bytes(s->dev.store);
     const uint64_t bytes = tmp.dev.epoch_stride * s->dev.n_epochs * rb;
+    // the plane follows in the same pass when it keeps its size (no render reads it:
+    // the stack is not busy)
+    std::lock_guard<std::mutex> g(s->mu);
+    const bool in_step = plane_in_step(s);
+    void *plane = s->jplane && s->jplane_bytes == plane_bytes(&tmp) && in_step ? s->jplane : nullptr;
+    s->jplane_gen.store(0, std::memory_order_release);
+    const bool same = tmp.dev.epoch_stride == s->dev.epoch_stride && s->dev.n_epochs > 1;
     void *data = nullptr;
-    hipError_t em = hipMalloc(&data, bytes);
-    if (em == hipErrorOutOfMemory && tmp.dev.epoch_stride == s->dev.epoch_stride &&
-        s->dev.n_epochs > 1) {
-        // No room for a second copy: re-lay one epoch at a time through a
-        // one-epoch buffer and copy it back in place (same epoch size).
-        (void)hipGetLastError();
+    hipError_t em = hipErrorOutOfMemory;
+    if (!same || bytes <= SECOND_COPY_BYTES) {
+        em = hipMalloc(&data, bytes);
+        if (em != hipSuccess) (void)hipGetLastError();
+    }
+    if (em == hipErrorOutOfMemory && same) {
+        // Without a second copy: one epoch at a time through a one-epoch buffer,
+        // copied back (32 epochs of 384^3 FP16, 14.5 GB: 18.5 ms, against 13.7
+        // through a second copy of fresh memory and 400 ms more through one that
+        // the driver has to clear).
         const uint64_t eb = s->dev.epoch_stride * rb;
         void *one = nullptr;
         HIP_TRY(hipMalloc(&one, eb), "hipMalloc(rebrick epoch)");
@@ -705,13 +734,15 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
             from.data = (const char *)s->dev.data + (uint64_t)m * eb;
             from.n_epochs = to.n_epochs = 1;
             to.data = one;
-            e = launch_rebrick(s->dev.store, from, to, one, nullptr, stream);
+            e = launch_rebrick(s->dev.store, from, to, one,
+                               plane ? (char *)plane + (uint64_t)m * (eb / 4) : nullptr, stream);
             if (e == hipSuccess)
                 e = hipMemcpyAsync((char *)s->dev.data + (uint64_t)m * eb, one, eb,
                                    hipMemcpyDeviceToDevice, stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         (void)hipFree(one);
+        if (e != hipSuccess || !plane) s->plane_ok.assign(s->plane_ok.size(), 0);
         // a failure part-way leaves epochs in mixed layouts: the stack is unusable
         if (e != hipSuccess) {
             for (int32_t m = 0; m < s->dev.n_epochs; m++) s->filled[m] = false;
@@ -720,18 +751,12 @@ extern "C" dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3],
         }
         tmp.dev.data = s->dev.data;
         s->dev = tmp.dev;
-        s->plane_ok.assign(s->plane_ok.size(), 0);
         s->generation = next_generation();
+        if (plane) s->jplane_gen.store(s->generation, std::memory_order_release);
         return DART_OK;
     }
     HIP_TRY(em, "hipMalloc(rebrick)");
     tmp.dev.data = data;
-    // the plane follows in the same pass when it keeps its size (no render reads it:
-    // the stack is not busy)
-    std::lock_guard<std::mutex> g(s->mu);
-    const bool in_step = plane_in_step(s);
-    void *plane = s->jplane && s->jplane_bytes == plane_bytes(&tmp) && in_step ? s->jplane : nullptr;
-    s->jplane_gen.store(0, std::memory_order_release);
     hipError_t e = launch_rebrick(s->dev.store, s->dev, tmp.dev, data, plane, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess || !plane) s->plane_ok.assign(s->plane_ok.size(), 0);
@@ -1277,6 +1302,72 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
     return DART_OK;
 }
 
+// Pairs are packed once the batches of the same records have walked PAIRS_CELLS cells
+// and PAIRS_AFTER more per record, at (n0 + n1 + n2) / 2 cells a ray.  Reading the
+// plane until then has lost about what packing costs (0.5 ms to allocate and 1.5 ps
+// a record, against 0.05 to 0.2 ps a cell), whatever the views' sizes; records that
+// change with every few batches never come to it.  64 FP16 views of 128^2 to 1024^2
+// on 32 epochs of 384^3 do with their third batch (2.8 ms of packing, 8.23 -> 7.15 ms
+// a batch); 24 served requests of as many sizes on three of 128^3 1.58 -> 1.49 ms,
+// ten calls of a 3-million-cell light curve 879 -> 850 us.  16-bit stacks of fewer
+// than 2^32 records (the index of a buffer load), whose pairs take at most
+// SECOND_COPY_BYTES and little of the memory that is left.
+static constexpr double PAIRS_CELLS = 4e9, PAIRS_AFTER = 16.0;
+
+static bool pairs_eligible(const dart_stack *s) {
+    return jplane_eligible(s) && (s->dev.store == ST_F16 || s->dev.store == ST_BF16) &&
+           s->dev.n_epochs > 1 &&
+           (uint64_t)s->dev.epoch_stride * s->dev.n_epochs < (1ull << 32) &&
+           2 * plane_bytes(s) <= SECOND_COPY_BYTES;
+}
+
+bool dart::pairs_ready(const dart_stack *s) {
+    return pairs_eligible(s) && s->pairs_gen.load(std::memory_order_acquire) == s->generation &&
+           own_plane_ready(s);
+}
+
+dart_status dart::refresh_pairs(const dart_stack *cs, double rays, hipStream_t stream) {
+    if (!pairs_eligible(cs) || !own_plane_ready(cs)) return DART_OK;
+    dart_stack *s = const_cast<dart_stack *>(cs);
+    std::lock_guard<std::mutex> g(s->mu);
+    if (s->tuning_now || s->pairs_gen.load(std::memory_order_relaxed) == s->generation ||
+        s->pairs_no_room == s->generation)
+        return DART_OK;
+    if (s->walked_gen != s->generation) {
+        s->walked_gen = s->generation;
+        s->walked = 0;
+    }
+    s->walked += rays * 0.5 * ((double)s->dev.n[0] + s->dev.n[1] + s->dev.n[2]);
+    if (s->walked < PAIRS_CELLS + PAIRS_AFTER * (double)s->dev.epoch_stride * s->dev.n_epochs)
+        return DART_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
+    if (cap != hipStreamCaptureStatusNone) return DART_OK;
+    const uint64_t need = 2 * plane_bytes(s);
+    if (s->pairs) {
+        // renders still reading the old pairs must finish first
+        HIP_TRY(wait_renders(s), "wait for renders");
+        if (s->pairs_bytes != need) drop_pairs(s);
+    }
+    if (!s->pairs) {
+        size_t room = 0, all = 0;
+        if (hipMemGetInfo(&room, &all) != hipSuccess || need > room / 16 ||
+            hipMalloc(&s->pairs, need) != hipSuccess) {
+            (void)hipGetLastError();  // no room: batches read the plane
+            s->pairs = nullptr;
+            s->pairs_no_room = s->generation;
+            return DART_OK;
+        }
+        s->pairs_bytes = need;
+    }
+    HIP_TRY(launch_pack_pairs(s->jplane, s->pairs, (uint64_t)s->dev.epoch_stride,
+                              s->dev.n_epochs, stream),
+            "pack pairs");
+    HIP_TRY(hipStreamSynchronize(stream), "sync");
+    s->pairs_gen.store(s->generation, std::memory_order_release);
+    return DART_OK;
+}
+
 dart_tuning dart::tuning_for(const dart_stack *s) {
     if (s && s->tuned) return s->tuning;
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -1471,7 +1562,14 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
         if (!images[i]) return fail(DART_E_INVAL, "images[%d] is NULL", i);
         rv.image = images[i];
         rv.acc_index = i;
-        const int key = ((rv.flags & F_PLANE32) ? 128 : 0) + (rv.st.jplane ? 64 : 0) +
+        // two epochs per cell, from pairs where the stack has them
+        if (rv.st.jplane && rv.n_chan == 1 && rv.n_blocks == 0 &&
+            !(rv.flags & (F_NEAREST | F_EXACT)) && !(views[i].flags & DART_PLANE_ADDR64) &&
+            pairs_ready(stacks[i])) {
+            rv.st.jplane = stacks[i]->pairs;
+            rv.flags = (rv.flags & ~F_PLANE32) | F_PAIRS;
+        }
+        const int key = ((rv.flags & F_PAIRS) ? 256 : 0) + ((rv.flags & F_PLANE32) ? 128 : 0) + (rv.st.jplane ? 64 : 0) +
                         rv.st.store * 16 + (rv.n_chan > 1 ? 8 : 0) +
                         ((rv.flags & F_F64_DDA) ? 4 : 0) + (rv.n_blocks > 0 ? 2 : 0) +
                         ((rv.flags & F_EXACT) ? 1 : 0);
@@ -1488,6 +1586,7 @@ dart_status dart::plan_batch(const dart_stack *const *stacks, const dart_view *v
             groups.back().vec = rv.n_chan > 1;
             groups.back().jp = rv.st.jplane != nullptr;
             groups.back().jp32 = (rv.flags & F_PLANE32) != 0;
+            groups.back().pairs = (rv.flags & F_PAIRS) != 0;
         }
         Group &g = groups[it->second];
         std::vector<TileRow> &rows = all_rows[it->second], &clear = all_clear[it->second];
@@ -1738,6 +1837,7 @@ hipError_t dart::enqueue_plan(const std::vector<Group> &groups, const SumLayout 
                                   : (tun.depth_sync > 0 ? KV_SYNC : 0) |
                                         (g.labelled ? KV_LABELLED : 0) | (g.exact ? KV_EXACT : 0) |
                                         (g.jp ? KV_JP : 0) | (g.jp32 ? KV_JP32 : 0) |
+                                        (g.pairs ? KV_PAIRS : 0) |
                                         (tun.cells_per_batch == 8 ? KV_K8 : 0);
         // no more wavefronts than queued tiles: a small batch (one served
         // request of a few hundred tiles) launches only the workgroups its
@@ -1858,6 +1958,10 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     for (const dart_stack *s : each_stack(stacks, n)) {
         dart_status st = refresh_vector(s, stream);
         if (st == DART_OK) st = refresh_jplane(s, stream, true);
+        double rays = 0;
+        for (int32_t i = 0; i < n; i++)
+            if (stacks[i] == s) rays += view_rays(views[i]);
+        if (st == DART_OK) st = refresh_pairs(s, rays, stream);
         if (st != DART_OK) return st;
     }
     const dart_tuning tun = tuning_for(stacks[0]);
@@ -1875,7 +1979,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     for (int32_t i = 0; i < n; i++) {
         put(&stacks[i], sizeof(void *));
         put(&stacks[i]->generation, sizeof(stacks[i]->generation));
-        const uint8_t jp = jplane_ready(stacks[i]) ? 1 : 0;
+        const uint8_t jp = (jplane_ready(stacks[i]) ? 1 : 0) | (pairs_ready(stacks[i]) ? 2 : 0);
         put(&jp, 1);
         put(&views[i], sizeof(dart_view));
         put(&images[i], sizeof(void *));
@@ -2008,6 +2112,19 @@ extern "C" dart_status dart_autotune(dart_stack *const *stacks, const dart_view 
         if (!stacks[i] || (rebrick && (stacks[i]->labelled() || stacks[i]->vector())))
             return fail(DART_E_INVAL, "stacks[%d]: NULL, or labelled with rebrick != 0", i);
     hipStream_t stream = (hipStream_t)hip_stream;
+    // (no candidate's time holds a pack of pairs)
+    struct Tuning {
+        std::vector<const dart_stack *> s;
+        void set(bool on) {
+            for (const dart_stack *p : s) {
+                dart_stack *q = const_cast<dart_stack *>(p);
+                std::lock_guard<std::mutex> g(q->mu);
+                q->tuning_now = on;
+            }
+        }
+        ~Tuning() { set(false); }
+    } tuning{each_stack(stacks, n)};
+    tuning.set(true);
     // scratch device images
     std::vector<dart_view> vv(views, views + n);
     size_t total = 0;

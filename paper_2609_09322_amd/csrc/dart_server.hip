@@ -497,6 +497,7 @@ extern "C" dart_status dart_submit(dart_server *srv, const dart_stack *s, const 
     // (the stack's emissivity plane is packed here, in the caller's thread,
     // when the records changed since it was last packed)
     dart_status st = refresh_jplane(s, nullptr, true);
+    if (st == DART_OK) st = refresh_pairs(s, view_rays(*v), nullptr);
     if (st != DART_OK) return st;
     RayView rv;
     st = resolve_view(s, v, &rv);
