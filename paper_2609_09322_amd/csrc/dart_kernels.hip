@@ -10,7 +10,8 @@
 //   * per cell: chord ds_n = exit - entry, retarded time at the chord midpoint,
 //     epoch pair by a monotone pointer (tbar only decreases along the ray),
 //     linear weight (Eqs. 6-7), two record gathers, D^p per epoch (Eq. 14 with
-//     p = 2 + alpha) and Kahan-compensated accumulation of Eq. 19.
+//     p = 2 + alpha) and compensated accumulation of Eq. 19
+//     (FP32 terms summed in FP64, FP64 terms by Kahan's steps).
 // The same device routine serves the one-launch-per-image kernel and the
 // persistent tile-queue kernel; a MARK instantiation records the (cell, epoch)
 // samples a render touches instead of summing them.
@@ -225,17 +226,21 @@ __device__ __forceinline__ typename JFieldT<S>::raw jplane_element(const typenam
 typedef int v4int __attribute__((ext_vector_type(4)));
 constexpr uint32_t PAIR_MARKS = 0x80008000u;
 
-// llvm.amdgcn.struct.buffer.load: the word at index * stride, both from the
-// descriptor's base and record (0 past its end).
+// llvm.amdgcn.struct.buffer.load: the word `index` of a descriptor's buffer (0 past
+// its end).  The unit multiplies the index by the record size in 32 bits, so a
+// descriptor covers PAIR_WINDOW words, 4 GiB, and pairs of up to 8 GiB have two.
+constexpr uint32_t PAIR_WINDOW = 1u << 30;
 __device__ uint32_t struct_buffer_load(v4int rsrc, int index, int offset, int soffset, int aux)
     __asm("llvm.amdgcn.struct.buffer.load.i32");
 
-__device__ __forceinline__ v4int pair_buffer(const StackDev &st) {
-    const uint64_t a = (uint64_t)st.jplane;
+__device__ __forceinline__ v4int pair_buffer(const StackDev &st, uint32_t first) {
+    const uint64_t a = (uint64_t)st.jplane + 4ull * first;
+    const uint64_t words = (uint64_t)st.epoch_stride * (uint64_t)st.n_epochs;
+    const uint64_t here = words > first ? words - first : 0;
     v4int r;
     r.x = (int)(uint32_t)a;
     r.y = (int)(((uint32_t)(a >> 32) & 0xffffu) | 4u << 16);  // (words of 4 bytes)
-    r.z = (int)(uint32_t)(st.epoch_stride * st.n_epochs);      // (fewer than 2^32)
+    r.z = (int)(uint32_t)(here < PAIR_WINDOW ? here : PAIR_WINDOW);
     r.w = 0x00020000;                                          // (32-bit data, raw)
     return r;
 }
@@ -926,7 +931,7 @@ __device__ __forceinline__ double wave_min(double x) {
 // then takes one piece instead of one cell; a cell counts as one cell-step.
 // (Linear interpolation with lookback only: the host clears EX otherwise.)
 // VEC (vector stacks): the same walk, weights and D^p also integrate the
-// emissivity of components 1..n_chan-1, each with its own compensated sum,
+// emissivity of components 1..n_chan-1, each with its own sum,
 // returned in ext[0..2].
 // SINGLE: one epoch per cell (nearest-epoch mode, or a one-epoch stack), a
 // property of the view and stack, so each lane's walk has no per-cell test.
@@ -1013,8 +1018,11 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
     Addr abase;
     if constexpr (O32 || PAIR) abase = 0u;
     else abase = wdata;
-    v4int pairs{};
-    if constexpr (PAIR) pairs = pair_buffer(st);
+    v4int pairs0{}, pairs1{};
+    if constexpr (PAIR) {
+        pairs0 = pair_buffer(st, 0u);
+        pairs1 = pair_buffer(st, PAIR_WINDOW);
+    }
     Addr ebase = abase + (int64_t)br.m * estride;
     int ebase_m = br.m;
     // (O32) the two epochs' loads: one byte offset from two bases
@@ -1061,7 +1069,9 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
         A cds[K];  // chord, already in the accumulation type
 #pragma unroll
         for (int k = 0; k < K; k++) {
-            addr[k] = abase;  // a valid element for cells not taken in this batch
+            // a valid element for cells not taken in this batch (PAIR: of the
+            // lane's epoch, most likely in the window of the others)
+            addr[k] = PAIR ? ebase : abase;
             cds[k] = (A)0;
             if (take) {
                 const R entry = r.entry;
@@ -1161,9 +1171,31 @@ __device__ __forceinline__ double march_walk(const RayView &v, const StackDev &s
             QJ q0[K], q1[K];
             if constexpr (PAIR) {
                 uint32_t w[K];
+                // The epochs of a wavefront's cells are the same or neighbours, so
+                // nearly always all of a batch is in one window.
+                uint32_t some = 0u, all = ~0u;
 #pragma unroll
-                for (int k = 0; k < K; k++)
-                    w[k] = struct_buffer_load(pairs, (int)addr[k], 0, 0, 0);
+                for (int k = 0; k < K; k++) {
+                    some |= addr[k];
+                    all &= addr[k];
+                }
+                if (!__any(some >= PAIR_WINDOW)) {
+#pragma unroll
+                    for (int k = 0; k < K; k++)
+                        w[k] = struct_buffer_load(pairs0, (int)addr[k], 0, 0, 0);
+                } else if (!__any(all < PAIR_WINDOW)) {
+#pragma unroll
+                    for (int k = 0; k < K; k++)
+                        w[k] = struct_buffer_load(pairs1, (int)(addr[k] - PAIR_WINDOW), 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < K; k++) {
+                        if (addr[k] < PAIR_WINDOW)
+                            w[k] = struct_buffer_load(pairs0, (int)addr[k], 0, 0, 0);
+                        else
+                            w[k] = struct_buffer_load(pairs1, (int)(addr[k] - PAIR_WINDOW), 0, 0, 0);
+                    }
+                }
                 uint32_t any_bits = 0u;
 #pragma unroll
                 for (int k = 0; k < K; k++) any_bits |= w[k];

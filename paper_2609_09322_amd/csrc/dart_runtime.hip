@@ -1309,16 +1309,14 @@ dart_status dart::refresh_jplane(const dart_stack *cs, hipStream_t stream, bool 
 // change with every few batches never come to it.  64 FP16 views of 128^2 to 1024^2
 // on 32 epochs of 384^3 do with their third batch (2.8 ms of packing, 8.23 -> 7.15 ms
 // a batch); 24 served requests of as many sizes on three of 128^3 1.58 -> 1.49 ms,
-// ten calls of a 3-million-cell light curve 879 -> 850 us.  16-bit stacks of fewer
-// than 2^32 records (the index of a buffer load), whose pairs take at most
-// SECOND_COPY_BYTES and little of the memory that is left.
+// ten calls of a 3-million-cell light curve 879 -> 850 us.  16-bit stacks whose pairs
+// take at most SECOND_COPY_BYTES (2^31 words: the two windows of the kernel's
+// descriptors) and little of the memory that is left.
 static constexpr double PAIRS_CELLS = 4e9, PAIRS_AFTER = 16.0;
 
 static bool pairs_eligible(const dart_stack *s) {
     return jplane_eligible(s) && (s->dev.store == ST_F16 || s->dev.store == ST_BF16) &&
-           s->dev.n_epochs > 1 &&
-           (uint64_t)s->dev.epoch_stride * s->dev.n_epochs < (1ull << 32) &&
-           2 * plane_bytes(s) <= SECOND_COPY_BYTES;
+           s->dev.n_epochs > 1 && 2 * plane_bytes(s) <= SECOND_COPY_BYTES;
 }
 
 bool dart::pairs_ready(const dart_stack *s) {
