@@ -305,7 +305,7 @@ dart_status dart_render_batch(const dart_stack *const *stacks, const dart_view *
  * stream once before launching, so it returns after earlier work on the
  * stream has finished; without flux_out / steps_out it returns once the
  * render is enqueued.  A batch whose accumulators and descriptors (2n + 4
- * words per launch group, then 384 bytes per view and 8 per 64-pixel
+ * words per launch group, then 400 bytes per view and 8 per 64-pixel
  * tile) exceed the scratch returns DART_E_INVAL before anything is enqueued.
  * Every call on one GPU shares that GPU's scratch and overwrites what the last
  * call left there: calls on one stream are ordered, but calls that overlap on
