@@ -302,6 +302,9 @@ static dart_status set_epochs_impl(dart_stack *s, int32_t m0, int32_t count, dar
         for (int32_t q = 0; q < count; q++) s->plane_ok[m0 + q] = 0;
         s->jplane_gen.store(0, std::memory_order_release);
     }
+    // From here on the records may be other ones, whatever becomes of this load: what
+    // was made of the old ones (pairs, packed components, plans) is out of date.
+    s->generation = next_generation();
     if (flags & F_DEVICE_PTRS) {
         e = launch_convert(src_f64, s->dev.store, j, beta, m0, count, s->dev, (void *)s->dev.data,
                            plane, err, stream);

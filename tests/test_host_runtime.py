@@ -1,0 +1,63 @@
+"""The host runtime's bookkeeping and order of calls, on a CPU: the library's host
+code against a stand-in for the HIP runtime that reports every call and can make
+one fail (hip_stub).  What cannot be seen in an image, or would need a failing
+allocation or a second GPU to be seen in one, is tested here."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import hip_stub
+from hip_stub import Watch
+
+KV_PAIRS = 128  # (the kernel variant that reads pairs of plane elements)
+DEV = 0x20      # DART_DEVICE_PTRS
+
+
+@pytest.fixture(scope="module")
+def dart():
+    return hip_stub.load()
+
+
+def _stack(dart, store, dims=(8, 8, 8), M=2, load=True):
+    times = np.linspace(-50.0, 50.0, M)
+    st = dart.dart_stack_create(dims, (1, 1, 1), times, store)
+    if load:
+        _fill(dart, st, 0, M)
+    return st
+
+
+def _fill(dart, st, m0, count):
+    """A load from device memory (addresses that the stand-in never reads)."""
+    dart._check(dart._load().dart_stack_set_epochs(st.handle, m0, count, dart.DART_F32, 4096, 8192,
+                                                   DEV, None))
+
+
+def _view(dart, P=32, flags=0, theta=30.0, out=None):
+    return dart.View(theta, 40.0, P, P, 8.0 / P, 0.0, 0.6, flags,
+                     dart.DART_F32 if out is None else out)
+
+
+def _variants(w):
+    return [c[2] or 0 for c in w.of("launch_batch")]
+
+
+def test_failed_refill_leaves_no_pairs(dart):
+    """A refill that ends in DART_E_RANGE has written records: batches read neither
+    the pairs nor plans made of the old ones."""
+    st = _stack(dart, dart.DART_F16)
+    big = [_view(dart, 8192, DEV)] * 2  # 1.6e9 cells each by the pairs' rule
+
+    def batch():
+        with Watch(dart) as w:
+            dart.dart_render_batch([st] * 2, big, [4096, 8192], stats=False)
+        return w
+
+    while not any(v & KV_PAIRS for v in _variants(batch())):
+        pass
+    dart.stub.stub_bad_element(5)
+    with pytest.raises(dart.DartError) as ei:
+        _fill(dart, st, 0, 1)
+    assert ei.value.status == dart.DART_E_RANGE
+    w = batch()
+    assert w.of("launch_pack_jplane") and not any(v & KV_PAIRS for v in _variants(w))
