@@ -21,7 +21,6 @@
 #include <mutex>
 #include <thread>
 #include <unordered_map>
-#include <unordered_set>
 #include <vector>
 
 #include "../../include/dart.h"
@@ -101,6 +100,13 @@ struct Req {
     std::string err_msg;
 };
 
+// A device destination that waves in flight write, and the stream of the last of
+// them (-1: that one has ended).
+struct Dest {
+    int users = 0;
+    int last = -1;
+};
+
 struct Wave {
     std::vector<Req *> reqs;
     int stream_idx = 0;
@@ -134,7 +140,7 @@ struct dart_server {
     Arena dev_arena, host_arena;
     std::mutex mu;
     std::condition_variable cv;
-    std::unordered_set<void *> dests;               // rendered in place by waves in flight
+    std::unordered_map<void *, Dest> dests;         // of the waves in flight
     std::deque<Req *> queue;                        // submitted, waiting for admission / a wave
     std::unordered_map<uint64_t, std::unique_ptr<Req>> reqs;
     std::vector<std::unique_ptr<Wave>> waves;       // in flight
@@ -157,6 +163,14 @@ static void on_wave_done(void *p) {
     w->done = true;
     w->t_done = Clock::now();
     srv->cv.notify_all();
+}
+
+// A request's wave has ended.  Caller holds mu.
+static void leave_dest(dart_server *srv, const Req *r, int stream_idx) {
+    if (r->host_dest) return;
+    auto it = srv->dests.find(r->dest);
+    if (it->second.last == stream_idx) it->second.last = -1;
+    if (--it->second.users == 0) srv->dests.erase(it);
 }
 
 // Frees a finished wave's resources and publishes its results.  Caller holds mu.
@@ -183,7 +197,7 @@ static void retire(dart_server *srv, Wave *w) {
         r->steps = acc_h[n + i];
         if (r->host_dest)
             memcpy(r->dest, (char *)srv->host_base + r->host_off, r->img_bytes);
-        if (r->in_place) srv->dests.erase(r->dest);
+        leave_dest(srv, r, w->stream_idx);
         r->latency_ms =
             std::chrono::duration<double, std::milli>(w->t_done - r->t_submit).count();
         r->state = 3;
@@ -202,7 +216,7 @@ static void fail_wave(dart_server *srv, Wave *w, dart_status st, const std::stri
         r->state = 4;
         r->err = st;
         r->err_msg = msg;
-        if (r->in_place) srv->dests.erase(r->dest);
+        leave_dest(srv, r, w->stream_idx);
         srv->dev_arena.release(r->dev_off, r->img_bytes);
         if (r->host_dest) srv->host_arena.release(r->host_off, r->img_bytes);
         const_cast<dart_stack *>(r->stack)->pinned--;
@@ -268,6 +282,7 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     std::vector<const dart_stack *> stacks(n);
     std::vector<dart_view> views(n);
     std::vector<void *> imgs(n);
+    std::vector<int> behind(n, -1);  // the stream a request's copy waits for
     for (int32_t i = 0; i < n; i++) {
         Req *r = w->reqs[i];
         r->state = 2;
@@ -275,9 +290,14 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         views[i] = r->view;
         views[i].flags |= DART_DEVICE_PTRS;
         // Device destinations are rendered in place (a copy command per request
-        // took about 5 us of the wave's stream each); a destination that another
-        // request in flight also has is staged, so each gets a whole image.
-        r->in_place = !r->host_dest && srv->dests.insert(r->dest).second;
+        // took about 5 us of the wave's stream each).  Where another request in
+        // flight has the same one, the image is staged and copied behind the wave of
+        // that request: two writers at a time would leave parts of both.
+        if (!r->host_dest) {
+            Dest &d = srv->dests[r->dest];
+            r->in_place = d.users++ == 0;
+            behind[i] = d.last;
+        }
         imgs[i] = r->in_place ? r->dest : (void *)((char *)srv->dev_base + r->dev_off);
     }
     dart_tuning tun = tuning_for(stacks[0]);
@@ -321,6 +341,8 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         fail_wave(srv, w.get(), DART_E_INTERNAL, "wave descriptors exceed their buffer");
         return;
     }
+    for (const Req *r : w->reqs)
+        if (!r->host_dest) srv->dests[r->dest].last = sidx;
     srv->stream_busy[sidx] = true;
     srv->stats.waves++;
     if ((uint64_t)n > srv->stats.max_wave_requests) srv->stats.max_wave_requests = n;
@@ -351,8 +373,12 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         if (r->host_dest)
             e = hipMemcpyAsync((char *)srv->host_base + r->host_off, imgs[i], r->img_bytes,
                                hipMemcpyDeviceToHost, stream);
-        else if (!r->in_place)
-            e = hipMemcpyAsync(r->dest, imgs[i], r->img_bytes, hipMemcpyDeviceToDevice, stream);
+        else if (!r->in_place) {
+            // (waves are launched by one thread: that wave's end is recorded)
+            if (behind[i] >= 0) e = hipStreamWaitEvent(stream, srv->ev_end[behind[i]], 0);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(r->dest, imgs[i], r->img_bytes, hipMemcpyDeviceToDevice, stream);
+        }
     }
     // flux and steps overwrite the (already consumed) descriptor staging
     if (e == hipSuccess) e = launch_totals(lay.sums(dacc), n, hstage, stream);

@@ -3,6 +3,7 @@ code against a stand-in for the HIP runtime that reports every call and can make
 one fail (hip_stub).  What cannot be seen in an image, or would need a failing
 allocation or a second GPU to be seen in one, is tested here."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -61,3 +62,68 @@ def test_failed_refill_leaves_no_pairs(dart):
     assert ei.value.status == dart.DART_E_RANGE
     w = batch()
     assert w.of("launch_pack_jplane") and not any(v & KV_PAIRS for v in _variants(w))
+
+
+class _Held:
+    """A server whose waves stay in flight until `finish`."""
+
+    def __init__(self, dart, streams=3):
+        self.dart = dart
+        dart.stub.stub_hold_host_funcs(1)
+        self.srv = dart.dart_server_create(64 << 20, 16, streams)
+        self.tickets = []
+
+    def submit(self, st, view, image):
+        """Sends a request and waits until its wave is on its way."""
+        waves = self.dart.dart_server_get_stats(self.srv).waves
+        t = ctypes.c_uint64(0)
+        v = view.c()
+        self.dart._check(self.dart._load().dart_submit(self.srv.handle, st.handle, ctypes.byref(v),
+                                                       image, ctypes.byref(t)))
+        self.tickets.append(t.value)
+        deadline = time.time() + 20
+        while self.dart.dart_server_get_timeline(self.srv).enqueue_ms == self._enqueued or \
+                self.dart.dart_server_get_stats(self.srv).waves == waves:
+            assert time.time() < deadline
+            time.sleep(1e-3)
+        self._enqueued = self.dart.dart_server_get_timeline(self.srv).enqueue_ms
+
+    _enqueued = 0.0
+
+    def finish(self):
+        self.dart.stub.stub_hold_host_funcs(0)
+        self.dart.stub.stub_run_host_funcs()
+        for t in self.tickets:
+            self.dart.dart_wait(self.srv, t)
+        self.dart.dart_server_destroy(self.srv)
+
+
+def test_requests_with_one_destination_write_it_in_order(dart):
+    """Of the waves in flight with one device destination, the first renders into it
+    and each later one copies behind the one before."""
+    st = _stack(dart, dart.DART_F16)
+    dest, other = 1 << 20, 2 << 20
+    held = _Held(dart)
+    with Watch(dart) as w:
+        for im in (dest, dest, dest):
+            held.submit(st, _view(dart, 32, DEV), im)
+    held.finish()
+    copies = [k for k, c in enumerate(w.calls) if c[0] == "hipMemcpyAsync" and c[1] == dest]
+    assert len(copies) == 2  # (the second and the third)
+    streams = [c[1] for c in w.of("launch_totals")]
+    assert len(set(streams)) == 3
+    ends = {}  # the last event of each wave's stream, behind its copies and totals
+    for k, c in enumerate(w.calls):
+        if c[0] == "launch_totals":
+            ends[c[1]] = next(e[1] for e in w.calls[k:] if e[0] == "hipEventRecord")
+    order = [c[1] for c in w.of("launch_totals")]
+    for n, k in enumerate(copies):
+        mine, before = w.calls[k][2], order[n]
+        assert ("hipStreamWaitEvent", mine, ends[before]) in w.calls[:k]
+    # once they are done the destination is rendered into again
+    held = _Held(dart)
+    with Watch(dart) as w:
+        for im in (dest, other):
+            held.submit(st, _view(dart, 32, DEV), im)
+    held.finish()
+    assert not w.of("hipMemcpyAsync") and not w.of("hipStreamWaitEvent")
