@@ -77,7 +77,8 @@ struct RayView {
     void *image;            // [height][width] float or double (device)
     int32_t out_f64;
     int32_t acc_index;      // slot in the flux / step accumulators
-    int32_t tile_w_log2;    // batched kernel: tile width 1 << tile_w_log2, height 64 >> it
+    int32_t tile_w_log2;    // tile width 1 << tile_w_log2, height 64 >> it (plain kernel: 3, 6 or
+                            // PLAIN_ROWS)
     StackDev st;            // the stack (a labelled stack: its first sub-domain)
     const Block *blocks;    // labelled stack: its sub-domains (device), else null
     int32_t n_blocks;       // 0 for a plain stack
@@ -88,6 +89,8 @@ struct RayView {
     int32_t n_chan;
     const void *chan_data[3];
 };
+
+constexpr int PLAIN_ROWS = 7;  // RayView::tile_w_log2 of k_plain_rows
 
 constexpr int TILE_SEG_SHIFT = 28;  // Tile::view: the view, and above it the depth segment
 constexpr int MAX_SEG_LOG2 = 2;

@@ -818,14 +818,24 @@ static void sincos_deg(double deg, double *s, double *c) {
 // 2 parts) march whole rays.
 constexpr double SEG_WAVES = 7000.0, SEG_CELLS = 8.0;
 
+// The area of the grid's projection on the image plane.
+static double projected_area(const RayView &rv) {
+    double area = 0.0;
+    for (int a = 0; a < 3; a++) {
+        const int b = (a + 1) % 3, c = (a + 2) % 3;
+        area += fabs(rv.shat[a]) * (rv.st.n[b] * rv.st.cell[b]) * (rv.st.n[c] * rv.st.cell[c]);
+    }
+    return area;
+}
+
 static int segments_log2(const dart_stack *s, const RayView &rv) {
     if (s->labelled() || s->interval) return 0;
-    double volume = 1.0, area = 0.0, per_len = 0.0;  // area: of the grid's projection
-    for (int a = 0; a < 3; a++) volume *= rv.st.n[a] * rv.st.cell[a];
+    double volume = 1.0, per_len = 0.0;
     for (int a = 0; a < 3; a++) {
-        area += fabs(rv.shat[a]) * volume / (rv.st.n[a] * rv.st.cell[a]);
+        volume *= rv.st.n[a] * rv.st.cell[a];
         per_len += fabs(rv.shat[a]) / rv.st.cell[a];
     }
+    const double area = projected_area(rv);
     const double rays = std::min((double)rv.width * rv.height, area / (rv.ps * rv.ps));
     const double cells = std::min(volume / area, rv.s_hi - rv.s_lo) * per_len;
     int l = 0;
@@ -1082,6 +1092,42 @@ void dart::read_totals(const void *host, int32_t n, double *flux, uint64_t *step
 
 static constexpr size_t MAPPED_IMAGE = 256u << 10;
 
+// How the plain kernel takes an image (RayView::tile_w_log2).
+//
+// 8 x 8 tiles with their depth segments side by side, but for rays that are sparse in
+// large epochs and whose neighbours along an image row are near in memory, those of
+// the next row far.  There a tile's eight rows, at up to four depths at once, hold so
+// many pages and lines that the reuse along each ray is lost:
+//   64 x 1 tiles, segments side by side, where the rays are few: 256^2 pixels of
+//       300x300x2000 FP16 x 3, 8 cells a pixel 294 -> 103 us (rows of whole rays 191);
+//   rows of pixels, a ray's segments one after the other, up to as many rays as a
+//       wavefront for each SIMD: the same stack's records, 4 cells a pixel 532 -> 228 us;
+//       512x512x1024 BF16, 256^2 pixels 633 -> 364.
+// (More rays than that lose it either way, and the tiles' parallel parts win.)
+constexpr double PLAIN_FAR = 640e3, PLAIN_NEAR = 6e3;   // bytes from a pixel to the next
+constexpr double PLAIN_EPOCH = 256 << 20;               // bytes read of an epoch
+constexpr double PLAIN_FEW = 256.0, PLAIN_MOST = 1024.0;  // wavefronts of rays
+constexpr double PLAIN_CELLS = 4.0;                     // cells a pixel, for few rays
+
+static int plain_tiles(const dart_stack *s, const RayView &rv) {
+    if (s->labelled()) return 3;
+    const double size = record_bytes(rv.st.store) / 4.0 * ((rv.st.jplane ? 1 : 4) + rv.n_chan - 1);
+    const double epoch = size * (double)s->dev.epoch_stride;
+    if (epoch <= PLAIN_EPOCH) return 3;
+    double next = 0.0, up = 0.0, at = size;  // bytes to the next pixel of the row, of the column
+    for (int a = 0; a < 3; a++) {
+        next += fabs(rv.eu[a]) * rv.ps / rv.st.cell[a] * at;
+        up += fabs(rv.ev[a]) * rv.ps / rv.st.cell[a] * at;
+        at *= rv.st.n[a];
+    }
+    if (up <= PLAIN_FAR || next >= PLAIN_NEAR) return 3;
+    const double rays = std::min((double)rv.width * rv.height, projected_area(rv) / (rv.ps * rv.ps));
+    const double cell = cbrt(rv.st.cell[0] * rv.st.cell[1] * rv.st.cell[2]);
+    if (rays <= 64.0 * PLAIN_FEW) return rv.ps > PLAIN_CELLS * cell ? 6 : 3;
+    const bool rows = rv.n_chan == 1 && !(rv.flags & F_EXACT) && epoch > 1.5 * PLAIN_EPOCH;
+    return rows && rays <= 64.0 * PLAIN_MOST ? PLAIN_ROWS : 3;
+}
+
 extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void *image,
                                    double *flux_out, uint64_t *steps_out, void *hip_stream) {
     if (!image) return fail(DART_E_INVAL, "image is NULL");
@@ -1108,7 +1154,7 @@ extern "C" dart_status dart_render(const dart_stack *s, const dart_view *v, void
     if (mapped) HIP_TRY(grow_host(ws->img_host, ws->img_host_cap, MAPPED_IMAGE), "image staging");
     rv.image = dev_img ? image : mapped ? ws->img_host : (void *)ws->img;
     rv.acc_index = 0;
-    rv.tile_w_log2 = 3;
+    rv.tile_w_log2 = plain_tiles(s, rv);
     if (sums) {
         HIP_TRY(grow_host(ws->sums_host, ws->sums_host_cap, 16), "totals");
         HIP_TRY(launch_begin(ws->acc, lay.words(), nullptr, nullptr, 0, nullptr, 0, nullptr, stream),
