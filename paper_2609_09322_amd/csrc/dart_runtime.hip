@@ -2076,8 +2076,6 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         pack_descriptors(groups, ws->stage);
         drop_graph(ws);
         ws->plan_groups.swap(groups);
-        ws->plan_key = key;
-        ws->plan_ready = true;
     }
     const SumLayout lay(n, ws->plan_groups.size());
     const bool sums = flux_out || steps_out;
@@ -2121,9 +2119,11 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
                               : begin_plan(ws->plan_groups, ws->stage, ws->desc, ws->acc, n_clear,
                                            stream);
         if (e == hipSuccess && !replay) e = hipEventRecord(ws->stage_done, stream);
-        if (e != hipSuccess) {
-            drop_graph(ws);  // (no descriptors to replay)
-            return hip_fail(e, "begin");
+        if (e != hipSuccess) return hip_fail(e, "begin");
+        // (a plan is one to replay once its descriptors are on their way)
+        if (!replay) {
+            ws->plan_key.swap(key);
+            ws->plan_ready = true;
         }
         HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles, tun,
                              ws->device, stream),

@@ -127,3 +127,28 @@ def test_requests_with_one_destination_write_it_in_order(dart):
             held.submit(st, _view(dart, 32, DEV), im)
     held.finish()
     assert not w.of("hipMemcpyAsync") and not w.of("hipStreamWaitEvent")
+
+
+def test_failed_call_leaves_no_plan(dart):
+    """A batch that fails between its plan and its descriptors' upload is planned and
+    uploaded again by the next equal call."""
+    st = _stack(dart, dart.DART_F32)
+    n = 24
+    views = [_view(dart, 32, DEV)] * n
+    images = [(k + 1) << 20 for k in range(n)]
+    failed = []
+
+    def answer(name, a, b):
+        if name == "hipHostMalloc" and a == 16 * n and not failed:  # (the totals)
+            failed.append(name)
+            return 2
+        return 0
+
+    with Watch(dart, answer) as w:
+        with pytest.raises(dart.DartError):
+            dart.dart_render_batch([st] * n, views, images)
+    assert failed and not w.of("launch_batch")
+    with Watch(dart) as w:
+        dart.dart_render_batch([st] * n, views, images)
+    begins = [k for k, c in enumerate(w.calls) if c[0] == "launch_begin" and c[1]]
+    assert begins and begins[0] < w.names().index("launch_batch")
