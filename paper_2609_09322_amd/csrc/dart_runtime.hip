@@ -2049,6 +2049,16 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
 #endif
     const bool use_graph = DART_USE_GRAPH && stream != nullptr;
     const bool replay = ws->plan_ready && key == ws->plan_key;
+    const bool sums = flux_out || steps_out;
+    // Not into a capture of the caller's: its replays would read staging and descriptors
+    // that later calls overwrite.
+    if (stream && !(replay && ws->graph_exec[sums ? 1 : 0])) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
+        if (cap != hipStreamCaptureStatusNone)
+            return fail(DART_E_DEVICE, "the stream is under capture, and the batch's descriptors "
+                                       "are shared with later calls on it");
+    }
     if (!replay) {
         std::vector<Group> groups;
         // the plan needs image pointers; host ones are patched after reserve
@@ -2078,7 +2088,6 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         ws->plan_groups.swap(groups);
     }
     const SumLayout lay(n, ws->plan_groups.size());
-    const bool sums = flux_out || steps_out;
     hipGraphExec_t &exec = ws->graph_exec[sums ? 1 : 0];
     size_t n_desc = 0;
     for (const Group &gr : ws->plan_groups) n_desc += gr.views.size();

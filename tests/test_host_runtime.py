@@ -152,3 +152,19 @@ def test_failed_call_leaves_no_plan(dart):
         dart.dart_render_batch([st] * n, views, images)
     begins = [k for k, c in enumerate(w.calls) if c[0] == "launch_begin" and c[1]]
     assert begins and begins[0] < w.names().index("launch_batch")
+
+
+def test_batch_is_refused_under_capture(dart):
+    """A new plan's descriptors are staged by the library: a call on a stream that its
+    caller captures is refused and enqueues nothing, with and without totals."""
+    st = _stack(dart, dart.DART_F32)
+    im = [1 << 20]
+    dart.dart_render_batch([st], [_view(dart, 32, DEV)], im, stream=4096, stats=False)
+    for stats in (False, True):
+        for stream in (4097, 4099):  # (odd: under capture)
+            with Watch(dart) as w:
+                with pytest.raises(dart.DartError) as ei:
+                    dart.dart_render_batch([st], [_view(dart, 32, DEV)], im, stream=stream,
+                                           stats=stats)
+            assert ei.value.status == dart.DART_E_DEVICE
+            assert not {c[0] for c in w.calls} - {"hipStreamIsCapturing"}
