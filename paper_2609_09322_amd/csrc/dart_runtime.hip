@@ -455,14 +455,15 @@ extern "C" dart_status dart_free_epochs(dart_stack *s) {
     if (s->refs.load() > 0)
         return fail(DART_E_BUSY, "the stack is held by %d labelled or vector stack(s)",
                     s->refs.load());
+    // (a load into a part waits for the holders' events: they let go of it first)
+    for (dart_stack *p : s->parts) release(s, p);
+    for (dart_stack *c : s->comps) release(s, c);
     for (auto &u : s->uses) (void)hipEventDestroy(u.second);
     if (s->labelled()) {
         // the grids belong to the sub-domains
         (void)hipFree(s->dev_blocks);
-        for (dart_stack *p : s->parts) release(s, p);
     } else if (s->vector()) {
         (void)hipFree(s->packed);
-        for (dart_stack *c : s->comps) release(s, c);
     } else {
         (void)hipFree((void *)s->dev.data);
         (void)hipFree((void *)s->dev.times);

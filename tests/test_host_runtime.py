@@ -168,3 +168,31 @@ def test_batch_is_refused_under_capture(dart):
                                            stats=stats)
             assert ei.value.status == dart.DART_E_DEVICE
             assert not {c[0] for c in w.calls} - {"hipStreamIsCapturing"}
+
+
+@pytest.mark.parametrize("kind", ["vector", "labelled"])
+def test_holder_freed_beside_a_load(dart, kind):
+    """A load into a part waits for its holders' renders: a holder lets go of its parts
+    before its events end."""
+    parts = [_stack(dart, dart.DART_F32) for _ in range(2)]
+    for k, p in enumerate(parts):
+        dart.dart_stack_set_placement(p, (0, 0, 8 * k if kind == "labelled" else 0), (4, 4, 8))
+    holder = (dart.dart_vector_create if kind == "vector" else dart.dart_labelled_create)(parts)
+    for _ in range(2):  # (the second packs the planes, which loads then keep in step)
+        dart.dart_render_batch([holder], [_view(dart, 32, DEV)], [1 << 20], stats=False)
+    dead = []
+
+    def answer(name, a, b):
+        if name == "hipEventDestroy" and not dead:
+            dead.append(a)
+            _fill(dart, parts[0], 0, 1)  # (another thread's load, just now)
+        if name == "hipEventSynchronize":
+            assert dart.stub.stub_event_alive(a)
+        return 0
+
+    with Watch(dart, answer) as w:
+        dart.dart_free_epochs(holder)
+    assert dead and w.of("launch_convert")
+    assert dead[0] not in [c[1] for c in w.of("hipEventSynchronize")]
+    for p in parts:
+        dart.dart_free_epochs(p)
