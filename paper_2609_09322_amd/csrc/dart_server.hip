@@ -86,6 +86,7 @@ struct Req {
     dart_view view{};
     void *dest = nullptr;
     bool host_dest = false;
+    bool own_mem = false;   // dest is device memory of the server's GPU
     bool in_place = false;  // the wave renders into dest itself
     size_t img_bytes = 0;
     size_t desc_bound = 0;  // upper bound of the request's share of a wave's descriptors
@@ -289,13 +290,13 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
         stacks[i] = r->stack;
         views[i] = r->view;
         views[i].flags |= DART_DEVICE_PTRS;
-        // Device destinations are rendered in place (a copy command per request
+        // Destinations on this GPU are rendered in place (a copy command per request
         // took about 5 us of the wave's stream each).  Where another request in
         // flight has the same one, the image is staged and copied behind the wave of
         // that request: two writers at a time would leave parts of both.
         if (!r->host_dest) {
             Dest &d = srv->dests[r->dest];
-            r->in_place = d.users++ == 0;
+            r->in_place = d.users++ == 0 && r->own_mem;
             behind[i] = d.last;
         }
         imgs[i] = r->in_place ? r->dest : (void *)((char *)srv->dev_base + r->dev_off);
@@ -538,6 +539,13 @@ extern "C" dart_status dart_submit(dart_server *srv, const dart_stack *s, const 
     r->dest = image;
     r->host_dest = !(v->flags & DART_DEVICE_PTRS);
     r->img_bytes = (size_t)v->width * v->height * 4;
+    if (!r->host_dest) {
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, image) == hipSuccess)
+            r->own_mem = at.type == hipMemoryTypeDevice && at.device == srv->device;
+        else
+            (void)hipGetLastError();
+    }
     // any 64-pixel tile shape w x h cuts the image into at most
     // (W/w + 1)(H/h + 1) <= WH/64 + W + H + 1 tiles
     r->desc_bound = sizeof(RayView) + 64 +

@@ -167,7 +167,8 @@ def test_batch_is_refused_under_capture(dart):
                     dart.dart_render_batch([st], [_view(dart, 32, DEV)], im, stream=stream,
                                            stats=stats)
             assert ei.value.status == dart.DART_E_DEVICE
-            assert not {c[0] for c in w.calls} - {"hipStreamIsCapturing"}
+            assert not [c for c in w.calls if c[0].startswith("launch_") or c[0] in
+                        ("hipMemcpyAsync", "hipEventRecord", "hipStreamBeginCapture")]
 
 
 @pytest.mark.parametrize("kind", ["vector", "labelled"])
@@ -196,3 +197,15 @@ def test_holder_freed_beside_a_load(dart, kind):
     assert dead[0] not in [c[1] for c in w.of("hipEventSynchronize")]
     for p in parts:
         dart.dart_free_epochs(p)
+
+
+def test_destination_on_another_gpu_is_copied_to(dart):
+    """Only memory of the server's own GPU is rendered into."""
+    st = _stack(dart, dart.DART_F16)
+    far = 1 << 60  # (the stand-in's second GPU)
+    held = _Held(dart)
+    with Watch(dart) as w:
+        held.submit(st, _view(dart, 32, DEV), far)
+        held.submit(st, _view(dart, 32, DEV), 1 << 20)
+    held.finish()
+    assert [c[1] for c in w.of("hipMemcpyAsync")] == [far]
