@@ -77,6 +77,11 @@ dart_status fail(dart_status st, const char *fmt, ...);
 dart_status hip_fail(hipError_t e, const char *what);
 int device_cus(int dev);
 uint32_t record_bytes(int store);
+// dart_stack_create; rendered: the stack is rendered itself (a streamer's ring is not,
+// and needs no emissivity plane).
+dart_status create_stack(const int32_t dims[3], const double cell[3], int32_t n_epochs,
+                         const double *epoch_times, dart_dtype storage, bool rendered,
+                         dart_stack **out);
 dart_status resolve_view(const dart_stack *s, const dart_view *v, RayView *rv);
 // Packs the stack's emissivity plane when it is missing or stale (allocating it
 // only if may_alloc); a stack without one is rendered from whole records.

@@ -191,10 +191,9 @@ static dart_status check_geometry(const int32_t dims[3], const double cell[3], i
     return DART_OK;
 }
 
-extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cell[3],
-                                         int32_t n_epochs, const double *epoch_times,
-                                         dart_dtype storage, uint32_t flags, dart_stack **out) {
-    (void)flags;
+dart_status dart::create_stack(const int32_t dims[3], const double cell[3], int32_t n_epochs,
+                               const double *epoch_times, dart_dtype storage, bool rendered,
+                               dart_stack **out) {
     if (!out) return fail(DART_E_INVAL, "out is NULL");
     *out = nullptr;
     dart_status st = check_geometry(dims, cell, n_epochs, epoch_times);
@@ -246,7 +245,7 @@ extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cel
     // would cost that one more than it saves); only where it takes little of the
     // memory that is left.
     size_t room = 0, all = 0;
-    if (store == ST_F64 && s->bytes > F64_PLANE_BYTES &&
+    if (rendered && store == ST_F64 && s->bytes > F64_PLANE_BYTES &&
         hipMemGetInfo(&room, &all) == hipSuccess && plane_bytes(s.get()) <= room / 16) {
         if (hipMalloc(&s->jplane, plane_bytes(s.get())) == hipSuccess) {
             s->jplane_bytes = plane_bytes(s.get());
@@ -257,6 +256,13 @@ extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cel
     }
     *out = s.release();
     return DART_OK;
+}
+
+extern "C" dart_status dart_stack_create(const int32_t dims[3], const double cell[3],
+                                         int32_t n_epochs, const double *epoch_times,
+                                         dart_dtype storage, uint32_t flags, dart_stack **out) {
+    (void)flags;
+    return create_stack(dims, cell, n_epochs, epoch_times, storage, true, out);
 }
 
 static hipError_t wait_renders(dart_stack *s);

@@ -82,7 +82,7 @@ extern "C" dart_status dart_streamer_create(const int32_t dims[3], const double 
     std::vector<double> slot_t(ring_epochs);
     for (int32_t k = 0; k < ring_epochs; k++) slot_t[k] = k;
     dart_stack *ring = nullptr;
-    dart_status st = dart_stack_create(dims, cell, ring_epochs, slot_t.data(), storage, 0, &ring);
+    dart_status st = create_stack(dims, cell, ring_epochs, slot_t.data(), storage, false, &ring);
     if (st != DART_OK) return st;
     std::unique_ptr<dart_streamer> s(new dart_streamer);
     s->ring = ring;

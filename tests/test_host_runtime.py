@@ -209,3 +209,19 @@ def test_destination_on_another_gpu_is_copied_to(dart):
         held.submit(st, _view(dart, 32, DEV), 1 << 20)
     held.finish()
     assert [c[1] for c in w.of("hipMemcpyAsync")] == [far]
+
+
+def test_a_streamers_ring_has_no_plane(dart):
+    """A streamed window reads whole records: its FP64 ring is allocated without the
+    emissivity plane that an FP64 stack of its size has."""
+    dims, M = (128, 128, 160), 5
+    times = np.linspace(-50.0, 50.0, M)
+    held = dart.stub.stub_held()
+    sm = dart.dart_streamer_create(dims, (1, 1, 1), times, dart.DART_F64, ring_epochs=4)
+    ring = 4 * int(np.prod(dims)) * 32  # 335 MB
+    assert ring <= dart.stub.stub_held() - held < ring + (1 << 20)
+    dart.dart_streamer_destroy(sm)
+    assert dart.stub.stub_held() == held
+    st = dart.dart_stack_create(dims, (1, 1, 1), times[:4], dart.DART_F64)
+    assert dart.stub.stub_held() - held > ring * 5 // 4
+    dart.dart_free_epochs(st)
