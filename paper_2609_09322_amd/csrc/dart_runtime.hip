@@ -1308,20 +1308,26 @@ static void publish_plane(dart_stack *s) {
 // has them.
 static dart_status refresh_blocks(dart_stack *s, hipStream_t stream, bool may_alloc) {
     if (!s->rendered.exchange(true)) return DART_OK;
-    std::vector<dart_stack *> packed;
-    for (dart_stack *p : s->parts) {
+    for (dart_stack *p : s->parts)
         if (!jplane_eligible(p)) return DART_OK;  // (whole records then)
+    std::vector<dart_stack *> packed;
+    dart_status st = DART_OK;
+    for (size_t k = 0; k < s->parts.size() && st == DART_OK; k++) {
+        dart_stack *p = s->parts[k];
         std::lock_guard<std::mutex> g(p->mu);
         bool pk = false;
-        dart_status st = pack_plane(p, stream, may_alloc, &pk);
-        if (st != DART_OK) return st;
+        st = pack_plane(p, stream, may_alloc, &pk);
         if (pk) packed.push_back(p);
     }
-    if (!packed.empty()) HIP_TRY(hipStreamSynchronize(stream), "sync");
-    for (dart_stack *p : packed) {
-        std::lock_guard<std::mutex> g(p->mu);
-        publish_plane(p);
+    // (those packed before an error are packed all the same)
+    if (!packed.empty()) {
+        HIP_TRY(hipStreamSynchronize(stream), "sync");
+        for (dart_stack *p : packed) {
+            std::lock_guard<std::mutex> g(p->mu);
+            publish_plane(p);
+        }
     }
+    if (st != DART_OK) return st;
     std::lock_guard<std::mutex> g(s->mu);
     std::vector<const void *> planes;
     for (dart_stack *p : s->parts) {

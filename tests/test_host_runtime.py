@@ -225,3 +225,48 @@ def test_a_streamers_ring_has_no_plane(dart):
     st = dart.dart_stack_create(dims, (1, 1, 1), times[:4], dart.DART_F64)
     assert dart.stub.stub_held() - held > ring * 5 // 4
     dart.dart_free_epochs(st)
+
+
+def test_labelled_parts_without_planes_are_not_packed(dart):
+    """Sub-domains one of which has no plane (FP64, at most 256 MiB) are read as whole
+    records: the planes of the others are not packed, call after call, for nothing."""
+    M = 4
+    dart.stub.stub_room(dart.stub.stub_held() + (900 << 20))  # (none at creation either)
+    try:
+        big, small = (_stack(dart, dart.DART_F64, d, M) for d in ((128, 128, 160), (8, 8, 8)))
+    finally:
+        dart.stub.stub_room(256 << 30)
+    for k, p in enumerate((big, small)):
+        dart.dart_stack_set_placement(p, (0, 0, 160 * k), (64, 64, 84))
+    for parts in ((big, small), (small, big)):
+        st = dart.dart_labelled_create(parts)
+        with Watch(dart) as w:
+            for k in range(4):
+                dart.dart_render_batch([st], [_view(dart, 32, DEV, 30.0 + k)], [1 << 20], stats=False)
+        assert len(w.of("launch_batch")) == 4 and not w.of("launch_pack_jplane")
+        dart.dart_free_epochs(st)
+
+
+def test_labelled_planes_packed_before_an_error_are_used(dart):
+    """Planes whose packing was enqueued before a later part's failed are packed once."""
+    parts = [_stack(dart, dart.DART_F32) for _ in range(3)]
+    for k, p in enumerate(parts):
+        dart.dart_stack_set_placement(p, (0, 0, 8 * k), (4, 4, 12))
+    st = dart.dart_labelled_create(parts)
+    packs = []
+
+    def answer(name, a, b):
+        if name == "launch_pack_jplane":
+            packs.append(a)
+            return 1 if len(packs) == 3 else 0
+        return 0
+
+    call = lambda k: dart.dart_render_batch([st], [_view(dart, 32, DEV, 30.0 + k)], [1 << 20],
+                                            stats=False)
+    with Watch(dart, answer):
+        call(0)
+        with pytest.raises(dart.DartError):
+            call(1)
+        call(2)
+        call(3)
+    assert len(packs) == 4 and packs[3] == packs[2] and len(set(packs)) == 3
