@@ -66,7 +66,7 @@ struct dart_stack {
     uint64_t pairs_no_room = 0;
     uint64_t walked_gen = 0;            // the generation whose batches `walked` counts
     double walked = 0;                  // cells walked by them, as refresh_pairs estimates
-    bool tuning_now = false;            // (inside dart_autotune)
+    std::atomic<bool> tuning_now{false};  // (inside dart_autotune)
     bool vector() const { return !comps.empty(); }
     int channels() const { return comps.empty() ? 1 : (int)comps.size(); }
 };

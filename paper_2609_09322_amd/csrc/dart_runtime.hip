@@ -2108,11 +2108,20 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (sums) HIP_TRY(grow_host(ws->sums_host, ws->sums_host_cap, 16 * (size_t)n), "totals");
     const RayView *dviews = (const RayView *)ws->desc;
     const Tile *dtiles = (const Tile *)(ws->desc + n_desc * sizeof(RayView));
+    if (!replay) {
+        hipError_t e = begin_plan(ws->plan_groups, ws->stage, ws->desc, ws->acc, n_clear, stream);
+        if (e == hipSuccess) e = hipEventRecord(ws->stage_done, stream);
+        if (e != hipSuccess) return hip_fail(e, "begin");
+        // (a plan is one to replay once its descriptors are on their way)
+        ws->plan_key.swap(key);
+        ws->plan_ready = true;
+    }
     // A plan's first call launches its kernels one by one; the second captures
     // them, and from then on one graph launch replays them.  (Capturing and
     // instantiating on the first call cost a light curve, whose calls all differ,
-    // 14 of its 130 us per call.)
-    if (use_graph && !exec && replay) {
+    // 14 of its 130 us per call.)  The tuner's first call, which it does not time,
+    // captures: what it times are the replays that its choice is for.
+    if (use_graph && !exec && (replay || stacks[0]->tuning_now)) {
         hipGraph_t graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "begin capture");
         hipError_t e = launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, nullptr, 0, nullptr,
@@ -2136,17 +2145,9 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
     if (exec) {
         HIP_TRY(hipGraphLaunch(exec, stream), "graph launch");
     } else {
-        hipError_t e = replay ? launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, nullptr, 0,
-                                             nullptr, stream)
-                              : begin_plan(ws->plan_groups, ws->stage, ws->desc, ws->acc, n_clear,
-                                           stream);
-        if (e == hipSuccess && !replay) e = hipEventRecord(ws->stage_done, stream);
-        if (e != hipSuccess) return hip_fail(e, "begin");
-        // (a plan is one to replay once its descriptors are on their way)
-        if (!replay) {
-            ws->plan_key.swap(key);
-            ws->plan_ready = true;
-        }
+        if (replay)
+            HIP_TRY(launch_begin(ws->acc, n_clear, nullptr, nullptr, 0, nullptr, 0, nullptr, stream),
+                    "begin");
         HIP_TRY(enqueue_plan(ws->plan_groups, lay, ws->acc, sums, ws->parts, dviews, dtiles, tun,
                              ws->device, stream),
                 "batch kernels");
@@ -2244,7 +2245,7 @@ extern "C" dart_status dart_autotune(dart_stack *const *stacks, const dart_view 
     } else {
         bricks = {{0, 0, 0}};
     }
-    // one warm-up call (plans and captures the graph), then the best of two replays
+    // one warm-up call (plans, and captures the graph), then the best of the replays
     auto measure = [&](const dart_tuning &c, float *ms_out) -> dart_status {
         for (int32_t i = 0; i < n; i++) {
             stacks[i]->tuning = c;

@@ -270,3 +270,29 @@ def test_labelled_planes_packed_before_an_error_are_used(dart):
         call(2)
         call(3)
     assert len(packs) == 4 and packs[3] == packs[2] and len(set(packs)) == 3
+
+
+def test_tuning_times_no_capture(dart):
+    """The replays that the tuner times are graph launches: the graph is captured by the
+    warm-up call, as many calls as there were replays and one."""
+    st = _stack(dart, dart.DART_F32)
+    with Watch(dart) as w:
+        dart.dart_autotune([st], [_view(dart, 32)], stream=4096)
+    # between the two timing events of a replay
+    n = w.names()
+    timed = [k for k, c in enumerate(w.calls) if c[0] == "hipGraphLaunch"]
+    assert len(timed) > 100
+    begin = None
+    for k, c in enumerate(w.calls):
+        if c[0] == "hipEventElapsedTime":
+            end = max(q for q in range(k) if n[q] == "hipEventSynchronize")
+            start = max(q for q in range(end) if n[q] == "hipGraphLaunch")
+            first = max(q for q in range(start) if n[q] == "hipEventRecord")
+            assert "hipGraphInstantiate" not in n[first:end]
+            begin = first
+    assert begin is not None
+    # a tuned stack's next new plan is launched kernel by kernel
+    with Watch(dart) as w:
+        dart.dart_render_batch([st], [_view(dart, 32, DEV, 77.0)], [1 << 20], stream=4096, stats=False)
+    assert "hipGraphInstantiate" not in w.names() and w.of("launch_batch")
+    dart.dart_free_epochs(st)
