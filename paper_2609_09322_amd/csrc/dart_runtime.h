@@ -65,7 +65,7 @@ struct dart_stack {
     std::atomic<uint64_t> pairs_gen{0};
     uint64_t pairs_no_room = 0;
     uint64_t walked_gen = 0;            // the generation whose batches `walked` counts
-    double walked = 0;                  // cells walked by them, as refresh_pairs estimates
+    double walked = 0;                  // cells walked by them, as pairs_due estimates
     std::atomic<bool> tuning_now{false};  // (inside dart_autotune)
     bool vector() const { return !comps.empty(); }
     int channels() const { return comps.empty() ? 1 : (int)comps.size(); }
@@ -86,8 +86,9 @@ dart_status resolve_view(const dart_stack *s, const dart_view *v, RayView *rv);
 // Packs the stack's emissivity plane when it is missing or stale (allocating it
 // only if may_alloc); a stack without one is rendered from whole records.
 dart_status refresh_jplane(const dart_stack *s, hipStream_t stream, bool may_alloc);
-// Counts a batch's rays through the stack and packs its pairs when they are due.
-dart_status refresh_pairs(const dart_stack *s, double rays, hipStream_t stream);
+// Counts a batch's rays through the stack; whether its pairs are due, and packing them.
+bool pairs_due(const dart_stack *s, double rays);
+dart_status pack_pairs(const dart_stack *s, hipStream_t stream);
 bool pairs_ready(const dart_stack *s);
 // Rays of a view that pairs serve: views of one epoch per cell, of exact time, of
 // whole records or of 64-bit plane addresses do not read them.

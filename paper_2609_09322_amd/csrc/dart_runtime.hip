@@ -1386,20 +1386,29 @@ bool dart::pairs_ready(const dart_stack *s) {
            own_plane_ready(s);
 }
 
-dart_status dart::refresh_pairs(const dart_stack *cs, double rays, hipStream_t stream) {
-    if (!pairs_eligible(cs) || !own_plane_ready(cs)) return DART_OK;
+// (caller holds s->mu)
+static bool pairs_wanted(const dart_stack *s) {
+    return !s->tuning_now && s->pairs_gen.load(std::memory_order_relaxed) != s->generation &&
+           s->pairs_no_room != s->generation;
+}
+
+bool dart::pairs_due(const dart_stack *cs, double rays) {
+    if (!pairs_eligible(cs) || !own_plane_ready(cs)) return false;
     dart_stack *s = const_cast<dart_stack *>(cs);
     std::lock_guard<std::mutex> g(s->mu);
-    if (s->tuning_now || s->pairs_gen.load(std::memory_order_relaxed) == s->generation ||
-        s->pairs_no_room == s->generation)
-        return DART_OK;
+    if (!pairs_wanted(s)) return false;
     if (s->walked_gen != s->generation) {
         s->walked_gen = s->generation;
         s->walked = 0;
     }
     s->walked += rays * 0.5 * ((double)s->dev.n[0] + s->dev.n[1] + s->dev.n[2]);
-    if (s->walked < PAIRS_CELLS + PAIRS_AFTER * (double)s->dev.epoch_stride * s->dev.n_epochs)
-        return DART_OK;
+    return s->walked >= PAIRS_CELLS + PAIRS_AFTER * (double)s->dev.epoch_stride * s->dev.n_epochs;
+}
+
+dart_status dart::pack_pairs(const dart_stack *cs, hipStream_t stream) {
+    dart_stack *s = const_cast<dart_stack *>(cs);
+    std::lock_guard<std::mutex> g(s->mu);
+    if (!own_plane_ready(s) || !pairs_wanted(s)) return DART_OK;  // (another thread's, since)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
     if (cap != hipStreamCaptureStatusNone) return DART_OK;
@@ -2021,7 +2030,7 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         double rays = 0;
         for (int32_t i = 0; i < n; i++)
             if (stacks[i] == s) rays += view_rays(views[i]);
-        if (st == DART_OK) st = refresh_pairs(s, rays, stream);
+        if (st == DART_OK && pairs_due(s, rays)) st = pack_pairs(s, stream);
         if (st != DART_OK) return st;
     }
     const dart_tuning tun = tuning_for(stacks[0]);

@@ -125,6 +125,9 @@ struct dart_server {
     size_t budget = 0;
     int max_inflight = 0;
     std::vector<hipStream_t> streams;
+    // pairs of the stacks it serves are packed here (made when some are due)
+    hipStream_t pack = nullptr;
+    std::mutex pack_mu;
     std::vector<bool> stream_busy;
     // per stream: descriptor buffer on the device and its pinned upload staging
     // (also the flux / step readback), fixed at creation and outside the budget
@@ -524,7 +527,6 @@ extern "C" dart_status dart_submit(dart_server *srv, const dart_stack *s, const 
     // (the stack's emissivity plane is packed here, in the caller's thread,
     // when the records changed since it was last packed)
     dart_status st = refresh_jplane(s, nullptr, true);
-    if (st == DART_OK) st = refresh_pairs(s, view_rays(*v), nullptr);
     if (st != DART_OK) return st;
     RayView rv;
     st = resolve_view(s, v, &rv);
@@ -533,6 +535,16 @@ extern "C" dart_status dart_submit(dart_server *srv, const dart_stack *s, const 
     if (s->vector()) return fail(DART_E_INVAL, "the server does not render vector stacks");
     if (v->flags & DART_ACCUMULATE)
         return fail(DART_E_INVAL, "the server does not accept DART_ACCUMULATE");
+    // (not on the null stream, where it would wait for the caller's blocking streams)
+    if (pairs_due(s, view_rays(*v))) {
+        std::lock_guard<std::mutex> g(srv->pack_mu);
+        if (!srv->pack && hipStreamCreateWithFlags(&srv->pack, hipStreamNonBlocking) != hipSuccess) {
+            (void)hipGetLastError();  // (the plane is read as before)
+            srv->pack = nullptr;
+        }
+        if (srv->pack) st = pack_pairs(s, srv->pack);
+        if (st != DART_OK) return st;
+    }
     std::unique_ptr<Req> r(new Req());
     r->stack = s;
     r->view = *v;
@@ -629,6 +641,7 @@ extern "C" dart_status dart_server_destroy(dart_server *srv) {
         (void)hipStreamSynchronize(s);
         (void)hipStreamDestroy(s);
     }
+    if (srv->pack) (void)hipStreamDestroy(srv->pack);
     for (auto *v : {&srv->ev_begin, &srv->ev_kbegin, &srv->ev_kend, &srv->ev_end})
         for (hipEvent_t q : *v) (void)hipEventDestroy(q);
     for (void *q : srv->desc_dev) (void)hipFree(q);

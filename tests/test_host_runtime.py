@@ -296,3 +296,30 @@ def test_tuning_times_no_capture(dart):
         dart.dart_render_batch([st], [_view(dart, 32, DEV, 77.0)], [1 << 20], stream=4096, stats=False)
     assert "hipGraphInstantiate" not in w.names() and w.of("launch_batch")
     dart.dart_free_epochs(st)
+
+
+def test_pairs_of_a_served_stack_are_packed_beside_the_caller(dart):
+    """dart_submit packs due pairs on a stream of the server's, not behind what the
+    caller's blocking streams hold; a request that is refused counts for nothing."""
+    st = _stack(dart, dart.DART_F16, (512, 512, 512))
+    srv = dart.dart_server_create(64 << 20, 4, 1)
+    with Watch(dart) as w:
+        for flags, n in ((DEV | dart.DART_ACCUMULATE, 40), (DEV, 12)):  # 8.05e8 cells each, 8.3e9
+            for k in range(n):                                        # make them due
+                v, t = _view(dart, 1024, flags).c(), ctypes.c_uint64(0)
+                rc = dart._load().dart_submit(srv.handle, st.handle, ctypes.byref(v), 1 << 20,
+                                              ctypes.byref(t))
+                assert (rc == dart.DART_OK) == (flags == DEV)
+                if rc == dart.DART_OK:
+                    dart.dart_wait(srv, t.value)
+            if flags != DEV:
+                assert not w.of("launch_pack_pairs")
+    packs = w.of("launch_pack_pairs")
+    assert len(packs) == 1 and packs[0][2]
+    assert ("hipStreamSynchronize", packs[0][2], None) in w.calls
+    plane = w.names().index("launch_pack_jplane")  # (the plane's own pack is the only other wait)
+    assert [c[1] for c in w.calls[plane:] if c[0] == "hipStreamSynchronize"].count(None) == 1
+    streams = {c[1] for c in w.of("launch_totals")}
+    assert packs[0][2] not in streams
+    dart.dart_server_destroy(srv)
+    dart.dart_free_epochs(st)
