@@ -42,6 +42,7 @@ struct dart_stack {
     std::atomic<int> refs{0};
     std::atomic<bool> rendered{false};       // (labelled) by a call before this one
     std::vector<const void *> block_planes;  // the sub-domains' planes in dev_blocks
+    std::atomic<bool> planes_named{false};   // dev_blocks names every sub-domain's
     std::vector<dart_stack *> holders;       // labelled and vector stacks that hold this one
     bool labelled() const { return !parts.empty(); }
     // vector stack: its components (owned by the caller, counted in refs);

@@ -1244,10 +1244,12 @@ bool dart::jplane_ready(const dart_stack *s) {
     if (!s) return false;
     if (s->vector()) return own_plane_ready(s->comps[0]);
     if (!s->labelled()) return own_plane_ready(s);
-    std::lock_guard<std::mutex> g(const_cast<dart_stack *>(s)->mu);
-    if (s->block_planes.size() != s->parts.size()) return false;
-    for (size_t k = 0; k < s->parts.size(); k++)
-        if (!own_plane_ready(s->parts[k]) || s->parts[k]->jplane != s->block_planes[k]) return false;
+    // (no lock: waves are planned with the server's held, and a refresh may wait for
+    // renders with the stack's.  A sub-domain keeps its layout while it is held, and so
+    // the plane that dev_blocks names.)
+    if (!s->planes_named.load(std::memory_order_acquire)) return false;
+    for (const dart_stack *p : s->parts)
+        if (!own_plane_ready(p)) return false;
     return true;
 }
 
@@ -1339,6 +1341,7 @@ static dart_status refresh_blocks(dart_stack *s, hipStream_t stream, bool may_al
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
     if (cap != hipStreamCaptureStatusNone) return DART_OK;
     for (auto &u : s->uses) HIP_TRY(hipEventSynchronize(u.second), "wait for renders");
+    s->planes_named.store(false, std::memory_order_release);
     s->block_planes.clear();
     std::vector<Block> hb(s->parts.size());
     for (size_t k = 0; k < hb.size(); k++) hb[k] = block_of(s->parts[k]);
@@ -1346,6 +1349,7 @@ static dart_status refresh_blocks(dart_stack *s, hipStream_t stream, bool may_al
                            hipMemcpyHostToDevice, stream), "upload blocks");
     HIP_TRY(hipStreamSynchronize(stream), "sync");
     s->block_planes.swap(planes);
+    s->planes_named.store(true, std::memory_order_release);
     return DART_OK;
 }
 

@@ -3,6 +3,7 @@ code against a stand-in for the HIP runtime that reports every call and can make
 one fail (hip_stub).  What cannot be seen in an image, or would need a failing
 allocation or a second GPU to be seen in one, is tested here."""
 import ctypes
+import threading
 import time
 
 import numpy as np
@@ -323,3 +324,52 @@ def test_pairs_of_a_served_stack_are_packed_beside_the_caller(dart):
     assert packs[0][2] not in streams
     dart.dart_server_destroy(srv)
     dart.dart_free_epochs(st)
+
+
+def test_planning_a_wave_waits_for_no_refresh(dart):
+    """While a caller uploads a labelled stack's planes (and may wait for renders with the
+    stack locked), the server plans a wave of that stack and answers."""
+    parts = [_stack(dart, dart.DART_F32) for _ in range(2)]
+    for k, p in enumerate(parts):
+        dart.dart_stack_set_placement(p, (0, 0, 8 * k), (4, 4, 8))
+    st = dart.dart_labelled_create(parts)
+    plain = _stack(dart, dart.DART_F32)
+    dart.stub.stub_hold_host_funcs(1)
+    srv = dart.dart_server_create(64 << 20, 1, 2)
+    tickets, seen = [], []
+
+    def submit(s):
+        v, t = _view(dart, 32, DEV).c(), ctypes.c_uint64(0)
+        dart._check(dart._load().dart_submit(srv.handle, s.handle, ctypes.byref(v),
+                                             (len(tickets) + 1) << 20, ctypes.byref(t)))
+        tickets.append(t.value)
+
+    def second_wave():
+        while dart.dart_server_get_stats(srv).waves < 2:
+            time.sleep(1e-3)
+        seen.append("planned")
+
+    def answer(name, a, b):
+        if name == "hipMemcpyAsync" and not seen:  # (the blocks, with their planes)
+            seen.append("refreshing")
+            dart.stub.stub_run_host_funcs()  # (the first wave ends: the queued request is next)
+            t = threading.Thread(target=second_wave, daemon=True)
+            t.start()
+            t.join(5.0)
+        return 0
+
+    submit(plain)
+    while dart.dart_server_get_stats(srv).waves < 1:
+        time.sleep(1e-3)
+    submit(st)
+    with Watch(dart, answer):
+        dart.dart_render_batch([st], [_view(dart, 32, DEV)], [5 << 20], stats=False)
+    during = list(seen)
+    dart.stub.stub_hold_host_funcs(0)
+    for _ in range(200):
+        dart.stub.stub_run_host_funcs()
+        time.sleep(1e-3)
+    for t in tickets:
+        dart.dart_wait(srv, t)
+    dart.dart_server_destroy(srv)
+    assert during == ["refreshing", "planned"]
