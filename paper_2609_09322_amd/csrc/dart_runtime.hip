@@ -2028,12 +2028,15 @@ extern "C" dart_status dart_render_batch(const dart_stack *const *stacks, const 
         }
         return DART_OK;
     }
-    for (const dart_stack *s : each_stack(stacks, n)) {
+    std::vector<std::pair<const dart_stack *, double>> seen(n);  // each with its rays
+    for (int32_t i = 0; i < n; i++) seen[i] = {stacks[i], view_rays(views[i])};
+    std::sort(seen.begin(), seen.end());
+    for (size_t k = 0; k < seen.size();) {
+        const dart_stack *s = seen[k].first;
+        double rays = 0;
+        for (; k < seen.size() && seen[k].first == s; k++) rays += seen[k].second;
         dart_status st = refresh_vector(s, stream);
         if (st == DART_OK) st = refresh_jplane(s, stream, true);
-        double rays = 0;
-        for (int32_t i = 0; i < n; i++)
-            if (stacks[i] == s) rays += view_rays(views[i]);
         if (st == DART_OK && pairs_due(s, rays)) st = pack_pairs(s, stream);
         if (st != DART_OK) return st;
     }
