@@ -1502,7 +1502,8 @@ __device__ __forceinline__ void add_sums(const RenderSums &sums, const RayView &
 // the image; dealt along the rows, the few columns of tiles that a narrow grid covers
 // were on as few XCDs.  One image each of 900 (15 stacks from 32^3 to 300x300x3000,
 // 128^2 to 2048^2 pixels): 20% less time in the mean, 1577 -> 1092 us for 512^2 pixels of
-// 300x300x2000 FP16.  An image of less than two rows for each XCD is not dealt.
+// 300x300x2000 FP16.  An image of less than four rows for each XCD is not dealt (128^2
+// pixels: no difference in the mean).
 constexpr uint32_t XCDS = 8;
 struct PlainGrid {
     uint32_t per_row, groups;
@@ -1512,7 +1513,7 @@ struct PlainGrid {
         const uint32_t rows = ((uint32_t)v.height + (1u << hl) - 1u) >> hl;
         const uint32_t gl = 2u - (uint32_t)v.seg_log2;  // (tiles of a workgroup)
         per_row = ((((uint32_t)v.width + (1u << wl) - 1u) >> wl) + (1u << gl) - 1u) >> gl;
-        dealt = rows >= 2u * XCDS;
+        dealt = rows >= 4u * XCDS;
         groups = (dealt ? (rows + XCDS - 1u) / XCDS * XCDS : rows) * per_row;
     }
 };

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 # Cells a pixel: under 4 the tiles are square, or, for 257 to 1024 wavefronts of rays in
 # whole records of these stacks (more than 384 MiB an epoch), rows of pixels; above 4,
 # with fewer rays, 64 x 1.
-IMAGES = [(1, 1), (8, 8), (1, 4099), (4097, 3), (65, 120), (129, 121), (63, 257), (300, 128),
+IMAGES = [(1, 1), (8, 8), (1, 4099), (4097, 3), (65, 120), (129, 121), (63, 257), (300, 128), (40, 249),
           (251, 249), (701, 130)]
 STACKS = {"f64": (230, 240, 235), "f32": (300, 290, 300), "f16": (376, 372, 370),
           "bf16": (376, 372, 370)}
