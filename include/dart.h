@@ -307,6 +307,8 @@ dart_status dart_render_batch(const dart_stack *const *stacks, const dart_view *
  * render is enqueued.  A batch whose accumulators and descriptors (2n + 4
  * words per launch group, then 400 bytes per view and 8 per 64-pixel
  * tile) exceed the scratch returns DART_E_INVAL before anything is enqueued.
+ * Depth segments of small views are marched at once while the scratch left
+ * holds their sums, else one after the other.
  * Every call on one GPU shares that GPU's scratch and overwrites what the last
  * call left there: calls on one stream are ordered, but calls that overlap on
  * one GPU from different streams or host threads race. */

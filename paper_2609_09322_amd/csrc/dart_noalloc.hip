@@ -35,8 +35,8 @@ using namespace dart;
 namespace {
 
 // Accumulators (flux and cell-steps per view, queue heads per launch group),
-// then the view descriptors, then the tile descriptors.  Each GPU holds its
-// own copy until the process ends.
+// then the view descriptors, then the tile descriptors, then the sums of tiles that
+// are queued by depth segment.  Each GPU holds its own copy until the process ends.
 static __device__ __align__(256) unsigned char scratch[DART_NOALLOC_SCRATCH_BYTES];
 
 struct DeviceScratch {
@@ -67,6 +67,21 @@ dart_status scratch_of(int device, DeviceScratch **out) {
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Values of BatchLaunch::parts that the scratch holds beside everything else of these
+// views, whatever their tiles' shapes.  Each 64 of them also bring a tile descriptor.
+// (Segments marched one after the other cost a set-up each: one 128^2 image of 32^3
+// cells took 66 us so, 54 in whole rays.)
+size_t room_for_parts(const dart_view *views, int32_t n) {
+    size_t fixed = align256(SumLayout(n, std::min(n, 64)).words() * 8) + 256;
+    for (int32_t i = 0; i < n; i++) {
+        const size_t w = std::max(views[i].width, 0), h = std::max(views[i].height, 0);
+        // (a 64-pixel tile shape a x b cuts it into at most (w/a + 1)(h/b + 1) tiles)
+        fixed += sizeof(RayView) + (w * h / 64 + w + h + 1) * sizeof(Tile);
+        if (fixed >= DART_NOALLOC_SCRATCH_BYTES) return 0;
+    }
+    return (DART_NOALLOC_SCRATCH_BYTES - fixed) * 64 / (64 * sizeof(double) + sizeof(Tile));
+}
 
 }  // namespace
 
@@ -103,15 +118,21 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     }
     const dart_tuning tun = tuning_for(stacks[0]);
     std::vector<Group> groups;
-    st = plan_batch(stacks, views, n, images, tun, 0, false, groups);
-    if (st != DART_OK) return st;
-    size_t nv = 0, nt = 0;
-    assign_offsets(groups, &nv, &nt);
-    // (a batch that fits only with its sums side by side keeps them so)
-    const size_t desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
-    SumLayout lay(n, groups.size());
-    if (align256(lay.words() * 8) + desc_bytes > (size_t)DART_NOALLOC_SCRATCH_BYTES)
-        lay = SumLayout(n, groups.size(), true);
+    size_t nv = 0, nt = 0, desc_bytes = 0, parts_off = 0;
+    SumLayout lay(n, 0);
+    for (size_t max_parts : {room_for_parts(views, n), (size_t)0}) {
+        st = plan_batch(stacks, views, n, images, tun, max_parts, false, groups);
+        if (st != DART_OK) return st;
+        assign_offsets(groups, &nv, &nt);
+        // (a batch that fits only with its sums side by side keeps them so)
+        desc_bytes = nv * sizeof(RayView) + nt * sizeof(Tile);
+        lay = SumLayout(n, groups.size());
+        if (align256(lay.words() * 8) + desc_bytes > (size_t)DART_NOALLOC_SCRATCH_BYTES)
+            lay = SumLayout(n, groups.size(), true);
+        const size_t parts = parts_of(groups) * sizeof(double);
+        parts_off = align256(align256(lay.words() * 8) + desc_bytes);
+        if (parts == 0 || parts_off + parts <= (size_t)DART_NOALLOC_SCRATCH_BYTES) break;
+    }
     const size_t desc_off = align256(lay.words() * 8);
     if (desc_off + desc_bytes > (size_t)DART_NOALLOC_SCRATCH_BYTES)
         return fail(DART_E_INVAL,
@@ -139,7 +160,8 @@ extern "C" dart_status dart_render_batch_noalloc(const dart_stack *const *stacks
     HIP_TRY_STATUS(launch_begin(acc, sums ? lay.words() : lay.heads_words(), nullptr, nullptr, 0,
                                 nullptr, 0, nullptr, stream),
                    "clear accumulators");
-    HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, nullptr, dviews, dtiles, tun, device, stream),
+    HIP_TRY_STATUS(enqueue_plan(groups, lay, acc, sums, (double *)(sc->ptr + parts_off), dviews,
+                                dtiles, tun, device, stream),
                    "batch kernels");
     note_uses(stacks, n, stream);
     if (sums) {

@@ -259,6 +259,7 @@ hipError_t launch_plain(const RayView &v, const RenderSums &, hipStream_t s) {
 }
 hipError_t launch_batch(int, bool, int variant, const BatchLaunch &bl, int, hipStream_t s) {
     ASK("launch_batch", bl.views, (const void *)(size_t)variant);
+    ASK("launch_batch parts", bl.parts, (const void *)(size_t)bl.n_tiles);
     return ask("launch_batch on", s);
 }
 hipError_t launch_finish(const RayView *, const Tile *, uint32_t, uint32_t, const double *,

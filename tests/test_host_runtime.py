@@ -373,3 +373,18 @@ def test_planning_a_wave_waits_for_no_refresh(dart):
         dart.dart_wait(srv, t)
     dart.dart_server_destroy(srv)
     assert during == ["refreshing", "planned"]
+
+
+def test_noalloc_queues_segments_where_they_fit(dart):
+    """The allocation-free batch marches the depth segments of small views at once, in the
+    scratch that their descriptors leave, and a batch too large for that in sequence."""
+    st = _stack(dart, dart.DART_F32, (64, 64, 64))
+    one = dart.View(30.0, 40.0, 128, 128, 1.0, 0.0, 0.6, DEV)
+    for n, by_segment in ((1, True), (4, True), (20000, False)):
+        images = [(k + 1) << 20 for k in range(n)]
+        view = one if n < 100 else dart.View(30.0, 40.0, 16, 16, 8.0, 0.0, 0.6, DEV)
+        with Watch(dart) as w:
+            dart.dart_render_batch_noalloc([st] * n, [view] * n, images, stats=False)
+        (_, parts, tiles), = w.of("launch_batch parts")
+        assert (parts is not None) == by_segment
+        assert not w.of("hipMalloc")
