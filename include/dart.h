@@ -143,10 +143,11 @@ dart_status dart_free_epochs(dart_stack *s);
 /* Emissivity plane.  A plain stack with FP32, FP16 or BF16 records, or with FP64
  * records of more than 256 MiB in all, also keeps its emissivity alone, one
  * value per record at the record's own index (a quarter of the record bytes),
- * packed on the device by the first render after its records change (not inside a stream capture, and by
- * dart_render_batch_noalloc only into a plane already allocated); loads into a
- * stack whose plane is packed keep it in step.  The value's
- * sign bit marks records that must be read whole: any velocity bit set, or a
+ * packed on the device by the first render after its records change (not inside a
+ * stream capture, and by dart_render_batch_noalloc only into a plane already
+ * allocated); loads into a stack whose plane is packed keep it in step.  An FP64
+ * stack's is allocated with the stack, where it takes at most a sixteenth of the
+ * free memory, and filled by its loads.  The value's sign bit marks records that must be read whole: any velocity bit set, or a
  * negative (or -0) emissivity.  A render reads the plane, and whole records
  * only of the marked elements; a jet's volume at rest is then read at a
  * quarter of the bytes.  Images, flux
@@ -154,9 +155,10 @@ dart_status dart_free_epochs(dart_stack *s);
  * (DART_RECORDS_ONLY).  Without room for the plane (hipMalloc fails) renders
  * read whole records, as do views with DART_NO_KAHAN.  Planes of at most 4 GiB
  * are read through 32-bit offsets, larger ones through 64-bit addresses
- * (DART_PLANE_ADDR64 asks for those on any plane).  From its second render on, a
- * labelled stack reads its sub-domains' planes, and a vector stack reads
- * component 0's; streamed windows have none.
+ * (DART_PLANE_ADDR64 asks for those on any plane).  A vector stack reads component
+ * 0's plane, and from its second render on a labelled stack reads its sub-domains' (if
+ * all of them can have one); streamed windows have none.  The other components'
+ * planes, where there are some, serve renders of those stacks alone.
  * Batches and served requests of a plain FP16 or BF16 stack read the plane's values
  * in pairs, a record's and the next epoch's side by side, once batches of the same
  * records have walked some 4e9 cells and 16 more per record (half the record bytes,
@@ -242,7 +244,8 @@ dart_status dart_vector_create(dart_stack *const *components, int32_t n, dart_st
  * 1..16, at most 4096 cells per brick); the current shape returns at once.
  * Uses a second copy of the stack when it is at most 8 GiB and device memory
  * allows, else (when the epoch size does not change) re-lays one epoch at a
- * time in place through a one-epoch buffer.  If that in-place pass fails part-way the stack reports
+ * time in place through a one-epoch buffer.  If that in-place pass fails part-way the
+ * stack reports
  * its epochs as unfilled and renders on it return DART_E_INVAL until they are
  * loaded again.  Synchronises the stream. */
 dart_status dart_stack_rebrick(dart_stack *s, const int32_t brick[3], void *hip_stream);
@@ -284,7 +287,8 @@ dart_status dart_render(const dart_stack *s, const dart_view *v, void *image, do
  * tile-queue launch per (storage type, precision) group.  Stacks may differ.
  * images[i] follows views[i].flags like dart_render; flux_out[n] and
  * steps_out[n] are nullable host arrays.  A call whose arguments equal those of
- * the previous call on the same stream replays a captured hipGraph. */
+ * the previous call on the same stream replays a captured hipGraph.  A stream that
+ * its caller captures is refused (DART_E_DEVICE). */
 dart_status dart_render_batch(const dart_stack *const *stacks, const dart_view *views, int32_t n,
                               void *const *images, double *flux_out, uint64_t *steps_out,
                               void *hip_stream);
@@ -417,7 +421,8 @@ dart_status dart_count_lines(const dart_stack *s, const dart_view *v, uint64_t *
  * first if it is missing or stale), each sample of positive weight costs one
  * plane value (a quarter of a record) and, when its record carries the
  * read-whole mark, the record as well; without it (DART_RECORDS_ONLY,
- * DART_NO_KAHAN, or no plane) a record.  compulsory_out: those bytes; line_bytes_out: the distinct
+ * DART_NO_KAHAN, or no plane) a record; of a vector stack component 0's records are
+ * counted.  compulsory_out: those bytes; line_bytes_out: the distinct
  * 128-byte lines of the plane and of the records that hold them, times 128.
  * The image bytes are not included.  Either output may be NULL.  Untimed
  * instrumentation, as above. */
@@ -449,7 +454,8 @@ dart_status dart_gather_probe(const void *src, uint64_t bytes, int32_t reps, voi
  * scheduler thread that batches requests as they arrive (continuous batching):
  * every admitted, unfinished request is rendered by the next wave, waves run
  * on several streams and overlap on the device.  Output images for host memory
- * (and device images that another request in flight also has) are staged in
+ * (and device images of another GPU, or that another request in flight also has:
+ * those are written one after the other) are staged in
  * server-owned device memory; admission waits until the staged images of the
  * requests in flight fit in hbm_budget_bytes and fewer than max_inflight are
  * admitted.  Wave descriptors live in per-stream buffers fixed at creation

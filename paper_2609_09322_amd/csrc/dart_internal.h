@@ -70,7 +70,8 @@ struct RayView {
     // consecutive parts of its chord, added in order; which cells a part holds
     // depends on the view and the ray alone.  seg_items: the parts of a tile are
     // queued on their own (their sums meet in BatchLaunch::parts and k_finish
-    // adds them); 0: a lane marches its ray's parts one after the other.  The
+    // adds them); 0: a lane marches its ray's parts one after the other.  (The plain
+    // kernel has its own arrangements, by tile_w_log2.)  The
     // pixels are the same bit for bit.
     int16_t seg_log2, seg_items;
     double sync_gap;        // batched kernel: depth-synchronous horizon (length), 0 = off
@@ -146,8 +147,8 @@ struct BatchLaunch {
 hipError_t launch_plain(const RayView &v, const RenderSums &sums, hipStream_t s);
 // Kernel variant bits: 1 depth-synchronous wavefronts, 2 the launch's views are
 // labelled stacks (block loop), 4 exact temporal integration, 8 eight cells per
-// batch (else four), 16 vector stacks (only alone: no other bit but 8), 32 the
-// views' stacks have an emissivity plane.
+// batch (else four), 16 vector stacks (with 8, 32 and 64 only), 32 the views'
+// stacks have an emissivity plane.
 enum : int {
     KV_SYNC = 1, KV_LABELLED = 2, KV_EXACT = 4, KV_K8 = 8, KV_VEC = 16, KV_JP = 32,
     KV_JP32 = 64,  // with KV_JP: the plane through 32-bit byte offsets (F_PLANE32; not with 2)

@@ -915,7 +915,6 @@ __device__ __forceinline__ double wave_min(double x) {
     return x;
 }
 
-// lo <= s <= hi (lo <= hi, no NaN): in FP32 one median-of-three and a compare.
 // Marching modes (SYNC):
 //   0  each lane walks its own ray, K cells per batch;
 //   1  depth-synchronous wavefront: a batch only takes cells whose entry lies
@@ -1940,8 +1939,8 @@ __device__ __forceinline__ bool valid_record(double jv, double bx, double by, do
 }
 
 // The same answer from FP32 for values far from the limits (true: valid; false:
-// ask valid_record).  A component is rounded by at most 2^-11 (FP16) or 2^-9
-// (BF16) of itself, so beta^2 grows by at most 0.1% or 0.4%; FP16 holds |j| up to
+// ask valid_record).  A component is rounded by at most 2^-11 (FP16) or 2^-8
+// (BF16) of itself, so beta^2 grows by at most 0.1% or 0.8%; FP16 holds |j| up to
 // 65504.
 template <int S>
 __device__ __forceinline__ bool surely_valid(float j, float bx, float by, float bz) {

@@ -168,8 +168,6 @@ dart_status plan_batch(const dart_stack *const *stacks, const dart_view *views, 
 // The launches of a plan share one parts array (they run one after the other).
 size_t parts_of(const std::vector<Group> &groups);
 
-// Per-(device, stream) scratch: accumulators, descriptor arrays, image staging,
-// pinned upload staging and the last captured batch graph.
 // Events that say that kernels have read something (a stack's records, staged
 // descriptors), so that it may be written again: no kernel's output is passed on by
 // them, so they carry no system-scope fence, whose cache write-back delayed the next
@@ -177,6 +175,8 @@ size_t parts_of(const std::vector<Group> &groups);
 // replaced epoch with its render and read-back 377 -> 364 us).
 constexpr unsigned READ_EVENT = hipEventDisableTiming | hipEventDisableSystemFence;
 
+// Per-(device, stream) scratch: accumulators, descriptor arrays, image staging,
+// pinned upload staging and the last captured batch graph.
 struct Workspace {
     hipStream_t stream = nullptr;
     int device = 0;

@@ -133,8 +133,8 @@ static void default_brick(int store, int lb[3]) {
     lb[2] = 1;
 }
 
-// The emissivity plane serves plain stacks (labelled and vector stacks read their
-// parts' records; streamed windows have no plane).  FP64 stacks have one when
+// A plain stack has an emissivity plane (labelled stacks read their sub-domains', vector
+// stacks component 0's; streamed windows have none).  FP64 stacks have one when
 // their records exceed the 256 MB of last-level cache: up to there the records are
 // near already, and a marked element's second, dependent load costs more than the
 // plane's smaller ones save.  One 128^2 / 256^2 / 512^2 image, plane against
@@ -1449,7 +1449,6 @@ dart_tuning dart::tuning_for(const dart_stack *s) {
 
 // ------------------------------------------------------------------ batch planner
 
-// Estimated cell-steps of the ray through the tile centre, times 64 rays.
 // Orientation of a view's tiles (tuning.orient): the tile's long side follows
 // the image-plane projection of the bricks' long axis, so that the lanes of one
 // wave read neighbouring cells of the same cache lines.  True when that turns
@@ -1553,6 +1552,7 @@ static bool band_span(const Footprint &f, double w0, double w1, double *u_lo, do
     return true;
 }
 
+// Estimated cell-steps of the ray through the tile centre, times 64 rays.
 static double tile_cost(const RayView &rv, int tx, int ty, int tw, int th) {
     const double u = ((tx + 0.5) * tw - 0.5 * rv.width) * rv.ps;
     const double w = ((ty + 0.5) * th - 0.5 * rv.height) * rv.ps;

@@ -314,9 +314,8 @@ static void launch_wave(dart_server *srv, std::unique_lock<std::mutex> &lk, int 
     std::vector<Group> groups;
     size_t nv = 0, nt = 0, desc_bytes = 0, acc_off = 0, parts_off = 0;
     SumLayout lay(n, 0);
-    // (tiles queued by depth segment when the buffer holds their parts too)
-    // (and tiles as rows unless those take more staging, as on an image of one
-    // column)
+    // Tiles are queued by depth segment when the buffer holds their parts too, and
+    // planned as rows unless those take more staging, as on an image of one column.
     const size_t values = srv->desc_cap / 8;
     const std::pair<size_t, bool> tries[] = {{values * 3 / 4, true}, {values / 4, true}, {0, true},
                                              {0, false}};
