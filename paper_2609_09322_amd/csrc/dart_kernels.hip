@@ -1496,13 +1496,13 @@ __device__ __forceinline__ void add_sums(const RenderSums &sums, const RayView &
 }
 
 // The workgroups of k_plain: per_row of them a row of tiles, and whether they are
-// dealt to the XCDs by rows (workgroups go to the XCDs in turn).  A row's tiles are
-// then in one XCD, whose L2 its neighbours share, and every XCD has rows from all over
-// the image; dealt along the rows, the few columns of tiles that a narrow grid covers
-// were on as few XCDs.  One image each of 900 (15 stacks from 32^3 to 300x300x3000,
-// 128^2 to 2048^2 pixels): 20% less time in the mean, 1577 -> 1092 us for 512^2 pixels of
-// 300x300x2000 FP16.  An image of less than four rows for each XCD is not dealt (128^2
-// pixels: no difference in the mean).
+// dealt to the XCDs by rows (workgroups go to the XCDs in turn), so that every XCD has
+// rows from all over the image.  Dealt along the rows, the few columns of tiles that a
+// narrow grid covers were on as few XCDs, and a full image's columns were unlike:
+// 512^2 pixels of 512x512x1024 BF16 1725 -> 1087 us though 1269 MB are fetched, not 804;
+// of 300x300x2000 FP16 1577 -> 1092; 20% less time in the mean over one image each of 900
+// views of 15 stacks (32^3 to 300x300x3000, 128^2 to 2048^2 pixels).  An image of less than
+// four rows for each XCD is not dealt (128^2 pixels: no difference in the mean).
 constexpr uint32_t XCDS = 8;
 struct PlainGrid {
     uint32_t per_row, groups;

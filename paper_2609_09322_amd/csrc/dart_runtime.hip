@@ -1103,14 +1103,16 @@ static constexpr size_t MAPPED_IMAGE = 256u << 10;
 //
 // 8 x 8 tiles with their depth segments side by side, but for rays that are sparse in
 // large epochs and whose neighbours along an image row are near in memory, those of
-// the next row far.  There a tile's eight rows, at up to four depths at once, hold so
-// many pages and lines that the reuse along each ray is lost:
-//   64 x 1 tiles, segments side by side, where the rays are few: 256^2 pixels of
-//       300x300x2000 FP16 x 3, 8 cells a pixel 294 -> 103 us (rows of whole rays 191);
+// the next row far.  A load of such a tile touches eight rows' pages, the workgroup's
+// four loads at as many depths, and address translation bounds it: 256^2 pixels of
+// 300x300x2000 FP16 x 3, 8 cells a pixel, take 294 us in 8 x 8 and 98 in 64 x 1 tiles, with
+// the same bytes fetched (150 MB) and the same L2 requests (3.8 and 3.6 million).
+//   64 x 1 tiles, segments side by side, where the rays are few: that view (191 us in
+//       rows of whole rays, before there were segments);
 //   rows of pixels, a ray's segments one after the other, up to as many rays as a
 //       wavefront for each SIMD: the same stack's records, 4 cells a pixel 532 -> 228 us;
 //       512x512x1024 BF16, 256^2 pixels 633 -> 364.
-// (More rays than that lose it either way, and the tiles' parallel parts win.)
+// (With more rays the rows gain in some views and lose more in others: tiles.)
 constexpr double PLAIN_FAR = 640e3, PLAIN_NEAR = 6e3;   // bytes from a pixel to the next
 constexpr double PLAIN_EPOCH = 256 << 20;               // bytes read of an epoch
 constexpr double PLAIN_FEW = 256.0, PLAIN_MOST = 1024.0;  // wavefronts of rays
