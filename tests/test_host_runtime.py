@@ -3,6 +3,7 @@ code against a stand-in for the HIP runtime that reports every call and can make
 one fail (hip_stub).  What cannot be seen in an image, or would need a failing
 allocation or a second GPU to be seen in one, is tested here."""
 import ctypes
+import gc
 import threading
 import time
 
@@ -19,6 +20,12 @@ DEV = 0x20      # DART_DEVICE_PTRS
 @pytest.fixture(scope="module")
 def dart():
     return hip_stub.load()
+
+
+@pytest.fixture(autouse=True)
+def _no_leftovers():
+    """(stacks of the last test are freed before this one counts calls and bytes)"""
+    gc.collect()
 
 
 def _stack(dart, store, dims=(8, 8, 8), M=2, load=True):
